@@ -87,9 +87,14 @@ int make_plan(int64_t n, int32_t nsets, int32_t n_leaf, uint32_t flags, const So
     p->counted = (1u << p->key_passes) - 1u;
   // tiles never straddle two sets: at most one partial tile per set
   p->cell_tiles = (n + kCellTile - 1) / kCellTile + nsets;
-  // chunks of at most kBboxChunk particles of one set: the auto box works chunk
-  // by chunk
-  p->bbox_chunks = (flags & kAutoBoxFlag) ? (n + kBboxChunk - 1) / kBboxChunk + nsets : 1;
+  // the auto box works chunk by chunk of one set: about four workgroups a CU (2^21
+  // particles: 118 us in 31 chunks of 65536, 12 us in 1024 of 2048), the chunks no
+  // smaller than eight particles a thread
+  const int64_t per = (n + 1023) / 1024;
+  p->bbox_chunk = (int32_t)(per < kBboxChunkMin ? kBboxChunkMin
+                                                : per > kBboxChunkMax ? kBboxChunkMax : per);
+  p->bbox_chunks =
+      (flags & kAutoBoxFlag) ? (n + p->bbox_chunk - 1) / p->bbox_chunk + nsets : 1;
   // a set of n_b particles has at most n_b + 21 floor(n_b / (n_leaf + 1)) cells,
   // and the sum over the sets is bounded by the same expression of n
   p->c_max = max_cells(n, n_leaf);
@@ -114,9 +119,7 @@ int make_plan(int64_t n, int32_t nsets, int32_t n_leaf, uint32_t flags, const So
   p->dig = take(p->counted ? ((size_t)n * (sc.bits > 8 ? 2 : 1) + 3) / 4 * 4 : 0);
   p->set_off = take(8 * B1);
   p->box = take(8 * 4 * (size_t)nsets);
-  p->bbox_part = take(8 * 6 * (size_t)p->bbox_chunks);
   p->chunk_start = take(8 * B1);
-  p->chunk_set = take(4 * (size_t)p->bbox_chunks);
   p->tile_start = take(8 * B1);
   p->tile_set = take(4 * (size_t)p->cell_tiles);
   p->cell_cnt = take(4 * (size_t)p->cell_tiles * kLevels);
@@ -131,6 +134,12 @@ int make_plan(int64_t n, int32_t nsets, int32_t n_leaf, uint32_t flags, const So
   p->seg_base = take(p->seg ? 4 * (size_t)nsets * p->key_passes * R : 0);
   p->packed = take(16 * (size_t)n);
   p->sorted = take(16 * (size_t)n);
+  // the boxes are known before the particles are sorted: the chunks' tables lie in
+  // the space of the sorted records (unless empty sets outnumber the particles)
+  const size_t part_bytes = align256(8 * 6 * (size_t)p->bbox_chunks);
+  const size_t set_bytes = align256(4 * (size_t)p->bbox_chunks);
+  p->bbox_part = part_bytes + set_bytes <= 16 * (size_t)n ? p->sorted : take(part_bytes + set_bytes);
+  p->chunk_set = p->bbox_part + part_bytes;
   p->ad = take(2 * (size_t)n);
   if (flags & TB_SUBTREES) {
     p->blk = take((size_t)n);

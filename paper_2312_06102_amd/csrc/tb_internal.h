@@ -41,8 +41,10 @@ constexpr uint32_t kXcds = 8;
 constexpr int kParentThreads = 256;
 constexpr int kParentChunk = kParentThreads;
 
-// Chunks of at most kBboxChunk particles of one set (the auto box).
-constexpr int kBboxChunk = 65536;
+// Chunks of one set's particles, one workgroup each (the auto box): of these many
+// particles at least and at most.
+constexpr int kBboxChunkMin = 2048;
+constexpr int kBboxChunkMax = 65536;
 
 // Largest number of sets in one batch.
 constexpr int kMaxSetsLds = TB_MAX_SETS;
@@ -101,6 +103,7 @@ struct Plan {
                     // (tiles never straddle a set; each set has its own digit bases)
   int64_t sort_tiles;
   int64_t cell_tiles;   // upper bound of the cell tiles of all sets
+  int32_t bbox_chunk;   // particles of a bounding-box chunk
   int64_t bbox_chunks;  // upper bound of the bounding-box chunks of all sets
   int64_t c_max;
   int64_t upper_cap;    // cells above the blocks, per depth: at most n / (n_serial + 1) + B

@@ -36,7 +36,7 @@ __global__ __launch_bounds__(kInitThreads) void k_init(
     int32_t *__restrict__ status_word, int64_t n, int32_t nsets,
     const int64_t *__restrict__ set_off_in, int64_t *__restrict__ set_off,
     const tb_box *__restrict__ boxes_in, double *__restrict__ box, int host_box, double lo0,
-    double lo1, double lo2, double side, int single, int with_chunks,
+    double lo1, double lo2, double side, int single, int chunk,
     int64_t *__restrict__ tile_start,
     int32_t *__restrict__ tile_set, int64_t *__restrict__ chunk_start,
     int32_t *__restrict__ chunk_set) {
@@ -45,15 +45,15 @@ __global__ __launch_bounds__(kInitThreads) void k_init(
   for (int64_t i = tid; i < n_status0; i += stride) status0[i] = 0;
   if (single) {
     // one set given by the host: its tables need no validation or scan (the
-    // chunk table exists only when the box comes from the data)
+    // chunk table exists only when the box comes from the data: chunk > 0)
     const int64_t nt = (n + kCellTile - 1) / kCellTile;
-    const int64_t nc = with_chunks ? (n + kBboxChunk - 1) / kBboxChunk : 0;
+    const int64_t nc = chunk ? (n + chunk - 1) / chunk : 0;
     for (int64_t t = tid; t < nt; t += stride) tile_set[t] = 0;
     for (int64_t c = tid; c < nc; c += stride) chunk_set[c] = 0;
     if (tid == 0) {
       tile_start[0] = 0;
       tile_start[1] = nt;
-      if (with_chunks) {
+      if (chunk) {
         chunk_start[0] = 0;
         chunk_start[1] = nc;
       }
@@ -99,7 +99,7 @@ hipError_t launch_init(const Plan &p, const Work &w, const BatchIn &in, const tb
                                          in.set_off, w.set_off, in.dev_boxes, w.box, hb ? 1 : 0,
                                          hb ? hb->lo[0] : 0.0, hb ? hb->lo[1] : 0.0,
                                          hb ? hb->lo[2] : 0.0, hb ? hb->side : 1.0,
-                                         single_set(p, in) ? 1 : 0, in.auto_box ? 1 : 0,
+                                         single_set(p, in) ? 1 : 0, in.auto_box ? p.bbox_chunk : 0,
                                          w.tile_start, w.tile_set,
                                          w.chunk_start, w.chunk_set);
   return hipGetLastError();
@@ -119,7 +119,7 @@ __device__ __forceinline__ bool box_valid(const double *b) {
 __global__ __launch_bounds__(kSetupThreads) void k_setup(
     int64_t *__restrict__ set_off, int32_t nsets, int64_t n, int64_t *__restrict__ tile_start,
     int64_t *__restrict__ chunk_start, int64_t *__restrict__ sort_tile_start, int sort_tile_keys,
-    int with_chunks, double *__restrict__ box, int check_boxes, int max_set_bits,
+    int chunk, double *__restrict__ box, int check_boxes, int max_set_bits,
     uint32_t *__restrict__ oversize, int32_t *__restrict__ status_word) {
   __shared__ uint32_t s_w[3][kSetupThreads / 64];
   __shared__ uint64_t s_carry[3];
@@ -173,7 +173,7 @@ __global__ __launch_bounds__(kSetupThreads) void k_setup(
     int64_t nb = 0;
     if (b < nsets) nb = set_off[b + 1] - set_off[b];
     const uint32_t nt = (uint32_t)((nb + kCellTile - 1) / kCellTile);
-    const uint32_t nc = with_chunks ? (uint32_t)((nb + kBboxChunk - 1) / kBboxChunk) : 0u;
+    const uint32_t nc = chunk ? (uint32_t)((nb + chunk - 1) / chunk) : 0u;
     const uint32_t ns = sort_tile_start ? (uint32_t)((nb + sort_tile_keys - 1) / sort_tile_keys)
                                         : 0u;
     const uint32_t it = wave_inclusive_scan(nt), ic = wave_inclusive_scan(nc),
@@ -200,7 +200,7 @@ __global__ __launch_bounds__(kSetupThreads) void k_setup(
     os += is - ns;
     if (b < nsets) {
       tile_start[b] = (int64_t)ot;
-      if (with_chunks) chunk_start[b] = (int64_t)oc;
+      if (chunk) chunk_start[b] = (int64_t)oc;
       if (sort_tile_start) sort_tile_start[b] = (int64_t)os;
     }
     __syncthreads();
@@ -213,7 +213,7 @@ __global__ __launch_bounds__(kSetupThreads) void k_setup(
   }
   if (threadIdx.x == 0) {
     tile_start[nsets] = (int64_t)s_carry[0];
-    if (with_chunks) chunk_start[nsets] = (int64_t)s_carry[1];
+    if (chunk) chunk_start[nsets] = (int64_t)s_carry[1];
     if (sort_tile_start) sort_tile_start[nsets] = (int64_t)s_carry[2];
   }
 }
@@ -251,7 +251,7 @@ hipError_t launch_setup(const Plan &p, const Work &w, const BatchIn &in, int32_t
   const bool with_chunks = in.auto_box;
   k_setup<<<1, kSetupThreads, 0, s>>>(w.set_off, p.nsets, p.n, w.tile_start, w.chunk_start,
                                       p.seg ? w.seg_tile_start : nullptr, p.sort.tile(),
-                                      with_chunks ? 1 : 0, w.box, in.dev_boxes ? 1 : 0,
+                                      with_chunks ? p.bbox_chunk : 0, w.box, in.dev_boxes ? 1 : 0,
                                       p.set_index_bits, w.counters + kOversizeCounter, status);
   const int64_t n_counts = p.seg ? (int64_t)p.nsets * p.key_passes * p.sort.radix() : 0;
   const int64_t entries = p.cell_tiles + (with_chunks ? p.bbox_chunks : 0) +
@@ -270,25 +270,37 @@ hipError_t launch_setup(const Plan &p, const Work &w, const BatchIn &in, int32_t
 // ---------------------------------------------------------------------------
 constexpr int kBboxThreads = 256;
 
+// Bound by the latency of its loads: every thread has kBboxIpt particles in flight.
+constexpr int kBboxIpt = 4;
+
 __global__ __launch_bounds__(kBboxThreads) void k_bbox_partial(
     const float *__restrict__ pos, const int64_t *__restrict__ set_off,
     const int64_t *__restrict__ chunk_start, const int32_t *__restrict__ chunk_set,
-    int32_t nsets, double *__restrict__ part) {
+    int32_t nsets, int chunk, double *__restrict__ part) {
   __shared__ double red[6][kBboxThreads / 64];
   const int64_t c = blockIdx.x;
   if (c >= chunk_start[nsets]) return;
   const int b = chunk_set[c];
-  const int64_t i0 = set_off[b] + (c - chunk_start[b]) * (int64_t)kBboxChunk;
-  const int64_t i1 = min(i0 + (int64_t)kBboxChunk, set_off[b + 1]);
+  const int64_t i0 = set_off[b] + (c - chunk_start[b]) * (int64_t)chunk;
+  const int64_t i1 = min(i0 + (int64_t)chunk, set_off[b + 1]);
   double mn[3] = {INFINITY, INFINITY, INFINITY};
   double mx[3] = {-INFINITY, -INFINITY, -INFINITY};
-  for (int64_t i = i0 + threadIdx.x; i < i1; i += kBboxThreads) {
+  for (int64_t i = i0 + threadIdx.x; i < i1; i += kBboxThreads * kBboxIpt) {
+    float v[kBboxIpt][3];
 #pragma unroll
-    for (int a = 0; a < 3; ++a) {
-      double v = (double)pos[3 * i + a];
-      mn[a] = fmin(mn[a], v);
-      mx[a] = fmax(mx[a], v);
+    for (int r = 0; r < kBboxIpt; ++r) {
+      // past the end: this thread's first particle again
+      const int64_t j = i + r * kBboxThreads < i1 ? i + r * kBboxThreads : i;
+#pragma unroll
+      for (int a = 0; a < 3; ++a) v[r][a] = pos[3 * j + a];
     }
+#pragma unroll
+    for (int r = 0; r < kBboxIpt; ++r)
+#pragma unroll
+      for (int a = 0; a < 3; ++a) {
+        mn[a] = fmin(mn[a], (double)v[r][a]);
+        mx[a] = fmax(mx[a], (double)v[r][a]);
+      }
   }
 #pragma unroll
   for (int a = 0; a < 3; ++a) {
@@ -358,7 +370,7 @@ __global__ __launch_bounds__(64) void k_bbox_final(const double *__restrict__ pa
 
 hipError_t launch_bbox(const Plan &p, const Work &w, const float *pos, hipStream_t s) {
   k_bbox_partial<<<(unsigned)p.bbox_chunks, kBboxThreads, 0, s>>>(
-      pos, w.set_off, w.chunk_start, w.chunk_set, p.nsets, w.bbox_part);
+      pos, w.set_off, w.chunk_start, w.chunk_set, p.nsets, p.bbox_chunk, w.bbox_part);
   const int blocks = p.nsets < 4096 ? p.nsets : 4096;
   k_bbox_final<<<blocks, 64, 0, s>>>(w.bbox_part, w.chunk_start, p.nsets, w.box);
   return hipGetLastError();
