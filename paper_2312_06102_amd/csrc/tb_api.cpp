@@ -39,36 +39,48 @@ int make_plan(int64_t n, int32_t nsets, int32_t n_leaf, uint32_t flags, const So
   p->flags = flags;
   p->nsets = nsets;
   p->sort = sc;
-  p->key_passes = sc.passes();
   // A batch sorts every set in place (tiles aligned to the sets, per-set digit
   // bases), so no radix pass over the set id is needed.
   p->seg = nsets > 1;
   // each set starts a tile of its own
   p->sort_tiles = (n + sc.tile() - 1) / sc.tile() + (p->seg ? nsets : 0);
-  // Element formats.  The index needs idx_bits bits; once the key bits still to
-  // be sorted fit beside it in 64 (or 32) bits, key and index travel as one
-  // packed word, so every later pass moves 8 (or 4) bytes an element in and out
-  // instead of 12.  With 8-bit digits and N = 2^24 the third pass writes 40 key
-  // bits + 24 index bits in 8 bytes, and the seventh 8 + 24 bits in 4.
   p->idx_bits = 1;
   while (p->idx_bits < 32 && (int64_t{1} << p->idx_bits) < n) ++p->idx_bits;
   // a batch sorts its sets in place, so an index within the set suffices: the
   // caller may bound the set size (TB_SET_INDEX_BITS), which k_setup checks
   p->set_index_bits = p->seg ? (int)((flags >> 24) & 0x1fu) : 0;
   if (p->set_index_bits > 0 && p->set_index_bits < p->idx_bits) p->idx_bits = p->set_index_bits;
-  // The leading 1 at bit 63 stays in the word (the key kernel's counts of the
-  // last 8-bit digit include it), so key >> consumed bits keeps 64 - consumed bits.
+  // Which key bits the radix passes sort.  Deep enough down the tree hardly two
+  // particles share a cell, so the passes take only the upper 32 or 40 of the 63 key bits, and the reorder, which has every particle's whole key anyway, orders the
+  // particles that agree in those (runs of at most kRunCap; longer ones go through
+  // k_sort_runs).  In the core of a Plummer sphere that spans its box a run holds about
+  // n 2^(18 - bits) particles: mean run (by particle) 3.5 for 2^18 in 32 bits, 1.7 for
+  // 2^24 in 40, and 0.1 % of the particles in runs past 32 for 2^26 clustered ones in
+  // 40.  Data that is denser than that is seen by a sample of the keys, which turns on
+  // the passes over the low bits.  Sort of 2^24
+  // with all that goes with it: 470 us against 788 in all 63 bits.
+  const int64_t typical =
+      p->set_index_bits > 0 ? int64_t{1} << p->set_index_bits : p->seg ? 8 * (n / nsets) : n;
+  const int64_t dense = typical < n ? typical : n;
+  const int sorted_bits = dense <= (int64_t{1} << 18) ? 32 : 40;
+  p->key_passes = (sorted_bits + sc.bits - 1) / sc.bits;
+  // the first pass packs what is left of the key above the index (9-bit digits and more
+  // than 2^28 particles: one pass less)
+  if ((p->key_passes - 1) * sc.bits + p->idx_bits > 64) --p->key_passes;
+  p->skip_bits = 63 - p->key_passes * sc.bits;
+  // (at least two: they leave and return to one array)
+  p->low_passes = (p->skip_bits + sc.bits - 1) / sc.bits;
+  if (p->low_passes < 2) p->low_passes = 2;
+  // Element formats.  The first pass reads 64-bit keys and packs the key bits still to
+  // be sorted above the index in one 64-bit word (at most 32 + 31 bits with 8-bit digits);
+  // once they fit in 32 bits the word has 32.  With N = 2^24 the passes move 8 + 8, 8 + 8,
+  // 8 + 8, 8 + 4 and 4 + 4 bytes an element in and out.
   p->form[0] = kFormKey64;
   for (int k = 0; k < p->key_passes; ++k) {
-    const int rem = 64 - (k + 1) * sc.bits;  // bits of key >> consumed bits after pass k
-    if (k + 1 == p->key_passes)
-      p->form[k + 1] = kFormIdx;
-    else if (rem + p->idx_bits <= 32)
-      p->form[k + 1] = kFormPack32;
-    else if (rem + p->idx_bits <= 64)
-      p->form[k + 1] = kFormPack64;
-    else
-      p->form[k + 1] = kFormKey64;
+    const int rem = 63 - p->skip_bits - (k + 1) * sc.bits;  // key bits left after pass k
+    p->form[k + 1] = k + 1 == p->key_passes                  ? kFormIdx
+                     : k > 0 && rem + p->idx_bits <= 32 ? kFormPack32
+                                                             : kFormPack64;
   }
   // The passes of a single set with at least kCountedMinTiles tiles count their
   // tiles' digits first (reduce, then scan) instead of chaining the tiles
@@ -98,7 +110,7 @@ int make_plan(int64_t n, int32_t nsets, int32_t n_leaf, uint32_t flags, const So
   // a set of n_b particles has at most n_b + 21 floor(n_b / (n_leaf + 1)) cells,
   // and the sum over the sets is bounded by the same expression of n
   p->c_max = max_cells(n, n_leaf);
-  const int P = p->key_passes, R = sc.radix();
+  const int P = p->key_passes + p->low_passes, R = sc.radix();
   const size_t B1 = (size_t)nsets + 1;
   size_t off = 0;
   auto take = [&](size_t bytes) {
@@ -131,7 +143,7 @@ int make_plan(int64_t n, int32_t nsets, int32_t n_leaf, uint32_t flags, const So
   p->par_start = take(8 * (size_t)kLevels * B1);
   p->seg_tile_start = take(p->seg ? 8 * B1 : 0);
   p->seg_tile_set = take(p->seg ? 4 * (size_t)p->sort_tiles : 0);
-  p->seg_base = take(p->seg ? 4 * (size_t)nsets * p->key_passes * R : 0);
+  p->seg_base = take(p->seg ? 4 * (size_t)nsets * P * R : 0);
   p->packed = take(16 * (size_t)n);
   p->sorted = take(16 * (size_t)n);
   // the boxes are known before the particles are sorted: the chunks' tables lie in
@@ -313,9 +325,11 @@ static int build_impl(const float *pos, const float *mass, int64_t n, int32_t ns
   if (in.auto_box) run("bbox", [&] { return launch_bbox(p, w, pos, s); });
   run("keygen", [&] { return launch_keygen(p, w, pos, mass, *out, s); });
   run("hist_reduce", [&] { return launch_hist_reduce(p, w, s); });
+  run("sort_low", [&] { return launch_low_passes(p, w, *out, s); });
   for (int pass = 0; pass < p.key_passes; ++pass)
     run("sort_pass", [&] { return launch_sort_pass(p, w, pass, *out, s); });
   run("reorder", [&] { return launch_reorder(p, w, *out, s); });
+  run("runs", [&] { return launch_runs(p, w, *out, s); });
   run("cell_scan", [&] { return launch_cell_scan(p, w, *out, cell_offsets, s); });
   if (flags & TB_SUBTREES) {
     run("blocks", [&] { return launch_blocks(p, w, s); });

@@ -38,23 +38,62 @@ constexpr int kMaxSpan = (kCellTile + TB_MAX_NLEAF + kCellThreads - 1) / kCellTh
 
 __host__ __device__ constexpr size_t round16(size_t x) { return (x + 15) & ~size_t(15); }
 
+// Particles of the reorder's window: the tile, the n_leaf + 1 before and n_leaf after
+// it, and kRunCap more on either side.
+__host__ __device__ constexpr int window_size(int tile, int nl) {
+  return tile + 2 * nl + 1 + 2 * kRunCap;
+}
+// The window's particles a thread gathers at once; up to this many its thread keeps
+// them (n_leaf <= 95), larger windows are gathered twice.
+constexpr int kWindowIpt = kCellIpt + 1;
+__host__ __device__ constexpr bool window_kept(int nl) {
+  return window_size(kCellTile, nl) <= kWindowIpt * kCellThreads;
+}
+
 // Shared layout of the reorder pass (dynamic LDS, sized for the actual n_leaf).
 struct WindowLds {
-  uint64_t *keys;  // [T + 2 NL + 1]  keys of [t0 - NL - 1, t1 + NL)
+  uint64_t *raw;   // [window]        keys in the order the radix passes left; the window's
+                   //                 place of each particle (u16) after them if not kept
+  uint16_t *place;
+  uint64_t *fin;   // [window]        keys in their final order (the same array if kept)
+  uint64_t *heads; // [window / 64]   where the window's runs start, a word of ones before
+                   //                 and after them
+  uint64_t *keys;  // [T + 2 NL + 1]  the final keys of [t0 - NL - 1, t1 + NL)
   uint8_t *m;      // [T + NL]        w_j, then the sparse max table, j in [t0 - NL, t1)
   uint8_t *a;      // [T + NL]        a_i, i in [t0, t1 + NL)
   uint32_t *wtot;  // [kWaves][kLevelWords]
 };
 
+__host__ __device__ inline size_t window_keys_bytes(int nl) {
+  return round16((size_t)window_size(kCellTile, nl) * 8);
+}
+
+// (rows of kCellThreads particles, kWaves words each)
+__host__ __device__ inline size_t window_heads_bytes(int nl) {
+  const int rows = (window_size(kCellTile, nl) + kCellThreads - 1) / kCellThreads;
+  return round16((size_t)(rows * kWaves + 2) * 8);
+}
+
 __host__ __device__ inline size_t window_lds_bytes(int nl) {
-  return round16((size_t)(kCellTile + 2 * nl + 1) * 8) + 2 * round16(kCellTile + nl) +
-         (size_t)kWaves * kLevelWords * 4;
+  const size_t keys = window_keys_bytes(nl);
+  return window_heads_bytes(nl) + keys + (window_kept(nl) ? 0 : keys + round16((size_t)window_size(kCellTile, nl) * 2)) +
+         2 * round16(kCellTile + nl) + (size_t)kWaves * kLevelWords * 4;
 }
 
 __device__ inline WindowLds carve_window(unsigned char *base, int nl) {
   WindowLds s;
-  s.keys = reinterpret_cast<uint64_t *>(base);
-  base += round16((size_t)(kCellTile + 2 * nl + 1) * 8);
+  s.raw = s.fin = reinterpret_cast<uint64_t *>(base);
+  s.place = nullptr;
+  base += window_keys_bytes(nl);
+  if (!window_kept(nl)) {
+    s.fin = reinterpret_cast<uint64_t *>(base);
+    base += window_keys_bytes(nl);
+    s.place = reinterpret_cast<uint16_t *>(base);
+    base += round16((size_t)window_size(kCellTile, nl) * 2);
+  }
+  s.keys = s.fin + kRunCap;
+  s.heads = reinterpret_cast<uint64_t *>(base);
+  base += window_heads_bytes(nl);
   s.m = base;
   base += round16(kCellTile + nl);
   s.a = base;
@@ -190,79 +229,254 @@ __device__ inline void depths_from_window(const WindowLds &s, int64_t S, int64_t
 // set), which gives it the key window of the leaf-depth formula: it stores
 // a_i | D_i << 8 for every particle of the tile and the tile's cell count per
 // depth.  Every thread issues all of a batch's index loads, then all of its
-// gathers, so the random reads overlap.  Also fills the optional pos_sorted /
-// mass_sorted / key_sorted outputs and checks the masses.
-__global__ __launch_bounds__(kCellThreads) void k_reorder(
-    const int32_t *__restrict__ perm, const float4 *__restrict__ packed, int64_t n, int nl,
-    const int64_t *__restrict__ tile_start, const int32_t *__restrict__ tile_set,
-    const int64_t *__restrict__ set_off, int32_t nsets, const double *__restrict__ box,
-    int64_t cell_tiles, float4 *__restrict__ sorted, uint64_t *__restrict__ keys,
-    uint64_t *__restrict__ key_out, float *__restrict__ pos_sorted,
-    float *__restrict__ mass_sorted, uint16_t *__restrict__ ad, uint32_t *__restrict__ tile_cnt,
-    int hilbert, const uint32_t *__restrict__ oversize, int32_t *__restrict__ status_word) {
-  extern __shared__ __align__(16) unsigned char lds[];
-  const WindowLds s = carve_window(lds, nl);
+// gathers, so the random reads overlap; they bound the pass (one 128-byte line a
+// 16-byte record: 2^24 in random order, 2.1 GB of lines in 0.45 ms).  Also fills perm and the optional
+// pos_sorted / mass_sorted / key_sorted outputs and checks the masses.
+//
+// The radix passes sort by the key bits from `skip` on, so a run of particles that
+// agree in those arrives in input order.  A particle's place in its run follows from
+// the run's other keys: those before it that are not larger and those after it that
+// are smaller (which keeps equal keys in input order).  A window reaches kRunCap
+// particles further than it needs, so every run of at most kRunCap particles that
+// touches the needed part is whole, and a longer one looks longer.  A tile
+// that meets a longer run writes nothing: it is listed, and so is the run if it starts
+// in the tile; k_sort_runs sorts the listed runs, and a second launch does the listed
+// tiles, where the particles of a longer run keep their places.  When the low bits were
+// sorted too (*full) nothing is left to do.
+struct ReorderArgs {
+  const int32_t *order;  // the radix passes' indices
+  const float4 *packed;
+  int64_t n;
+  int nl, skip, hilbert;
+  const int64_t *tile_start;
+  const int32_t *tile_set;
+  const int64_t *set_off;
+  int32_t nsets;
+  const double *box;
+  int64_t cell_tiles;
+  const uint32_t *full, *oversize;
+  uint32_t *n_runs, *n_run_tiles;
+  int32_t *runs, *run_tiles;
+  float4 *sorted;
+  uint64_t *keys, *key_out;
+  int32_t *perm;
+  float *pos_sorted, *mass_sorted;
+  uint16_t *ad;
+  uint32_t *tile_cnt;
+  int32_t *status_word;
+};
+
+// The window's runs, a bit a particle that does not agree with the one before it in the
+// sorted bits (and every one outside the set), 64 particles a word, between two words
+// of ones.
+__device__ __forceinline__ uint64_t *run_heads(const WindowLds &s) { return s.heads + 1; }
+
+// Places in the window of N particles, those at i0 + r * kCellThreads (i0 = threadIdx.x +
+// whole rows of threads, so a wave holds 64 particles of one word): the number of the
+// run's particles with smaller keys, or equal ones before it, after the run's start.
+// Keys of a run differ below bit 31 only.  All of a thread's particles meet the d-th
+// next of their runs (cyclically) in one step, as long as a run in the wave has more.
+// Returns whether one of them is in a run longer than kRunCap (it keeps its place);
+// *first: bit r if particle r is, and is the first of the run.
+template <int N>
+__device__ inline bool run_places(const WindowLds &s, int i0, int wn, const uint64_t (&key)[N],
+                                  int (&place)[N], uint32_t *first) {
+  const int lane = lane_id();
+  const uint32_t *low = reinterpret_cast<const uint32_t *>(s.raw);  // low words at 2 i
+  int end[N], len[N], most = 1;
+  bool any = false;
+  *first = 0;
+#pragma unroll
+  for (int r = 0; r < N; ++r) {
+    const int i = i0 + r * kCellThreads, w = i / 64;
+    end[r] = lane + 1;
+    len[r] = 1;
+    place[r] = i;
+    if (i < wn) {
+      const uint64_t *h = run_heads(s) + w;
+      const uint64_t here = h[0], le = here & ((2ull << lane) - 1ull);
+      const uint64_t gt = here & ~((2ull << lane) - 1ull);
+      // relative to the word; beyond its neighbours the run is too long anyway
+      const int start = le ? 63 - __clzll((long long)le)
+                           : h[-1] ? -1 - __clzll((long long)h[-1]) : -64;
+      end[r] = gt ? __ffsll((long long)gt) - 1 : h[1] ? 63 + __ffsll((long long)h[1]) : 128;
+      len[r] = end[r] - start;
+      if (len[r] > kRunCap) {
+        any = true;
+        if (start == lane) *first |= 1u << r;
+        len[r] = 1;
+      } else {
+        place[r] += start - lane;
+      }
+      most = max(most, len[r]);
+    }
+  }
+  for (int d = 1; __ballot(d < most) != 0; ++d) {
+    uint32_t other[N];
+#pragma unroll
+    for (int r = 0; r < N; ++r) {
+      const int j = lane + d, back = j >= end[r] ? len[r] : 0;
+      // (past the run's particles: this one itself)
+      const int at = d < len[r] ? i0 + r * kCellThreads + d - back : min(i0 + r * kCellThreads, wn - 1);
+      other[r] = low[2 * at];
+    }
+#pragma unroll
+    for (int r = 0; r < N; ++r) {
+      const uint32_t mine = (uint32_t)key[r];
+      const bool before = lane + d >= end[r];
+      const bool smaller = other[r] < mine || (before && other[r] == mine);
+      place[r] += d < len[r] && smaller ? 1 : 0;
+    }
+  }
+  return any;
+}
+
+// KEPT: the window's records stay with the threads that gathered them.
+template <bool KEPT>
+__device__ inline void reorder_tile(const ReorderArgs &g, const WindowLds &s, int64_t tile,
+                                    bool again) {
   // a batch set over the caller's index bound: every particle gets the root key
-  const bool flat = oversize && *oversize != 0u;
-  const int64_t tile = xcd_tile(blockIdx.x, gridDim.x);
-  if (tile >= tile_start[nsets]) return;
-  const TileRange tr = tile_range(tile, tile_start, tile_set, set_off);
+  const bool flat = g.oversize && *g.oversize != 0u;
+  const bool whole = flat || *g.full != 0u;  // the order is final
+  const int nl = g.nl;
+  const TileRange tr = tile_range(tile, g.tile_start, g.tile_set, g.set_off);
   const int64_t t0 = tr.t0, t1 = tr.t1;
-  const double lo0 = box[4 * tr.b + 0], lo1 = box[4 * tr.b + 1], lo2 = box[4 * tr.b + 2];
-  const double scale = 2097152.0 / box[4 * tr.b + 3];
+  const double lo0 = g.box[4 * tr.b + 0], lo1 = g.box[4 * tr.b + 1], lo2 = g.box[4 * tr.b + 2];
+  const double scale = 2097152.0 / g.box[4 * tr.b + 3];
   const int T = (int)(t1 - t0);
-  const int64_t ws = t0 - nl - 1;  // window start (may be negative)
-  const int wn = T + 2 * nl + 1;
+  const int64_t ws = t0 - nl - 1 - kRunCap;  // window start (may be negative)
+  const int wn = window_size(T, nl);
+  constexpr int kBatch = kWindowIpt;
   bool internal = false, bad = false;
-  // 9 items per thread cover the tile and its halo in one round trip for
-  // n_leaf <= 127
-  constexpr int kBatch = kCellIpt + 1;
-  for (int i0 = 0; i0 < wn; i0 += kBatch * kCellThreads) {
-    int32_t p[kBatch];
+  int32_t p[kBatch];
+  float4 rec[kBatch];
+  auto gather = [&](int i0) {
 #pragma unroll
     for (int r = 0; r < kBatch; ++r) {
       const int i = i0 + r * kCellThreads + threadIdx.x;
-      const int64_t g = ws + i;
-      const bool in = i < wn && g >= tr.S && g < tr.E;
-      p[r] = perm[in ? g : t0];
+      const int64_t q = ws + i;
+      const bool in = i < wn && q >= tr.S && q < tr.E;
+      p[r] = g.order[in ? q : t0];
     }
-    float4 rec[kBatch];
 #pragma unroll
     for (int r = 0; r < kBatch; ++r) {
       const int i = i0 + r * kCellThreads + threadIdx.x;
-      const int64_t g = ws + i;
-      const bool in = i < wn && g >= tr.S && g < tr.E;
-      const bool ok = p[r] >= 0 && p[r] < n;
+      const int64_t q = ws + i;
+      const bool in = i < wn && q >= tr.S && q < tr.E;
+      const bool ok = p[r] >= 0 && p[r] < g.n;
       internal |= in && !ok;
-      rec[r] = packed[ok ? p[r] : 0];
+      rec[r] = g.packed[ok ? p[r] : 0];
     }
+  };
+  for (int i0 = 0; i0 < wn; i0 += kBatch * kCellThreads) {
+    gather(i0);
 #pragma unroll
     for (int r = 0; r < kBatch; ++r) {
       const int i = i0 + r * kCellThreads + threadIdx.x;
-      const int64_t g = ws + i;
-      const bool in = i < wn && g >= tr.S && g < tr.E;
+      const int64_t q = ws + i;
+      const bool in = i < wn && q >= tr.S && q < tr.E;
       const uint64_t key =
           !in ? 0ull
           : flat
               ? 1ull << 63
-              : particle_key(rec[r].x, rec[r].y, rec[r].z, lo0, lo1, lo2, scale, hilbert != 0);
-      if (i < wn) s.keys[i] = key;
-      if (g >= t0 && g < t1 && i < wn) {
-        sorted[g] = rec[r];
-        keys[g] = key;
-        if (key_out) key_out[g] = key;
-        bad |= !(rec[r].w > 0.0f && isfinite(rec[r].w));
-        if (pos_sorted) {
-          pos_sorted[3 * g + 0] = rec[r].x;
-          pos_sorted[3 * g + 1] = rec[r].y;
-          pos_sorted[3 * g + 2] = rec[r].z;
+              : particle_key(rec[r].x, rec[r].y, rec[r].z, lo0, lo1, lo2, scale, g.hilbert != 0);
+      if (i < wn) s.raw[i] = key;
+    }
+    if (KEPT) break;  // one batch holds the window
+  }
+  __syncthreads();
+
+  // every particle's place
+  constexpr int kRow = KEPT ? kBatch : 1;
+  uint64_t key[kBatch];
+  int place[kBatch];
+  bool longer = false;
+  if (!whole) {
+    const int rows = (wn + kCellThreads - 1) / kCellThreads;
+    for (int r = 0; r < rows; ++r) {
+      const int i = r * kCellThreads + threadIdx.x;
+      bool head = true;
+      if (i > 0 && i < wn) {
+        const uint64_t k = s.raw[i];
+        head = k == 0ull || ((k ^ s.raw[i - 1]) >> g.skip) != 0;
+      }
+      const uint64_t m = __ballot(head);
+      if (lane_id() == 0) run_heads(s)[i / 64] = m;
+    }
+    if (threadIdx.x == 0) run_heads(s)[-1] = run_heads(s)[rows * kWaves] = ~0ull;
+    __syncthreads();
+  }
+  for (int i0 = threadIdx.x; i0 < (KEPT ? kCellThreads : wn); i0 += kRow * kCellThreads) {
+    uint64_t k[kRow];
+    int at[kRow];
+#pragma unroll
+    for (int r = 0; r < kRow; ++r) {
+      const int i = i0 + r * kCellThreads;
+      k[r] = i < wn ? s.raw[i] : 0ull;
+      at[r] = i;
+    }
+    if (!whole) {
+      uint32_t first;
+      if (run_places<kRow>(s, i0, wn, k, at, &first)) {
+        longer = true;
+#pragma unroll
+        for (int r = 0; r < kRow; ++r) {
+          const int64_t q = ws + i0 + r * kCellThreads;
+          if (((first >> r) & 1u) && !again && q >= t0 && q < t1)
+            g.runs[atomicAdd(g.n_runs, 1u)] = (int32_t)q;
         }
-        if (mass_sorted) mass_sorted[g] = rec[r].w;
       }
     }
+    if (KEPT) {
+#pragma unroll
+      for (int r = 0; r < kRow; ++r) {
+        key[r] = k[r];
+        place[r] = at[r];
+      }
+    } else {
+      s.place[i0] = (uint16_t)at[0];
+      s.fin[at[0]] = k[0];
+    }
   }
-  if (__ballot(bad) != 0 && lane_id() == 0) atomicOr(status_word, TB_STATUS_MASS);
-  if (__ballot(internal) != 0 && lane_id() == 0) atomicOr(status_word, TB_STATUS_INTERNAL);
+  const bool stop = __syncthreads_or(longer ? 1 : 0) != 0 && !again;
+  if (stop) {
+    if (threadIdx.x == 0) g.run_tiles[atomicAdd(g.n_run_tiles, 1u)] = (int32_t)tile;
+    return;
+  }
+  for (int i0 = 0; i0 < wn; i0 += kBatch * kCellThreads) {
+    if (!KEPT) {
+      gather(i0);
+#pragma unroll
+      for (int r = 0; r < kBatch; ++r) {
+        const int i = i0 + r * kCellThreads + threadIdx.x;
+        key[r] = i < wn ? s.raw[i] : 0ull;
+        place[r] = i < wn ? s.place[i] : 0;
+      }
+    }
+#pragma unroll
+    for (int r = 0; r < kBatch; ++r) {
+      const int i = i0 + r * kCellThreads + threadIdx.x;
+      if (i >= wn) continue;
+      if (KEPT) s.fin[place[r]] = key[r];
+      const int64_t q = ws + place[r];
+      if (q >= t0 && q < t1) {
+        g.sorted[q] = rec[r];
+        g.keys[q] = key[r];
+        g.perm[q] = p[r];
+        if (g.key_out) g.key_out[q] = key[r];
+        bad |= !(rec[r].w > 0.0f && isfinite(rec[r].w));
+        if (g.pos_sorted) {
+          g.pos_sorted[3 * q + 0] = rec[r].x;
+          g.pos_sorted[3 * q + 1] = rec[r].y;
+          g.pos_sorted[3 * q + 2] = rec[r].z;
+        }
+        if (g.mass_sorted) g.mass_sorted[q] = rec[r].w;
+      }
+    }
+    if (KEPT) break;
+  }
+  if (__ballot(bad) != 0 && lane_id() == 0) atomicOr(g.status_word, TB_STATUS_MASS);
+  if (__ballot(internal) != 0 && lane_id() == 0) atomicOr(g.status_word, TB_STATUS_INTERNAL);
   __syncthreads();
 
   uint8_t A[kCellIpt], D[kCellIpt];
@@ -270,7 +484,7 @@ __global__ __launch_bounds__(kCellThreads) void k_reorder(
 #pragma unroll
   for (int j = 0; j < kCellIpt; ++j) {
     const int li = threadIdx.x * kCellIpt + j;
-    if (li < T) ad[t0 + li] = (uint16_t)(A[j] | (D[j] << 8));
+    if (li < T) g.ad[t0 + li] = (uint16_t)(A[j] | (D[j] << 8));
   }
   uint32_t c[kLevelWords], tot[kLevelWords];
   thread_level_counts(A, D, c);
@@ -281,7 +495,129 @@ __global__ __launch_bounds__(kCellThreads) void k_reorder(
 #pragma unroll
     for (int wi = 0; wi < kLevelWords; ++wi)
       if (wi == (d >> 1)) cnt = (tot[wi] >> ((d & 1) * 16)) & 0xffffu;
-    tile_cnt[d * cell_tiles + tile] = cnt;
+    g.tile_cnt[d * g.cell_tiles + tile] = cnt;
+  }
+}
+
+template <bool KEPT>
+__global__ __launch_bounds__(kCellThreads) void k_reorder(ReorderArgs g) {
+  extern __shared__ __align__(16) unsigned char lds[];
+  const int64_t tile = xcd_tile(blockIdx.x, gridDim.x);
+  if (tile >= g.tile_start[g.nsets]) return;
+  reorder_tile<KEPT>(g, carve_window(lds, g.nl), tile, false);
+}
+
+// The tiles the first launch listed.
+template <bool KEPT>
+__global__ __launch_bounds__(kCellThreads) void k_reorder_again(ReorderArgs g) {
+  extern __shared__ __align__(16) unsigned char lds[];
+  const uint32_t n = *g.n_run_tiles;
+  for (uint32_t q = blockIdx.x; q < n; q += gridDim.x) {
+    reorder_tile<KEPT>(g, carve_window(lds, g.nl), g.run_tiles[q], true);
+    __syncthreads();
+  }
+}
+
+// Sorts each listed run of the radix passes' order by the key bits below `skip`, one
+// workgroup a run: an LSD radix sort with 8-bit digits of (low bits << 32 | index)
+// words in global memory.  The run lies in listed tiles only, whose sorted keys are not
+// written yet, so keys0 and keys1 hold the words.  A run that is in order already
+// (coincident particles) stays.  Rare (0.1 % of the particles of 2^26 clustered ones),
+// so one workgroup's latency a step is what it costs: 2^26, 1856 runs, 60 us.
+__global__ __launch_bounds__(kCellThreads) void k_sort_runs(
+    ReorderArgs g, int32_t *__restrict__ order, uint64_t *__restrict__ buf0,
+    uint64_t *__restrict__ buf1) {
+  constexpr int kThreads = kCellThreads, kRunWaves = kThreads / 64;
+  static_assert(kThreads == 256, "one thread per digit");
+  __shared__ uint32_t s_hist[256];
+  __shared__ uint32_t s_wave[kRunWaves][256];
+  __shared__ uint32_t s_w[kRunWaves];
+  __shared__ int s_set;
+  const uint32_t n_runs = *g.n_runs;
+  const int t = threadIdx.x, wv = t / 64;
+  for (uint32_t run = blockIdx.x; run < n_runs; run += gridDim.x) {
+    const int64_t s = g.runs[run];
+    if (t == 0) s_set = upper_index(g.set_off, g.nsets + 1, s);
+    __syncthreads();
+    const int b = s_set;
+    const int64_t E = g.set_off[b + 1];
+    const double lo0 = g.box[4 * b + 0], lo1 = g.box[4 * b + 1], lo2 = g.box[4 * b + 2];
+    const double scale = 2097152.0 / g.box[4 * b + 3];
+    // the run's words, chunk by chunk up to the first particle past it
+    uint64_t pre = 0;
+    int64_t len = 0;
+    bool rising = true;
+    for (int64_t c0 = s;; c0 += kThreads) {
+      const int64_t q = c0 + t;
+      uint64_t key = 0;
+      int32_t idx = 0;
+      if (q < E) {
+        idx = order[q];
+        const float4 r = g.packed[idx >= 0 && idx < g.n ? idx : 0];
+        key = particle_key(r.x, r.y, r.z, lo0, lo1, lo2, scale, g.hilbert != 0);
+      }
+      if (c0 == s) {
+        if (t == 0) buf1[s] = key;
+        __syncthreads();
+        pre = buf1[s] >> g.skip;
+        __syncthreads();
+      }
+      const bool in = q < E && (key >> g.skip) == pre;
+      const uint64_t low = key & ((1ull << g.skip) - 1);
+      if (in) buf0[q] = low << 32 | (uint32_t)idx;
+      const int members = __syncthreads_count(in ? 1 : 0);
+      // a run is contiguous: its members are the first of the chunk
+      if (in && q > s) rising &= (buf0[q - 1] >> 32) <= low;
+      len += members;
+      if (members < kThreads) break;
+    }
+    if (__syncthreads_and(rising ? 1 : 0)) continue;
+    uint64_t *src = buf0 + s, *dst = buf1 + s;
+    for (int sh = 32; sh < 32 + g.skip; sh += 8) {
+      s_hist[t] = 0;
+      __syncthreads();
+      for (int64_t i = t; i < len; i += kThreads) atomicAdd(&s_hist[(src[i] >> sh) & 255u], 1u);
+      __syncthreads();
+      const uint32_t v = s_hist[t], inc = wave_inclusive_scan(v);
+      if (lane_id() == 63) s_w[wv] = inc;
+      __syncthreads();
+      uint32_t off = inc - v;
+      for (int q = 0; q < wv; ++q) off += s_w[q];
+      s_hist[t] = off;
+      // 256 words at a time, in order: ranks by ballots within a wave, the waves in turn
+      for (int64_t c0 = 0; c0 < len; c0 += kThreads) {
+        for (int q = 0; q < kRunWaves; ++q) s_wave[q][t] = 0;
+        __syncthreads();
+        const bool in = c0 + t < len;
+        const uint64_t word = in ? src[c0 + t] : 0ull;
+        const uint32_t d = (uint32_t)(word >> sh) & 255u;
+        uint64_t peers = __ballot(in);
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+          const bool bit = (d >> k) & 1u;
+          const uint64_t m = __ballot(bit);
+          peers &= bit ? m : ~m;
+        }
+        const uint32_t before = (uint32_t)__popcll(peers & lanemask_lt());
+        if (in && before == 0) s_wave[wv][d] = (uint32_t)__popcll(peers);
+        __syncthreads();
+        if (in) {
+          uint32_t at = s_hist[d] + before;
+          for (int q = 0; q < wv; ++q) at += s_wave[q][d];
+          dst[at] = word;
+        }
+        __syncthreads();
+        uint32_t add = 0;
+        for (int q = 0; q < kRunWaves; ++q) add += s_wave[q][t];
+        s_hist[t] += add;
+        __syncthreads();
+      }
+      uint64_t *x = src;
+      src = dst;
+      dst = x;
+    }
+    for (int64_t i = t; i < len; i += kThreads) order[s + i] = (int32_t)(uint32_t)src[i];
+    __syncthreads();
   }
 }
 
@@ -783,12 +1119,57 @@ hipError_t launch_cell_scan(const Plan &p, const Work &w, const tb_tree &out,
   return hipGetLastError();
 }
 
+// The runs and tiles left to the second launch are listed in the look-back words' space:
+// at most n / (kRunCap + 1) runs, and as many tiles as there are.
+static ReorderArgs reorder_args(const Plan &p, const Work &w, const tb_tree &out) {
+  ReorderArgs g;
+  g.order = reinterpret_cast<const int32_t *>(w.vals1);
+  g.packed = w.packed;
+  g.n = p.n;
+  g.nl = p.n_leaf;
+  g.skip = p.skip_bits;
+  g.hilbert = (p.flags & TB_HILBERT) ? 1 : 0;
+  g.tile_start = w.tile_start;
+  g.tile_set = w.tile_set;
+  g.set_off = w.set_off;
+  g.nsets = p.nsets;
+  g.box = w.box;
+  g.cell_tiles = p.cell_tiles;
+  g.full = w.counters + kFullSortCounter;
+  g.oversize = p.set_index_bits ? w.counters + kOversizeCounter : nullptr;
+  g.n_runs = w.counters + kRunCounter;
+  g.n_run_tiles = w.counters + kRunTileCounter;
+  g.runs = reinterpret_cast<int32_t *>(w.status0);
+  g.run_tiles = reinterpret_cast<int32_t *>(w.status1);
+  g.sorted = w.sorted;
+  g.keys = sorted_keys(p, w);
+  g.key_out = out.key_sorted;
+  g.perm = out.perm;
+  g.pos_sorted = out.pos_sorted;
+  g.mass_sorted = out.mass_sorted;
+  g.ad = w.ad;
+  g.tile_cnt = w.cell_cnt;
+  g.status_word = out.status;
+  return g;
+}
+
 hipError_t launch_reorder(const Plan &p, const Work &w, const tb_tree &out, hipStream_t s) {
-  k_reorder<<<(unsigned)p.cell_tiles, kCellThreads, window_lds_bytes(p.n_leaf), s>>>(
-      out.perm, w.packed, p.n, p.n_leaf, w.tile_start, w.tile_set, w.set_off, p.nsets, w.box,
-      p.cell_tiles, w.sorted, sorted_keys(p, w), out.key_sorted, out.pos_sorted, out.mass_sorted,
-      w.ad, w.cell_cnt, (p.flags & TB_HILBERT) ? 1 : 0,
-      p.set_index_bits ? w.counters + kOversizeCounter : nullptr, out.status);
+  auto k = window_kept(p.n_leaf) ? k_reorder<true> : k_reorder<false>;
+  k<<<(unsigned)p.cell_tiles, kCellThreads, window_lds_bytes(p.n_leaf), s>>>(
+      reorder_args(p, w, out));
+  return hipGetLastError();
+}
+
+hipError_t launch_runs(const Plan &p, const Work &w, const tb_tree &out, hipStream_t s) {
+  const ReorderArgs g = reorder_args(p, w, out);
+  const int64_t most = p.n / (kRunCap + 1);
+  if (most == 0) return hipSuccess;  // too few particles for a run that long
+  // small grids, which return at once in the common case that nothing is listed
+  k_sort_runs<<<(unsigned)(most < 256 ? most : 256), kCellThreads, 0, s>>>(
+      g, reinterpret_cast<int32_t *>(w.vals1), w.keys0, w.keys1);
+  auto k = window_kept(p.n_leaf) ? k_reorder_again<true> : k_reorder_again<false>;
+  k<<<(unsigned)(p.cell_tiles < 512 ? p.cell_tiles : 512), kCellThreads,
+      window_lds_bytes(p.n_leaf), s>>>(g);
   return hipGetLastError();
 }
 
@@ -808,8 +1189,11 @@ size_t cell_lds_limit() {
                               hipFuncAttributeMaxDynamicSharedMemorySize, opt);
     (void)hipFuncSetAttribute(reinterpret_cast<const void *>(k_cell_emit<true>),
                               hipFuncAttributeMaxDynamicSharedMemorySize, opt);
-    (void)hipFuncSetAttribute(reinterpret_cast<const void *>(k_reorder),
-                              hipFuncAttributeMaxDynamicSharedMemorySize, opt);
+    for (const void *k : {reinterpret_cast<const void *>(k_reorder<true>),
+                          reinterpret_cast<const void *>(k_reorder<false>),
+                          reinterpret_cast<const void *>(k_reorder_again<true>),
+                          reinterpret_cast<const void *>(k_reorder_again<false>)})
+      (void)hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, opt);
     cached = (size_t)v;
     cached_dev = dev;
   }

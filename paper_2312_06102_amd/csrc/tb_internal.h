@@ -53,6 +53,17 @@ constexpr int kMaxSetsLds = TB_MAX_SETS;
 // bound TB_SET_INDEX_BITS gives (set by the setup, read by the reorder)
 constexpr int kOversizeCounter = 16;
 
+// counters[kFullSortCounter]: nonzero when the radix passes over the low key bits run
+// too (set by the key kernel's sample); counters[kRunCounter], [kRunTileCounter]: runs
+// and tiles the reorder leaves to k_sort_runs and its second launch
+constexpr int kFullSortCounter = 17;
+constexpr int kRunCounter = 18;
+constexpr int kRunTileCounter = 19;
+
+// Longest run of particles that agree in the sorted key bits which the reorder puts in
+// order by itself; also how far it looks past its window for the ends of runs.
+constexpr int kRunCap = 32;
+
 // counters[kUpperCounter + d]: number of cells above the blocks at depth d
 constexpr int kUpperCounter = 32;
 
@@ -68,12 +79,11 @@ struct SortConfig {
   int threads;  // threads per workgroup
   int tile() const { return ipt * threads; }
   int radix() const { return 1 << bits; }
-  int passes() const { return (63 + bits - 1) / bits; }  // bit 63 is always 1
 };
 
 // What one radix pass reads or writes per element.  The index is the element's
-// position before the sort (perm after the last pass); a packed element holds the
-// key bits later passes still need above the index bits.
+// position before the sort; a packed element holds the key bits later passes still
+// need above the index bits.
 enum SortForm : uint8_t {
   kFormIdx = 0,     // the index alone (the last pass's output)
   kFormKey64 = 2,   // the 64-bit key, with the index in a separate u32 array
@@ -93,7 +103,9 @@ struct Plan {
   uint32_t flags;
   int32_t nsets;    // B
   SortConfig sort;
-  int key_passes;   // radix passes over the 63 key bits
+  int key_passes;   // radix passes over the upper key bits, those above skip_bits
+  int low_passes;   // conditional passes over the skip_bits below (see make_plan)
+  int skip_bits;    // low key bits that only the conditional passes look at
   uint32_t counted; // bit k: key pass k takes its tile offsets from a count and a scan
   int idx_bits;     // bits of the largest index, n - 1 (at least 1); in a batch the index
                     // is the position within the set
@@ -109,8 +121,9 @@ struct Plan {
   int64_t upper_cap;    // cells above the blocks, per depth: at most n / (n_serial + 1) + B
   // offsets
   size_t keys0, keys1;  // u64 [n] ping-pong buffers of keys or packed words
-  size_t vals1;         // u32 [n] payload buffer (the other one is out->perm)
-  size_t hist;          // u32 [key_passes][radix] global digit counts, then bases (single set)
+  size_t vals1;         // u32 [n] payload buffer; the sort's last pass writes it
+  size_t hist;          // u32 [key_passes + low_passes][radix] global digit counts, then
+                        // bases (single set)
   size_t hist_part;     // u32 [keygen blocks][key_passes][radix] per-workgroup counts
   size_t status0, status1;  // u64 [sort_tiles][radix] look-back words (alternating passes)
   size_t counters;      // u32 [64] dynamic tile counters
@@ -134,7 +147,7 @@ struct Plan {
   size_t par_start;     // i64 [kLevels][B + 1] parent-pass chunks per depth and set
   size_t seg_tile_start;  // i64 [B + 1] first radix tile of each set (seg)
   size_t seg_tile_set;    // i32 [sort_tiles] set of each radix tile (seg)
-  size_t seg_base;        // u32 [B][key_passes][radix] digit counts of each set, then the
+  size_t seg_base;        // u32 [B][key_passes + low_passes][radix] digit counts of each set, then the
                           // position where each digit's run of the set starts (seg)
   size_t packed;        // f32x4 [n] (x, y, z, m) records in original order
   size_t sorted;        // f32x4 [n] the same records in key order
@@ -207,17 +220,20 @@ hipError_t launch_bbox(const Plan &p, const Work &w, const float *pos, hipStream
 hipError_t launch_keygen(const Plan &p, const Work &w, const float *pos, const float *mass,
                          const tb_tree &out, hipStream_t s);
 hipError_t launch_hist_reduce(const Plan &p, const Work &w, hipStream_t s);
+int low_shift(const Plan &p, int pass);
 int keygen_blocks(int64_t n);
 hipError_t launch_empty(const tb_tree &out, int32_t nsets, const BatchIn &in,
                         int64_t *cell_offsets, hipStream_t s);
 // tb_sort.hip
 hipError_t launch_sort_pass(const Plan &p, const Work &w, int pass, const tb_tree &out,
                             hipStream_t s);
+hipError_t launch_low_passes(const Plan &p, const Work &w, const tb_tree &out, hipStream_t s);
 bool sort_config_supported(const SortConfig &c);
 // tb_cells.hip
 hipError_t launch_cell_scan(const Plan &p, const Work &w, const tb_tree &out,
                             int64_t *cell_offsets, hipStream_t s);
 hipError_t launch_reorder(const Plan &p, const Work &w, const tb_tree &out, hipStream_t s);
+hipError_t launch_runs(const Plan &p, const Work &w, const tb_tree &out, hipStream_t s);
 size_t cell_lds_limit();
 size_t cell_reorder_lds(int nl);
 hipError_t launch_cell_emit(const Plan &p, const Work &w, const tb_tree &out, hipStream_t s);

@@ -13,11 +13,16 @@
 //               below a leading 1, plus per-workgroup digit histograms of every
 //               radix pass (so the sort never re-reads the keys to count them)
 //               and the packed (x, y, z, m) record of every particle.
-// k_hist_reduce column sums of those per-workgroup histograms.
+//               One workgroup samples the keys instead and decides whether
+//               the passes over the low key bits run.
+// k_hist_reduce column sums of those per-workgroup histograms, and the low
+//               digits' counts if they are wanted (k_low_counts_sets: a batch's).
 // k_keygen_sets the same for a batch, chunk by chunk of one set, with each set's
 //               digit counts added up per set;
 // k_set_base    each set's digit counts -> the start of every digit's run (a
 //               single set's global counts too).
+#include <cmath>
+
 #include "tb_internal.h"
 
 namespace tb {
@@ -32,8 +37,8 @@ constexpr int kSetupThreads = 1024;
 // init
 // ---------------------------------------------------------------------------
 __global__ __launch_bounds__(kInitThreads) void k_init(
-    uint64_t *__restrict__ status0, int64_t n_status0, uint32_t *__restrict__ counters,
-    int32_t *__restrict__ status_word, int64_t n, int32_t nsets,
+    uint64_t *__restrict__ status0, int64_t n_status0, uint32_t *__restrict__ low_hist,
+    int n_low, uint32_t *__restrict__ counters, int32_t *__restrict__ status_word, int64_t n, int32_t nsets,
     const int64_t *__restrict__ set_off_in, int64_t *__restrict__ set_off,
     const tb_box *__restrict__ boxes_in, double *__restrict__ box, int host_box, double lo0,
     double lo1, double lo2, double side, int single, int chunk,
@@ -43,6 +48,7 @@ __global__ __launch_bounds__(kInitThreads) void k_init(
   const int64_t tid = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   for (int64_t i = tid; i < n_status0; i += stride) status0[i] = 0;
+  for (int64_t i = tid; i < n_low; i += stride) low_hist[i] = 0;
   if (single) {
     // one set given by the host: its tables need no validation or scan (the
     // chunk table exists only when the box comes from the data: chunk > 0)
@@ -89,13 +95,16 @@ static bool single_set(const Plan &p, const BatchIn &in) {
 
 hipError_t launch_init(const Plan &p, const Work &w, const BatchIn &in, const tb_tree &out,
                        hipStream_t s) {
-  const int64_t n0 = p.sort_tiles * (int64_t)p.sort.radix();
+  // look-back words of the first pass (a counted one has none)
+  const int64_t n0 = (p.counted & 1u) ? 0 : p.sort_tiles * (int64_t)p.sort.radix();
+  const int n_low = p.seg ? 0 : p.low_passes * p.sort.radix();
   int64_t work = n0 > p.nsets ? n0 : p.nsets;
   int blocks = (int)((work + kInitThreads - 1) / kInitThreads);
   if (blocks > 1024) blocks = 1024;
   if (blocks < 1) blocks = 1;
+  uint32_t *low_hist = w.hist + (size_t)p.key_passes * p.sort.radix();
   const tb_box *hb = in.host_box;
-  k_init<<<blocks, kInitThreads, 0, s>>>(w.status0, n0, w.counters, out.status, p.n, p.nsets,
+  k_init<<<blocks, kInitThreads, 0, s>>>(w.status0, n0, low_hist, n_low, w.counters, out.status, p.n, p.nsets,
                                          in.set_off, w.set_off, in.dev_boxes, w.box, hb ? 1 : 0,
                                          hb ? hb->lo[0] : 0.0, hb ? hb->lo[1] : 0.0,
                                          hb ? hb->lo[2] : 0.0, hb ? hb->side : 1.0,
@@ -253,7 +262,8 @@ hipError_t launch_setup(const Plan &p, const Work &w, const BatchIn &in, int32_t
                                       p.seg ? w.seg_tile_start : nullptr, p.sort.tile(),
                                       with_chunks ? p.bbox_chunk : 0, w.box, in.dev_boxes ? 1 : 0,
                                       p.set_index_bits, w.counters + kOversizeCounter, status);
-  const int64_t n_counts = p.seg ? (int64_t)p.nsets * p.key_passes * p.sort.radix() : 0;
+  const int64_t n_counts =
+      p.seg ? (int64_t)p.nsets * (p.key_passes + p.low_passes) * p.sort.radix() : 0;
   const int64_t entries = p.cell_tiles + (with_chunks ? p.bbox_chunks : 0) +
                           (p.seg ? p.sort_tiles : 0) + n_counts;
   int64_t grid = (entries + 255) / 256;
@@ -388,9 +398,8 @@ __device__ __forceinline__ void key_one(float x, float y, float z, float m, bool
                                         int64_t i, double lo0, double lo1, double lo2,
                                         double scale, bool hilbert, uint64_t *__restrict__ keys,
                                         float4 *__restrict__ packed, void *__restrict__ dig0,
-                                        uint32_t *h, bool &bad) {
+                                        uint32_t *h, int passes, int skip, bool &bad) {
   constexpr int R = 1 << BITS;
-  constexpr int MAXP = (63 + BITS - 1) / BITS;
   bad |= valid && !(isfinite(x) && isfinite(y) && isfinite(z));
   const uint64_t key = particle_key(x, y, z, lo0, lo1, lo2, scale, hilbert);
   if (valid) {
@@ -398,13 +407,14 @@ __device__ __forceinline__ void key_one(float x, float y, float z, float m, bool
     // (x, y, z, m) in one 16-byte record: the reorder step gathers one line each
     packed[i] = make_float4(x, y, z, m);
     // the first radix pass's digit, for its tile counts (counted passes)
-    if (dig0) static_cast<DigitType<BITS> *>(dig0)[i] = (DigitType<BITS>)(key & (R - 1));
+    if (dig0) static_cast<DigitType<BITS> *>(dig0)[i] = (DigitType<BITS>)((key >> skip) & (R - 1));
   }
   const uint64_t active = __ballot(valid);
   if (valid) {
 #pragma unroll
-    for (int p = 0; p < MAXP; ++p) {
-      const uint32_t d = (uint32_t)(key >> (p * BITS)) & (R - 1);
+    for (int p = 0; p < kMaxKeyPasses; ++p) {
+      if (p >= passes) break;
+      const uint32_t d = (uint32_t)(key >> (skip + p * BITS)) & (R - 1);
       const uint32_t d0 = __builtin_amdgcn_readfirstlane(d);
       if (__ballot(d == d0) == active) {
         if (lane_id() == __ffsll((long long)active) - 1)
@@ -416,16 +426,118 @@ __device__ __forceinline__ void key_one(float x, float y, float z, float m, bool
   }
 }
 
+// Whether the keys crowd below the sorted bits: the sampler (one workgroup, beside
+// the key kernel's others) counts how many of its samples agree with an earlier one in
+// the sorted bits and sets *full from min_dups on.  The samples are distinct particles
+// spread over the whole input; equal prefixes are found through a hash table of 32-bit
+// fingerprints in LDS (a false match only runs passes that are not needed).  4096
+// samples see runs of kRunMean particles each in 2^24 as six pairs, 1024 in 2^20 as
+// many; small inputs take the fewer, whose 6 us the key kernel covers.
+constexpr int kSamples = 4096;
+constexpr int kSampleTable = 2 * kSamples;
+static int64_t sample_count(int64_t n) { return n > (int64_t{1} << 20) ? kSamples : kSamples / 4; }
+
+template <int SAMPLES>
+__device__ inline void sample_keys(const float *__restrict__ pos, int64_t n,
+                                   const int64_t *__restrict__ set_off, int32_t nsets,
+                                   const double *__restrict__ box, int skip, bool hilbert,
+                                   uint32_t min_dups, uint32_t *table, uint32_t *s_dups,
+                                   uint32_t *__restrict__ full) {
+  constexpr int kTable = 2 * SAMPLES;
+  for (int i = threadIdx.x; i < kTable; i += kKeygenThreads) table[i] = 0;
+  if (threadIdx.x == 0) *s_dups = 0;
+  __syncthreads();
+  constexpr int kPer = 2;  // at a time: the key kernel's registers set its occupancy
+  uint32_t dups = 0;
+#pragma unroll 1
+  for (int k0 = threadIdx.x; k0 < SAMPLES; k0 += kPer * kKeygenThreads) {
+    float x[kPer][3];
+    int64_t at[kPer];
+    int set[kPer], top[kPer];
+    bool use[kPer];
+#pragma unroll
+    for (int r = 0; r < kPer; ++r) {
+      const int64_t k = k0 + r * kKeygenThreads;
+      int64_t i = k;  // every particle of a small input
+      if (n > SAMPLES) {
+        // one of the k-th stretch of n / SAMPLES
+        const int64_t lo = k * n / SAMPLES, hi = (k + 1) * n / SAMPLES;
+        i = lo + (int64_t)(((uint64_t)k * 0x9e3779b97f4a7c15ull >> 33) % (uint64_t)(hi - lo));
+      }
+      use[r] = i < n;
+      at[r] = use[r] ? i : 0;
+      set[r] = 0;
+      top[r] = nsets - 1;
+#pragma unroll
+      for (int a = 0; a < 3; ++a) x[r][a] = pos[3 * at[r] + a];
+    }
+    // the samples' sets: one binary search for all of a thread's, in step
+    for (int span = nsets; span > 1; span = (span + 1) / 2) {
+#pragma unroll
+      for (int r = 0; r < kPer; ++r) {
+        const int mid = (set[r] + top[r] + 1) >> 1;
+        const bool up = set_off[mid] <= at[r];
+        if (set[r] < top[r]) {
+          if (up)
+            set[r] = mid;
+          else
+            top[r] = mid - 1;
+        }
+      }
+    }
+#pragma unroll
+    for (int r = 0; r < kPer; ++r) {
+      const double *bx = box + 4 * set[r];
+      const uint64_t key = particle_key(x[r][0], x[r][1], x[r][2], bx[0], bx[1], bx[2],
+                                        2097152.0 / bx[3], hilbert);
+      uint64_t hash =
+          ((key >> skip) + (uint64_t)set[r] * 0xd1342543de82ef95ull) * 0x9e3779b97f4a7c15ull;
+      hash = (hash ^ (hash >> 29)) * 0xbf58476d1ce4e5b9ull;
+      const uint32_t tag = (uint32_t)(hash >> 32) | 1u;
+      uint32_t slot = (uint32_t)hash % kTable;
+      // at most half of the slots are taken, so the probe ends
+      for (int probe = 0; use[r] && probe < kTable; ++probe) {
+        const uint32_t was = atomicCAS(&table[slot], 0u, tag);
+        if (was == tag) ++dups;
+        if (was == 0u || was == tag) break;
+        slot = (slot + 1) % kTable;
+      }
+    }
+  }
+  if (dups) atomicAdd(s_dups, dups);
+  __syncthreads();
+  if (threadIdx.x == 0 && *s_dups >= min_dups) *full = 1u;
+}
+
+// Samples that may agree with an earlier one before the low bits are sorted as well:
+// what runs of kRunMean particles each would give.
+static uint32_t sample_limit(int64_t n) {
+  constexpr double kRunMean = 12.0;
+  const double s = (double)(n < sample_count(n) ? n : sample_count(n));
+  const double per_run = kRunMean * s / (double)n;  // samples in a run
+  const double dups = s * (1.0 - (1.0 - std::exp(-per_run)) / per_run);
+  return dups < 4.0 ? 4u : (uint32_t)dups;
+}
+
 // A single set: a grid-stride loop, one histogram per workgroup.
 template <int BITS>
 __global__ __launch_bounds__(kKeygenThreads) void k_keygen(
     const float *__restrict__ pos, const float *__restrict__ mass, int64_t n,
     const double *__restrict__ box, uint64_t *__restrict__ keys, float4 *__restrict__ packed,
-    void *__restrict__ dig0, uint32_t *__restrict__ hist_part, int passes, int hilbert,
-    int32_t *__restrict__ status_word) {
+    void *__restrict__ dig0, uint32_t *__restrict__ hist_part, int passes, int skip, int hilbert,
+    int few, uint32_t min_dups, uint32_t *__restrict__ full, int32_t *__restrict__ status_word) {
   constexpr int R = 1 << BITS;
-  constexpr int MAXP = (63 + BITS - 1) / BITS;
-  __shared__ uint32_t h[MAXP * R];
+  __shared__ uint32_t h[kSampleTable];  // [passes][R] digit counts
+  __shared__ uint32_t s_dups;
+  static_assert(kMaxKeyPasses * R <= kSampleTable, "the counts fit in the sampler's table");
+  if (blockIdx.x == 0) {
+    if (few)
+      sample_keys<kSamples / 4>(pos, n, nullptr, 1, box, skip, hilbert != 0, min_dups, h, &s_dups, full);
+    else
+      sample_keys<kSamples>(pos, n, nullptr, 1, box, skip, hilbert != 0, min_dups, h, &s_dups, full);
+    return;
+  }
+  const int64_t block = blockIdx.x - 1, blocks = gridDim.x - 1;
   for (int i = threadIdx.x; i < passes * R; i += blockDim.x) h[i] = 0;
   __syncthreads();
   bool bad = false;
@@ -433,8 +545,8 @@ __global__ __launch_bounds__(kKeygenThreads) void k_keygen(
   const double scale = 2097152.0 / box[3];
   // each step a thread handles kKeygenIpt particles whose loads are all issued
   // before any is used (indices past the end are clamped and masked)
-  const int64_t step = (int64_t)gridDim.x * blockDim.x * kKeygenIpt;
-  for (int64_t i0 = (int64_t)blockIdx.x * blockDim.x * kKeygenIpt + threadIdx.x; i0 < n;
+  const int64_t step = blocks * blockDim.x * kKeygenIpt;
+  for (int64_t i0 = block * blockDim.x * kKeygenIpt + threadIdx.x; i0 < n;
        i0 += step) {
     float x[kKeygenIpt], y[kKeygenIpt], z[kKeygenIpt], m[kKeygenIpt];
 #pragma unroll
@@ -449,16 +561,16 @@ __global__ __launch_bounds__(kKeygenThreads) void k_keygen(
     for (int r = 0; r < kKeygenIpt; ++r) {
       const int64_t i = i0 + (int64_t)r * blockDim.x;
       key_one<BITS>(x[r], y[r], z[r], m[r], i < n, i, lo0, lo1, lo2, scale, hilbert != 0, keys,
-                    packed, dig0, h, bad);
+                    packed, dig0, h, passes, skip, bad);
     }
   }
   if (__ballot(bad) != 0 && lane_id() == 0) atomicOr(status_word, TB_STATUS_NONFINITE);
   __syncthreads();
-  uint32_t *dst = hist_part + (int64_t)blockIdx.x * passes * R;
+  uint32_t *dst = hist_part + block * passes * R;
   for (int i = threadIdx.x; i < passes * R; i += blockDim.x) dst[i] = h[i];
 }
 
-// A batch: workgroup g takes the particles [g N / G, (g + 1) N / G) of the whole
+// A batch: the first workgroup samples; of the G others, workgroup g takes the particles [g N / G, (g + 1) N / G) of the whole
 // batch, which may span several sets (or part of one).  Its histogram is added
 // to the set's counts, set_counts[b][p][d], each time its range leaves a set, so
 // every workgroup has the same number of particles whatever the set sizes.
@@ -467,14 +579,23 @@ __global__ __launch_bounds__(kKeygenThreads) void k_keygen_sets(
     const float *__restrict__ pos, const float *__restrict__ mass, int64_t n,
     const int64_t *__restrict__ set_off, int32_t nsets, const double *__restrict__ box,
     uint64_t *__restrict__ keys, float4 *__restrict__ packed, void *__restrict__ dig0,
-    uint32_t *__restrict__ set_counts, int passes, int hilbert, int32_t *__restrict__ status_word) {
+    uint32_t *__restrict__ set_counts, int passes, int rows, int skip, int hilbert,
+    int few, uint32_t min_dups, uint32_t *__restrict__ full, int32_t *__restrict__ status_word) {
   constexpr int R = 1 << BITS;
-  constexpr int MAXP = (63 + BITS - 1) / BITS;
   constexpr int64_t kStep = (int64_t)kKeygenThreads * kKeygenIpt;
-  __shared__ uint32_t h[MAXP * R];
+  __shared__ uint32_t h[kSampleTable];  // [passes][R] digit counts
+  __shared__ uint32_t s_dups;
   __shared__ int s_b;
-  const int64_t per = (n + gridDim.x - 1) / gridDim.x;
-  const int64_t g_lo = (int64_t)blockIdx.x * per;
+  static_assert(kMaxKeyPasses * R <= kSampleTable, "the counts fit in the sampler's table");
+  if (blockIdx.x == 0) {
+    if (few)
+      sample_keys<kSamples / 4>(pos, n, set_off, nsets, box, skip, hilbert != 0, min_dups, h, &s_dups, full);
+    else
+      sample_keys<kSamples>(pos, n, set_off, nsets, box, skip, hilbert != 0, min_dups, h, &s_dups, full);
+    return;
+  }
+  const int64_t per = (n + gridDim.x - 2) / (gridDim.x - 1);
+  const int64_t g_lo = (int64_t)(blockIdx.x - 1) * per;
   const int64_t g_hi = min(n, g_lo + per);
   if (g_lo >= g_hi) return;  // the same for the whole workgroup
   // the set holding g_lo: the last b with set_off[b] <= g_lo (the offsets start
@@ -510,11 +631,11 @@ __global__ __launch_bounds__(kKeygenThreads) void k_keygen_sets(
       for (int r = 0; r < kKeygenIpt; ++r) {
         const int64_t i = base + r * kKeygenThreads + threadIdx.x;
         key_one<BITS>(x[r], y[r], z[r], m[r], i < s1, i, lo0, lo1, lo2, scale, hilbert != 0,
-                      keys, packed, dig0, h, bad);
+                      keys, packed, dig0, h, passes, skip, bad);
       }
     }
     __syncthreads();
-    uint32_t *dst = set_counts + (int64_t)b * passes * R;
+    uint32_t *dst = set_counts + (int64_t)b * rows * R;
     for (int i = threadIdx.x; i < passes * R; i += blockDim.x) {
       const uint32_t c = h[i];
       if (c) {
@@ -552,11 +673,50 @@ __global__ __launch_bounds__(1 << BITS) void k_set_base(const int64_t *__restric
   }
 }
 
+// The conditional passes over the low key bits: shift of each one's digit.
+struct LowDigits {
+  int passes;
+  int shift[kMaxKeyPasses];
+};
+
+// Digit counts of the conditional passes of a single set, added to rows `hist`
+// [passes][R] by the workgroups [first, gridDim.x), which also clear the first such
+// pass's look-back words.
+template <int BITS>
+__device__ inline void low_counts(const uint64_t *__restrict__ keys, int64_t n, LowDigits low,
+                                  uint32_t *__restrict__ hist, uint64_t *__restrict__ status,
+                                  int64_t n_status, int first, uint32_t *h) {
+  constexpr int R = 1 << BITS;
+  for (int i = threadIdx.x; i < low.passes * R; i += blockDim.x) h[i] = 0;
+  __syncthreads();
+  const int64_t step = (int64_t)(gridDim.x - first) * blockDim.x;
+  const int64_t i0 = (int64_t)(blockIdx.x - first) * blockDim.x + threadIdx.x;
+  for (int64_t i = i0; i < n_status; i += step) status[i] = 0;
+  for (int64_t i = i0; i < n; i += step) {
+    const uint64_t k = keys[i];
+    for (int p = 0; p < low.passes; ++p)
+      atomicAdd(&h[p * R + ((uint32_t)(k >> low.shift[p]) & (R - 1))], 1u);
+  }
+  __syncthreads();
+  for (int i = threadIdx.x; i < low.passes * R; i += blockDim.x)
+    if (h[i]) atomicAdd(&hist[i], h[i]);
+}
+
 // hist[c] = sum over rows b of part[b][c], for c < cols.  16 columns per
 // workgroup, 16 row groups per column, so each thread sums only rows/16 values.
-__global__ __launch_bounds__(256) void k_hist_reduce(const uint32_t *__restrict__ part, int rows,
-                                                     int cols, uint32_t *__restrict__ hist) {
+// The workgroups past those count the low digits if the sample asked for it.
+template <int BITS>
+__global__ __launch_bounds__(256) void k_hist_reduce(
+    const uint32_t *__restrict__ part, int rows, int cols, uint32_t *__restrict__ hist,
+    const uint32_t *__restrict__ full, const uint64_t *__restrict__ keys, int64_t n, LowDigits low,
+    uint64_t *__restrict__ status, int64_t n_status) {
   __shared__ uint32_t red[16][17];
+  __shared__ uint32_t h[kMaxKeyPasses << BITS];
+  const int col_blocks = (cols + 15) / 16;
+  if ((int)blockIdx.x >= col_blocks) {
+    if (*full) low_counts<BITS>(keys, n, low, hist + cols, status, n_status, col_blocks, h);
+    return;
+  }
   const int col = threadIdx.x & 15;
   const int g = threadIdx.x >> 4;
   const int c = blockIdx.x * 16 + col;
@@ -575,10 +735,42 @@ __global__ __launch_bounds__(256) void k_hist_reduce(const uint32_t *__restrict_
   }
 }
 
+// The same for a batch, tile by tile of the radix passes: each set's counts of the low
+// digits, and the tile's look-back words.
+template <int BITS>
+__global__ __launch_bounds__(256) void k_low_counts_sets(
+    const uint32_t *__restrict__ full, const uint64_t *__restrict__ keys, LowDigits low,
+    const int64_t *__restrict__ tile_start, const int32_t *__restrict__ tile_set,
+    const int64_t *__restrict__ set_off, int32_t nsets, int tile_keys,
+    uint32_t *__restrict__ set_counts, int high, uint64_t *__restrict__ status) {
+  constexpr int R = 1 << BITS;
+  __shared__ uint32_t h[kMaxKeyPasses << BITS];
+  if (*full == 0u) return;
+  for (int64_t tile = blockIdx.x; tile < tile_start[nsets]; tile += gridDim.x) {
+    for (int i = threadIdx.x; i < low.passes * R; i += blockDim.x) h[i] = 0;
+    __syncthreads();
+    const int b = tile_set[tile];
+    const int64_t lo = set_off[b] + (tile - tile_start[b]) * tile_keys;
+    const int64_t hi = min(lo + tile_keys, set_off[b + 1]);
+    for (int i = threadIdx.x; i < R; i += blockDim.x) status[tile * R + i] = 0;
+    for (int64_t i = lo + threadIdx.x; i < hi; i += blockDim.x) {
+      const uint64_t k = keys[i];
+      for (int p = 0; p < low.passes; ++p)
+        atomicAdd(&h[p * R + ((uint32_t)(k >> low.shift[p]) & (R - 1))], 1u);
+    }
+    __syncthreads();
+    uint32_t *dst = set_counts + ((int64_t)b * (high + low.passes) + high) * R;
+    for (int i = threadIdx.x; i < low.passes * R; i += blockDim.x)
+      if (h[i]) atomicAdd(&dst[i], h[i]);
+    __syncthreads();
+  }
+}
+
 int keygen_blocks(int64_t n) {
   // at least four keys per thread; enough workgroups to fill every CU
   int64_t b = (n + 4 * kKeygenThreads - 1) / (4 * kKeygenThreads);
-  if (b > kKeygenMaxBlocks) b = kKeygenMaxBlocks;
+  // (the sampler beside them makes it two workgroups a CU)
+  if (b > kKeygenMaxBlocks - 1) b = kKeygenMaxBlocks - 1;
   if (b < 1) b = 1;
   return (int)b;
 }
@@ -587,12 +779,13 @@ hipError_t launch_keygen(const Plan &p, const Work &w, const float *pos, const f
                          const tb_tree &out, hipStream_t s) {
   const int passes = p.key_passes;
   const int hil = (p.flags & TB_HILBERT) ? 1 : 0;
+  const int few = sample_count(p.n) < kSamples ? 1 : 0;
   if (!p.seg) {
     const int blocks = keygen_blocks(p.n);
 #define TB_KEYGEN(B)                                                                           \
-  k_keygen<B><<<blocks, kKeygenThreads, 0, s>>>(pos, mass, p.n, w.box, w.keys0, w.packed,      \
-                                                (p.counted & 1u) ? w.dig : nullptr, w.hist_part, passes, \
-                                                hil, out.status)
+  k_keygen<B><<<blocks + 1, kKeygenThreads, 0, s>>>(                                           \
+      pos, mass, p.n, w.box, w.keys0, w.packed, (p.counted & 1u) ? w.dig : nullptr, w.hist_part, \
+      passes, p.skip_bits, hil, few, sample_limit(p.n), w.counters + kFullSortCounter, out.status)
     switch (p.sort.bits) {
       case 8: TB_KEYGEN(8); break;
       case 9: TB_KEYGEN(9); break;
@@ -603,9 +796,10 @@ hipError_t launch_keygen(const Plan &p, const Work &w, const float *pos, const f
     // as many particles per workgroup as the single-set kernel at its largest grid
     const int blocks = 2 * keygen_blocks(p.n);
 #define TB_KEYGEN_SETS(B)                                                                      \
-  k_keygen_sets<B><<<(unsigned)blocks, kKeygenThreads, 0, s>>>(                                \
+  k_keygen_sets<B><<<(unsigned)blocks + 1, kKeygenThreads, 0, s>>>(                            \
       pos, mass, p.n, w.set_off, p.nsets, w.box, w.keys0, w.packed,                            \
-      (p.counted & 1u) ? w.dig : nullptr, w.seg_base, passes, hil, out.status)
+      (p.counted & 1u) ? w.dig : nullptr, w.seg_base, passes, passes + p.low_passes,           \
+      p.skip_bits, hil, few, sample_limit(p.n), w.counters + kFullSortCounter, out.status)
     switch (p.sort.bits) {
       case 8: TB_KEYGEN_SETS(8); break;
       case 9: TB_KEYGEN_SETS(9); break;
@@ -616,23 +810,46 @@ hipError_t launch_keygen(const Plan &p, const Work &w, const float *pos, const f
   return hipGetLastError();
 }
 
-hipError_t launch_hist_reduce(const Plan &p, const Work &w, hipStream_t s) {
+// The conditional passes' digits end where the upper ones start; the first may overlap
+// the second (sorting a bit twice changes nothing).
+int low_shift(const Plan &p, int pass) {
+  const int sh = p.skip_bits - p.sort.bits * (p.low_passes - pass);
+  return sh > 0 ? sh : 0;
+}
+
+template <int BITS>
+static hipError_t hist_reduce_t(const Plan &p, const Work &w, hipStream_t s) {
   // each set's digit counts become its digit bases (a single set: once, rather
   // than in every tile of a pass)
+  const uint32_t *full = w.counters + kFullSortCounter;
+  LowDigits low = {p.low_passes, {}};
+  for (int k = 0; k < p.low_passes; ++k) low.shift[k] = low_shift(p, k);
+  // the first low pass's look-back words (see launch_low_passes)
+  uint64_t *status = p.low_passes % 2 ? w.status1 : w.status0;
+  const int64_t tiles = p.sort_tiles;
+  const unsigned low_blocks = (unsigned)(tiles < 512 ? tiles : 512);
   uint32_t *counts = w.seg_base;
   if (!p.seg) {
-    const int cols = p.key_passes * p.sort.radix();
-    k_hist_reduce<<<(cols + 15) / 16, 256, 0, s>>>(w.hist_part, keygen_blocks(p.n), cols, w.hist);
+    const int cols = p.key_passes << BITS;
+    k_hist_reduce<BITS><<<(cols + 15) / 16 + low_blocks, 256, 0, s>>>(
+        w.hist_part, keygen_blocks(p.n), cols, w.hist, full, w.keys0, p.n, low, status,
+        tiles << BITS);
     counts = w.hist;
+  } else {
+    k_low_counts_sets<BITS><<<low_blocks, 256, 0, s>>>(
+        full, w.keys0, low, w.seg_tile_start, w.seg_tile_set, w.set_off, p.nsets, p.sort.tile(),
+        counts, p.key_passes, status);
   }
-  const dim3 grid((unsigned)(p.nsets < 65535 ? p.nsets : 65535), (unsigned)p.key_passes);
-  if (p.sort.bits == 8)
-    k_set_base<8><<<grid, 256, 0, s>>>(w.set_off, counts, p.key_passes, p.nsets);
-  else if (p.sort.bits == 9)
-    k_set_base<9><<<grid, 512, 0, s>>>(w.set_off, counts, p.key_passes, p.nsets);
-  else
-    return hipErrorInvalidValue;
+  const int passes = p.key_passes + p.low_passes;
+  const dim3 grid((unsigned)(p.nsets < 65535 ? p.nsets : 65535), (unsigned)passes);
+  k_set_base<BITS><<<grid, 1 << BITS, 0, s>>>(w.set_off, counts, passes, p.nsets);
   return hipGetLastError();
+}
+
+hipError_t launch_hist_reduce(const Plan &p, const Work &w, hipStream_t s) {
+  if (p.sort.bits == 8) return hist_reduce_t<8>(p, w, s);
+  if (p.sort.bits == 9) return hist_reduce_t<9>(p, w, s);
+  return hipErrorInvalidValue;
 }
 
 // ---------------------------------------------------------------------------

@@ -14,8 +14,12 @@
 //     written so that consecutive lanes store consecutive addresses of a digit
 //     run.
 // The global digit counts come from the key-generation pass (and become each
-// digit's base once per build), so the keys are read only once per pass.  The
-// index payload of the last pass is `perm`.
+// digit's base once per build), so the keys are read only once per pass.
+//
+// The passes sort the upper 32 or 40 bits of the 63 (make_plan has the rule).  The
+// reorder orders the particles that agree in those by the rest of their keys and
+// writes perm.  Passes over the low bits come first when the key kernel's sample has
+// found that the keys crowd; they are launched in any case and return at once if not.
 //
 // By default the passes of a single set are "counted" instead (reduce, then
 // scan; a batch with TB_SORT_COUNTED too): a first kernel reads each element's
@@ -31,12 +35,12 @@
 // bases taken from its own digit counts (counted per set by the key kernel).
 // The passes thus give the (set, key) order with no pass over the set id.
 //
-// Elements shrink as the passes go: a pass carries only the key bits later
-// passes still need.  The first passes move the 64-bit key and the index in two
-// arrays (12 bytes); once the key bits left fit beside the index in 64 or 32
-// bits, both travel as one packed word, (key >> consumed bits) << idx_bits |
-// index, whose digit is read at bit idx_bits.  The last pass writes the index
-// alone.  The sorted keys themselves are recomputed from the sorted particles in
+// Elements shrink as the passes go: a pass carries only the key bits later passes
+// still need.  The first reads the 64-bit key and writes it, without the bits that are
+// consumed or not sorted, over the index in one packed word, (key bits << idx_bits) |
+// index, whose digit is read at bit idx_bits; once both fit in 32 bits the word has 32.
+// The last pass writes the index alone.  (The low passes move whole keys and indices in
+// two arrays.)  The sorted keys themselves are recomputed from the sorted particles in
 // the reorder pass, which reads those particles anyway.
 #include "tb_internal.h"
 
@@ -419,32 +423,38 @@ __device__ __forceinline__ void sweep_scatter(const typename S::Lds &L, uint32_t
 // 28-byte spill; the 4096-set batch's sort 6.45 -> 6.34 ms), while the counted
 // single-set pass loses more to its spill than it gains (sort 0.79 -> 0.87 ms)
 // and larger tiles leave no LDS for a third workgroup.
-template <int BITS, int IPT, int THREADS, int FIN, bool COUNTED, bool SEG>
+// The conditional passes' loop over tiles is held to four waves (two workgroups a CU)
+// where the LDS of two fits.
+template <int BITS, int IPT, int THREADS, int FIN, int FOUT, bool COUNTED, bool SEG>
 constexpr int sweep_waves() {
+  if (FIN == kFormKey64 && FOUT == kFormKey64) return THREADS == 512 && IPT <= 11 ? 4 : 1;
   if (BITS != 8) return 1;
   if (FIN == kFormPack32) return 6;
   if (FIN == kFormPack64 && SEG && !COUNTED && THREADS == 512 && THREADS * IPT <= 5120) return 6;
   return 1;
 }
 
+// One tile of a pass; false when the pass has no more.
 template <int BITS, int IPT, int THREADS, int FIN, int FOUT, bool COUNTED, bool SEG>
-__global__ __launch_bounds__(THREADS, (sweep_waves<BITS, IPT, THREADS, FIN, COUNTED, SEG>())) void k_onesweep(
-    const void *__restrict__ kin_v, void *__restrict__ kout_v,
-    const uint32_t *__restrict__ vin, uint32_t *__restrict__ vout, uint32_t n, int shift,
-    int ib, const uint32_t *__restrict__ hist, uint64_t *__restrict__ status,
-    uint64_t *__restrict__ status_next, uint32_t *__restrict__ tile_counter,
-    const uint32_t *__restrict__ tile_off, int32_t *__restrict__ status_word, uint32_t n_tiles,
-    SegTiles seg, void *__restrict__ dig_out) {
+__device__ __forceinline__ bool sweep_tile(
+    typename Sweep<BITS, IPT, THREADS, FIN, FOUT>::Lds &L, const void *__restrict__ kin_v,
+    void *__restrict__ kout_v, const uint32_t *__restrict__ vin, uint32_t *__restrict__ vout,
+    uint32_t n, int shift, int ib, const uint32_t *__restrict__ hist,
+    uint64_t *__restrict__ status, uint64_t *__restrict__ status_next,
+    uint32_t *__restrict__ tile_counter, const uint32_t *__restrict__ tile_off,
+    int32_t *__restrict__ status_word, uint32_t n_tiles, const SegTiles &seg,
+    void *__restrict__ dig_out) {
   using S = Sweep<BITS, IPT, THREADS, FIN, FOUT>;
   using KI = typename S::KI;
   constexpr int R = S::R, WAVES = S::WAVES, TILE = S::TILE, DPT = S::DPT;
-  __shared__ typename S::Lds L;
+  constexpr bool LOW = FIN == kFormKey64 && FOUT == kFormKey64;
   const KI *__restrict__ kin = static_cast<const KI *>(kin_v);
   typename S::KO *__restrict__ kout = static_cast<typename S::KO *>(kout_v);
   constexpr bool batch = SEG;
 
   // Look-back passes take tiles in the order they start, so that every earlier
-  // tile is already running; counted passes need no order.
+  // tile is already running; counted passes need no order.  The conditional passes'
+  // workgroups take tile after tile.
   if (!COUNTED && threadIdx.x == 0) L.tile = atomicAdd(tile_counter, 1u);
   for (int i = threadIdx.x; i < WAVES * R; i += THREADS) L.wc[i] = 0;
   __syncthreads();
@@ -453,8 +463,8 @@ __global__ __launch_bounds__(THREADS, (sweep_waves<BITS, IPT, THREADS, FIN, COUN
   const uint32_t tiles_here = batch ? (uint32_t)seg.tile_start[seg.nsets] : n_tiles;
   if (tile >= tiles_here) {
     // a single set launches one workgroup per tile: the counter was not reset
-    if (!batch && threadIdx.x == 0) atomicOr(status_word, TB_STATUS_INTERNAL);
-    return;
+    if (!LOW && !batch && threadIdx.x == 0) atomicOr(status_word, TB_STATUS_INTERNAL);
+    return false;
   }
   // the tile's elements [lo, lo + tile_n); its set's first tile starts the look-back
   uint32_t lo = tile * (uint32_t)TILE, hi = n, set_lo = 0u, set_tile0 = 0u;
@@ -483,6 +493,11 @@ __global__ __launch_bounds__(THREADS, (sweep_waves<BITS, IPT, THREADS, FIN, COUN
   KI k[IPT];
   uint32_t v[IPT];
   sweep_load<S, IPT>(kin, vin, wbase, last, set_lo, k, v);
+  if constexpr (FIN == kFormKey64 && !LOW) {
+    // the leading 1 is no part of the packed word
+#pragma unroll
+    for (int j = 0; j < IPT; ++j) k[j] &= ~(1ull << 63);
+  }
 
   uint32_t tcnt[DPT], trun_d[DPT];
   sweep_rank<S, BITS, IPT, THREADS, !COUNTED>(L, k, v, wbase, last, shift, status, tile, first,
@@ -517,26 +532,51 @@ __global__ __launch_bounds__(THREADS, (sweep_waves<BITS, IPT, THREADS, FIN, COUN
   sweep_scatter<S, BITS, THREADS, FOUT>(L, tile_n, shift, ib, set_lo, hi, kout, vout,
                                         static_cast<DigitType<BITS> *>(dig_out), bad);
   if (__ballot(bad) != 0 && lane_id() == 0) atomicOr(status_word, TB_STATUS_INTERNAL);
+  return true;
 }
 
+template <int BITS, int IPT, int THREADS, int FIN, int FOUT, bool COUNTED, bool SEG>
+__global__ __launch_bounds__(THREADS, (sweep_waves<BITS, IPT, THREADS, FIN, FOUT, COUNTED, SEG>())) void k_onesweep(
+    const void *__restrict__ kin, void *__restrict__ kout, const uint32_t *__restrict__ vin,
+    uint32_t *__restrict__ vout, uint32_t n, int shift, int ib, const uint32_t *__restrict__ hist,
+    uint64_t *__restrict__ status, uint64_t *__restrict__ status_next,
+    uint32_t *__restrict__ tile_counter, const uint32_t *__restrict__ tile_off,
+    int32_t *__restrict__ status_word, uint32_t n_tiles, SegTiles seg, void *__restrict__ dig_out,
+    const uint32_t *__restrict__ full) {
+  __shared__ typename Sweep<BITS, IPT, THREADS, FIN, FOUT>::Lds L;
+  // A pass over 64-bit keys that writes them whole sorts low bits, if the sample asked
+  // for it; the first pass over the upper bits takes their order then, else the input's.
+  constexpr bool LOW = FIN == kFormKey64 && FOUT == kFormKey64;
+  if constexpr (FIN == kFormKey64) {
+    if (*full == 0u) {
+      if constexpr (LOW) return;
+      vin = nullptr;
+    }
+  }
+  if constexpr (LOW) {
+    while (sweep_tile<BITS, IPT, THREADS, FIN, FOUT, COUNTED, SEG>(
+        L, kin, kout, vin, vout, n, shift, ib, hist, status, status_next, tile_counter, tile_off,
+        status_word, n_tiles, seg, dig_out))
+      __syncthreads();  // the tile's LDS is read out
+  } else {
+    sweep_tile<BITS, IPT, THREADS, FIN, FOUT, COUNTED, SEG>(
+        L, kin, kout, vin, vout, n, shift, ib, hist, status, status_next, tile_counter, tile_off,
+        status_word, n_tiles, seg, dig_out);
+  }
+}
+
+// One launch of a pass: pass p.key_passes + k is the conditional low pass k.
 template <int BITS, int IPT, int THREADS, int FIN, int FOUT, bool COUNTED>
-static hipError_t launch_pass_k(const Plan &p, const Work &w, int pass, const tb_tree &out,
-                                hipStream_t s) {
-  const int P = p.key_passes;
-  void *K[2] = {w.keys0, w.keys1};
-  // the last pass must write its index into out.perm
-  uint32_t *V[2];
-  V[P % 2] = reinterpret_cast<uint32_t *>(out.perm);
-  V[(P + 1) % 2] = w.vals1;
-  uint64_t *S[2] = {w.status0, w.status1};
-  const uint32_t *vin = (pass == 0 || FIN != kFormKey64) ? nullptr : V[pass % 2];
+static hipError_t launch_sweep(const Plan &p, const Work &w, int pass, const void *kin, void *kout,
+                               const uint32_t *vin, uint32_t *vout, int shift, uint64_t *status,
+                               uint64_t *status_next, void *dig_out, const tb_tree &out,
+                               hipStream_t s) {
   const int R = 1 << BITS;
-  const int shift = FIN == kFormKey64 ? pass * BITS : p.idx_bits;
   SegTiles seg{nullptr, nullptr, nullptr, 0, p.nsets};
   const uint32_t *hist = w.hist + (size_t)pass * R;
   if (p.seg) {
-    seg = SegTiles{w.seg_tile_start, w.seg_tile_set, w.set_off, (size_t)p.key_passes * R,
-                   p.nsets};
+    seg = SegTiles{w.seg_tile_start, w.seg_tile_set, w.set_off,
+                   (size_t)(p.key_passes + p.low_passes) * R, p.nsets};
     hist = w.seg_base + (size_t)pass * R;
   }
   if constexpr (COUNTED) {
@@ -548,35 +588,42 @@ static hipError_t launch_pass_k(const Plan &p, const Work &w, int pass, const tb
     // tile, so the scan's prefixes for the real tiles are unaffected
     k_tile_scan<1024><<<R, 1024, 0, s>>>(w.tile_off, (uint32_t)p.sort_tiles);
   }
-  // a counted pass that follows needs this pass to leave its digits behind
-  void *dig_out = (pass + 1 < P && ((p.counted >> (pass + 1)) & 1u)) ? w.dig : nullptr;
   auto k = p.seg ? k_onesweep<BITS, IPT, THREADS, FIN, FOUT, COUNTED, true>
                  : k_onesweep<BITS, IPT, THREADS, FIN, FOUT, COUNTED, false>;
-  k<<<(unsigned)p.sort_tiles, THREADS, 0, s>>>(
-      K[pass % 2], K[(pass + 1) % 2], vin, V[(pass + 1) % 2], (uint32_t)p.n, shift, p.idx_bits,
-      hist, S[pass % 2], S[(pass + 1) % 2], w.counters + pass, w.tile_off, out.status,
-      (uint32_t)p.sort_tiles, seg, dig_out);
+  // (a small grid of the conditional passes returns sooner when there is nothing to do;
+  // at 2^26 6.8 us with a workgroup a tile, 3.8 us so)
+  constexpr bool kLow = FIN == kFormKey64 && FOUT == kFormKey64;
+  const int64_t grid = kLow && p.sort_tiles > 512 ? 512 : p.sort_tiles;
+  k<<<(unsigned)grid, THREADS, 0, s>>>(
+      kin, kout, vin, vout, (uint32_t)p.n, shift, p.idx_bits, hist, status, status_next,
+      w.counters + pass, w.tile_off, out.status, (uint32_t)p.sort_tiles, seg, dig_out,
+      w.counters + kFullSortCounter);
   return hipGetLastError();
 }
 
 template <int BITS, int IPT, int THREADS, int FIN, int FOUT>
 static hipError_t launch_pass_c(const Plan &p, const Work &w, int pass, const tb_tree &out,
                                 hipStream_t s) {
-  return ((p.counted >> pass) & 1u)
-             ? launch_pass_k<BITS, IPT, THREADS, FIN, FOUT, true>(p, w, pass, out, s)
-             : launch_pass_k<BITS, IPT, THREADS, FIN, FOUT, false>(p, w, pass, out, s);
+  const int P = p.key_passes;
+  void *K[2] = {w.keys0, w.keys1};
+  uint64_t *S[2] = {w.status0, w.status1};
+  const int shift = FIN == kFormKey64 ? p.skip_bits : p.idx_bits;
+  // a counted pass that follows needs this pass to leave its digits behind
+  void *dig_out = (pass + 1 < P && ((p.counted >> (pass + 1)) & 1u)) ? w.dig : nullptr;
+  auto go = ((p.counted >> pass) & 1u) ? launch_sweep<BITS, IPT, THREADS, FIN, FOUT, true>
+                                       : launch_sweep<BITS, IPT, THREADS, FIN, FOUT, false>;
+  // vals1: the low passes' indices in (first pass), the sorted indices out (last pass)
+  return go(p, w, pass, K[pass % 2], K[(pass + 1) % 2], w.vals1, w.vals1, shift, S[pass % 2],
+            S[(pass + 1) % 2], dig_out, out, s);
 }
 
-// The format pairs make_plan produces for 8- and 9-bit digits and any N below
-// 2^32 (a 64-bit key is packed by the time 32 of its bits are consumed, since the
-// 32 bits left and at most 32 index bits fit in 64).
+// The format pairs make_plan produces for 8- and 9-bit digits and any N below 2^31.
 template <int BITS, int IPT, int THREADS>
 static hipError_t launch_pass_t(const Plan &p, const Work &w, int pass, const tb_tree &out,
                                 hipStream_t s) {
   const int fi = p.form[pass], fo = p.form[pass + 1];
 #define TB_PAIR(FI, FO) \
   if (fi == FI && fo == FO) return launch_pass_c<BITS, IPT, THREADS, FI, FO>(p, w, pass, out, s);
-  TB_PAIR(kFormKey64, kFormKey64)
   TB_PAIR(kFormKey64, kFormPack64)
   TB_PAIR(kFormPack64, kFormPack64)
   TB_PAIR(kFormPack64, kFormPack32)
@@ -587,19 +634,55 @@ static hipError_t launch_pass_t(const Plan &p, const Work &w, int pass, const tb
   return hipErrorInvalidValue;
 }
 
+// The conditional passes over the low key bits, before the others: whole keys and
+// their indices from keys0 through the space of the sorted records and back to keys0,
+// the indices through perm and vals1 to vals1.  They look back whatever the others do
+// (their launches return at once unless the sample asked for them), on the look-back
+// words that leave status0 clear for the first pass that follows.
+template <int BITS, int IPT, int THREADS>
+static hipError_t launch_low_t(const Plan &p, const Work &w, const tb_tree &out, hipStream_t s) {
+  const int L = p.low_passes;
+  uint64_t *A = reinterpret_cast<uint64_t *>(w.sorted);
+  uint64_t *K[2] = {A, A + p.n};
+  uint32_t *V[2] = {w.vals1, reinterpret_cast<uint32_t *>(out.perm)};
+  uint64_t *S[2] = {w.status0, w.status1};
+  const uint64_t *kin = w.keys0;
+  const uint32_t *vin = nullptr;
+  for (int k = 0; k < L; ++k) {
+    const bool last = k + 1 == L;
+    uint64_t *kout = last ? w.keys0 : K[k % 2];
+    uint32_t *vout = V[(L - 1 - k) % 2];
+    void *dig_out = last && (p.counted & 1u) ? w.dig : nullptr;
+    const hipError_t e = launch_sweep<BITS, IPT, THREADS, kFormKey64, kFormKey64, false>(
+        p, w, p.key_passes + k, kin, kout, vin, vout, low_shift(p, k), S[(k + L) % 2],
+        S[(k + L + 1) % 2], dig_out, out, s);
+    if (e != hipSuccess) return e;
+    kin = kout;
+    vin = vout;
+  }
+  return hipSuccess;
+}
+
+#define TB_SORT_SHAPES(CASE)                                                        \
+  CASE(8, 11, 512) CASE(8, 12, 512) CASE(8, 10, 512) CASE(8, 16, 256) CASE(9, 16, 256) \
+  CASE(8, 12, 256) CASE(8, 8, 512)
+
 hipError_t launch_sort_pass(const Plan &p, const Work &w, int pass, const tb_tree &out,
                             hipStream_t s) {
   const SortConfig &c = p.sort;
 #define TB_SORT_CASE(B, I, T)                                         \
   if (c.bits == B && c.ipt == I && c.threads == T)                    \
     return launch_pass_t<B, I, T>(p, w, pass, out, s);
-  TB_SORT_CASE(8, 11, 512)
-  TB_SORT_CASE(8, 12, 512)
-  TB_SORT_CASE(8, 10, 512)
-  TB_SORT_CASE(8, 16, 256)
-  TB_SORT_CASE(9, 16, 256)
-  TB_SORT_CASE(8, 12, 256)
-  TB_SORT_CASE(8, 8, 512)
+  TB_SORT_SHAPES(TB_SORT_CASE)
+#undef TB_SORT_CASE
+  return hipErrorInvalidValue;
+}
+
+hipError_t launch_low_passes(const Plan &p, const Work &w, const tb_tree &out, hipStream_t s) {
+  const SortConfig &c = p.sort;
+#define TB_SORT_CASE(B, I, T)                                         \
+  if (c.bits == B && c.ipt == I && c.threads == T) return launch_low_t<B, I, T>(p, w, out, s);
+  TB_SORT_SHAPES(TB_SORT_CASE)
 #undef TB_SORT_CASE
   return hipErrorInvalidValue;
 }
