@@ -57,7 +57,8 @@ int make_plan(int64_t n, int32_t nsets, int32_t n_leaf, uint32_t flags, const So
   // n 2^(18 - bits) particles: mean run (by particle) 3.5 for 2^18 in 32 bits, 1.7 for
   // 2^24 in 40, and 0.1 % of the particles in runs past 32 for 2^26 clustered ones in
   // 40.  Data that is denser than that is seen by a sample of the keys, which turns on
-  // the passes over the low bits.  Sort of 2^24
+  // the passes over the low bits (as does n_leaf > 95, whose windows the reorder cannot
+  // hold twice).  Sort of 2^24
   // with all that goes with it: 470 us against 788 in all 63 bits.
   const int64_t typical =
       p->set_index_bits > 0 ? int64_t{1} << p->set_index_bits : p->seg ? 8 * (n / nsets) : n;
@@ -337,8 +338,11 @@ static int build_impl(const float *pos, const float *mass, int64_t n, int32_t ns
     run("upper", [&] { return launch_upper(p, w, *out, s); });
   } else {
     run("cell_emit", [&] { return launch_cell_emit(p, w, *out, s); });
-    for (int d = kMaxDepth - 1; d >= 0; --d)
-      run("parents", [&] { return launch_parents(p, w, d, *out, s); });
+    if (owned_parents(p))
+      run("parents", [&] { return launch_owned_parents(p, w, *out, s); });
+    else
+      for (int d = kMaxDepth - 1; d >= 0; --d)
+        run("parents", [&] { return launch_parents(p, w, d, *out, s); });
   }
   return e == hipSuccess ? TB_OK : TB_ERR_HIP;
 }

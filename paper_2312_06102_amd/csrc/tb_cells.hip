@@ -39,25 +39,25 @@ constexpr int kMaxSpan = (kCellTile + TB_MAX_NLEAF + kCellThreads - 1) / kCellTh
 __host__ __device__ constexpr size_t round16(size_t x) { return (x + 15) & ~size_t(15); }
 
 // Particles of the reorder's window: the tile, the n_leaf + 1 before and n_leaf after
-// it, and kRunCap more on either side.
-__host__ __device__ constexpr int window_size(int tile, int nl) {
-  return tile + 2 * nl + 1 + 2 * kRunCap;
+// it, and `ext` more on either side.
+__host__ __device__ constexpr int window_size(int tile, int nl, int ext) {
+  return tile + 2 * nl + 1 + 2 * ext;
 }
-// The window's particles a thread gathers at once; up to this many its thread keeps
-// them (n_leaf <= 95), larger windows are gathered twice.
+// The window's particles a thread gathers at once.  If that holds the window with the
+// ends of its runs (n_leaf <= 95) the reorder finishes the sort; larger windows get
+// particles that the radix passes have sorted by their whole keys (make_plan).
 constexpr int kWindowIpt = kCellIpt + 1;
-__host__ __device__ constexpr bool window_kept(int nl) {
-  return window_size(kCellTile, nl) <= kWindowIpt * kCellThreads;
+__host__ __device__ constexpr int window_ext(int nl) {
+  return window_size(kCellTile, nl, kRunCap) <= kWindowIpt * kCellThreads ? kRunCap : 0;
 }
+bool reorder_finishes(int nl) { return window_ext(nl) != 0; }
 
 // Shared layout of the reorder pass (dynamic LDS, sized for the actual n_leaf).
 struct WindowLds {
-  uint64_t *raw;   // [window]        keys in the order the radix passes left; the window's
-                   //                 place of each particle (u16) after them if not kept
-  uint16_t *place;
-  uint64_t *fin;   // [window]        keys in their final order (the same array if kept)
+  uint64_t *raw;   // [window]        keys in the order the radix passes left, then the
+                   //                 final one
   uint64_t *heads; // [window / 64]   where the window's runs start, a word of ones before
-                   //                 and after them
+                   //                 and after them (if the reorder finishes the sort)
   uint64_t *keys;  // [T + 2 NL + 1]  the final keys of [t0 - NL - 1, t1 + NL)
   uint8_t *m;      // [T + NL]        w_j, then the sparse max table, j in [t0 - NL, t1)
   uint8_t *a;      // [T + NL]        a_i, i in [t0, t1 + NL)
@@ -65,33 +65,24 @@ struct WindowLds {
 };
 
 __host__ __device__ inline size_t window_keys_bytes(int nl) {
-  return round16((size_t)window_size(kCellTile, nl) * 8);
+  return round16((size_t)window_size(kCellTile, nl, window_ext(nl)) * 8);
 }
 
 // (rows of kCellThreads particles, kWaves words each)
 __host__ __device__ inline size_t window_heads_bytes(int nl) {
-  const int rows = (window_size(kCellTile, nl) + kCellThreads - 1) / kCellThreads;
-  return round16((size_t)(rows * kWaves + 2) * 8);
+  return window_ext(nl) ? round16((size_t)(kWindowIpt * kWaves + 2) * 8) : 0;
 }
 
 __host__ __device__ inline size_t window_lds_bytes(int nl) {
-  const size_t keys = window_keys_bytes(nl);
-  return window_heads_bytes(nl) + keys + (window_kept(nl) ? 0 : keys + round16((size_t)window_size(kCellTile, nl) * 2)) +
-         2 * round16(kCellTile + nl) + (size_t)kWaves * kLevelWords * 4;
+  return window_keys_bytes(nl) + window_heads_bytes(nl) + 2 * round16(kCellTile + nl) +
+         (size_t)kWaves * kLevelWords * 4;
 }
 
 __device__ inline WindowLds carve_window(unsigned char *base, int nl) {
   WindowLds s;
-  s.raw = s.fin = reinterpret_cast<uint64_t *>(base);
-  s.place = nullptr;
+  s.raw = reinterpret_cast<uint64_t *>(base);
+  s.keys = s.raw + window_ext(nl);
   base += window_keys_bytes(nl);
-  if (!window_kept(nl)) {
-    s.fin = reinterpret_cast<uint64_t *>(base);
-    base += window_keys_bytes(nl);
-    s.place = reinterpret_cast<uint16_t *>(base);
-    base += round16((size_t)window_size(kCellTile, nl) * 2);
-  }
-  s.keys = s.fin + kRunCap;
   s.heads = reinterpret_cast<uint64_t *>(base);
   base += window_heads_bytes(nl);
   s.m = base;
@@ -271,8 +262,8 @@ struct ReorderArgs {
 // of ones.
 __device__ __forceinline__ uint64_t *run_heads(const WindowLds &s) { return s.heads + 1; }
 
-// Places in the window of N particles, those at i0 + r * kCellThreads (i0 = threadIdx.x +
-// whole rows of threads, so a wave holds 64 particles of one word): the number of the
+// Places in the window of N particles, those at i0 + r * kCellThreads (i0 = threadIdx.x,
+// so a wave holds 64 particles of one word): the number of the
 // run's particles with smaller keys, or equal ones before it, after the run's start.
 // Keys of a run differ below bit 31 only.  All of a thread's particles meet the d-th
 // next of their runs (cyclically) in one step, as long as a run in the wave has more.
@@ -331,25 +322,43 @@ __device__ inline bool run_places(const WindowLds &s, int i0, int wn, const uint
   return any;
 }
 
-// KEPT: the window's records stay with the threads that gathered them.
-template <bool KEPT>
+// FINISH: the window's records stay with the threads that gathered them until the
+// particles' places are known.
+template <bool FINISH>
 __device__ inline void reorder_tile(const ReorderArgs &g, const WindowLds &s, int64_t tile,
                                     bool again) {
   // a batch set over the caller's index bound: every particle gets the root key
   const bool flat = g.oversize && *g.oversize != 0u;
-  const bool whole = flat || *g.full != 0u;  // the order is final
   const int nl = g.nl;
   const TileRange tr = tile_range(tile, g.tile_start, g.tile_set, g.set_off);
   const int64_t t0 = tr.t0, t1 = tr.t1;
   const double lo0 = g.box[4 * tr.b + 0], lo1 = g.box[4 * tr.b + 1], lo2 = g.box[4 * tr.b + 2];
   const double scale = 2097152.0 / g.box[4 * tr.b + 3];
   const int T = (int)(t1 - t0);
-  const int64_t ws = t0 - nl - 1 - kRunCap;  // window start (may be negative)
-  const int wn = window_size(T, nl);
+  constexpr int kExt = FINISH ? kRunCap : 0;
+  const int64_t ws = t0 - nl - 1 - kExt;  // window start (may be negative)
+  const int wn = window_size(T, nl, kExt);
   constexpr int kBatch = kWindowIpt;
   bool internal = false, bad = false;
   int32_t p[kBatch];
   float4 rec[kBatch];
+  // particle r of a thread's batch to place i of the window
+  auto put = [&](int r, int i, uint64_t key) {
+    const int64_t q = ws + i;
+    if (q < t0 || q >= t1) return;
+    g.sorted[q] = rec[r];
+    g.keys[q] = key;
+    g.perm[q] = p[r];
+    if (g.key_out) g.key_out[q] = key;
+    bad |= !(rec[r].w > 0.0f && isfinite(rec[r].w));
+    if (g.pos_sorted) {
+      g.pos_sorted[3 * q + 0] = rec[r].x;
+      g.pos_sorted[3 * q + 1] = rec[r].y;
+      g.pos_sorted[3 * q + 2] = rec[r].z;
+    }
+    if (g.mass_sorted) g.mass_sorted[q] = rec[r].w;
+  };
+  // particles i0 + r * kCellThreads + threadIdx.x of the window
   auto gather = [&](int i0) {
 #pragma unroll
     for (int r = 0; r < kBatch; ++r) {
@@ -367,9 +376,6 @@ __device__ inline void reorder_tile(const ReorderArgs &g, const WindowLds &s, in
       internal |= in && !ok;
       rec[r] = g.packed[ok ? p[r] : 0];
     }
-  };
-  for (int i0 = 0; i0 < wn; i0 += kBatch * kCellThreads) {
-    gather(i0);
 #pragma unroll
     for (int r = 0; r < kBatch; ++r) {
       const int i = i0 + r * kCellThreads + threadIdx.x;
@@ -381,99 +387,58 @@ __device__ inline void reorder_tile(const ReorderArgs &g, const WindowLds &s, in
               ? 1ull << 63
               : particle_key(rec[r].x, rec[r].y, rec[r].z, lo0, lo1, lo2, scale, g.hilbert != 0);
       if (i < wn) s.raw[i] = key;
+      if (!FINISH && i < wn) put(r, i, key);
     }
-    if (KEPT) break;  // one batch holds the window
-  }
-  __syncthreads();
-
-  // every particle's place
-  constexpr int kRow = KEPT ? kBatch : 1;
-  uint64_t key[kBatch];
-  int place[kBatch];
-  bool longer = false;
-  if (!whole) {
-    const int rows = (wn + kCellThreads - 1) / kCellThreads;
-    for (int r = 0; r < rows; ++r) {
-      const int i = r * kCellThreads + threadIdx.x;
-      bool head = true;
-      if (i > 0 && i < wn) {
-        const uint64_t k = s.raw[i];
-        head = k == 0ull || ((k ^ s.raw[i - 1]) >> g.skip) != 0;
-      }
-      const uint64_t m = __ballot(head);
-      if (lane_id() == 0) run_heads(s)[i / 64] = m;
-    }
-    if (threadIdx.x == 0) run_heads(s)[-1] = run_heads(s)[rows * kWaves] = ~0ull;
+  };
+  if constexpr (!FINISH) {
+    for (int i0 = 0; i0 < wn; i0 += kBatch * kCellThreads) gather(i0);
+  } else {
+    gather(0);
     __syncthreads();
-  }
-  for (int i0 = threadIdx.x; i0 < (KEPT ? kCellThreads : wn); i0 += kRow * kCellThreads) {
-    uint64_t k[kRow];
-    int at[kRow];
+    uint64_t key[kBatch];
+    int place[kBatch];
 #pragma unroll
-    for (int r = 0; r < kRow; ++r) {
-      const int i = i0 + r * kCellThreads;
-      k[r] = i < wn ? s.raw[i] : 0ull;
-      at[r] = i;
+    for (int r = 0; r < kBatch; ++r) {
+      const int i = r * kCellThreads + threadIdx.x;
+      key[r] = i < wn ? s.raw[i] : 0ull;
     }
+    const bool whole = flat || *g.full != 0u;  // the order is final
+    bool longer = false;
     if (!whole) {
-      uint32_t first;
-      if (run_places<kRow>(s, i0, wn, k, at, &first)) {
-        longer = true;
-#pragma unroll
-        for (int r = 0; r < kRow; ++r) {
-          const int64_t q = ws + i0 + r * kCellThreads;
-          if (((first >> r) & 1u) && !again && q >= t0 && q < t1)
-            g.runs[atomicAdd(g.n_runs, 1u)] = (int32_t)q;
-        }
-      }
-    }
-    if (KEPT) {
-#pragma unroll
-      for (int r = 0; r < kRow; ++r) {
-        key[r] = k[r];
-        place[r] = at[r];
-      }
-    } else {
-      s.place[i0] = (uint16_t)at[0];
-      s.fin[at[0]] = k[0];
-    }
-  }
-  const bool stop = __syncthreads_or(longer ? 1 : 0) != 0 && !again;
-  if (stop) {
-    if (threadIdx.x == 0) g.run_tiles[atomicAdd(g.n_run_tiles, 1u)] = (int32_t)tile;
-    return;
-  }
-  for (int i0 = 0; i0 < wn; i0 += kBatch * kCellThreads) {
-    if (!KEPT) {
-      gather(i0);
 #pragma unroll
       for (int r = 0; r < kBatch; ++r) {
-        const int i = i0 + r * kCellThreads + threadIdx.x;
-        key[r] = i < wn ? s.raw[i] : 0ull;
-        place[r] = i < wn ? s.place[i] : 0;
+        const int i = r * kCellThreads + threadIdx.x;
+        bool head = true;
+        if (i > 0 && i < wn) head = key[r] == 0ull || ((key[r] ^ s.raw[i - 1]) >> g.skip) != 0;
+        const uint64_t m = __ballot(head);
+        if (lane_id() == 0) run_heads(s)[i / 64] = m;
       }
+      if (threadIdx.x == 0) run_heads(s)[-1] = run_heads(s)[kBatch * kWaves] = ~0ull;
+      __syncthreads();
+      uint32_t first;
+      longer = run_places<kBatch>(s, threadIdx.x, wn, key, place, &first);
+#pragma unroll
+      for (int r = 0; r < kBatch; ++r) {
+        const int64_t q = ws + r * kCellThreads + threadIdx.x;
+        if (((first >> r) & 1u) && !again && q >= t0 && q < t1)
+          g.runs[atomicAdd(g.n_runs, 1u)] = (int32_t)q;
+      }
+    } else {
+#pragma unroll
+      for (int r = 0; r < kBatch; ++r) place[r] = r * kCellThreads + threadIdx.x;
+    }
+    // (every thread has read the keys it looks at)
+    const bool stop = __syncthreads_or(longer ? 1 : 0) != 0 && !again;
+    if (stop) {
+      if (threadIdx.x == 0) g.run_tiles[atomicAdd(g.n_run_tiles, 1u)] = (int32_t)tile;
+      return;
     }
 #pragma unroll
     for (int r = 0; r < kBatch; ++r) {
-      const int i = i0 + r * kCellThreads + threadIdx.x;
-      if (i >= wn) continue;
-      if (KEPT) s.fin[place[r]] = key[r];
-      const int64_t q = ws + place[r];
-      if (q >= t0 && q < t1) {
-        g.sorted[q] = rec[r];
-        g.keys[q] = key[r];
-        g.perm[q] = p[r];
-        if (g.key_out) g.key_out[q] = key[r];
-        bad |= !(rec[r].w > 0.0f && isfinite(rec[r].w));
-        if (g.pos_sorted) {
-          g.pos_sorted[3 * q + 0] = rec[r].x;
-          g.pos_sorted[3 * q + 1] = rec[r].y;
-          g.pos_sorted[3 * q + 2] = rec[r].z;
-        }
-        if (g.mass_sorted) g.mass_sorted[q] = rec[r].w;
-      }
+      if (r * kCellThreads + (int)threadIdx.x >= wn) continue;
+      s.raw[place[r]] = key[r];
+      put(r, place[r], key[r]);
     }
-    if (KEPT) break;
   }
   if (__ballot(bad) != 0 && lane_id() == 0) atomicOr(g.status_word, TB_STATUS_MASS);
   if (__ballot(internal) != 0 && lane_id() == 0) atomicOr(g.status_word, TB_STATUS_INTERNAL);
@@ -499,21 +464,20 @@ __device__ inline void reorder_tile(const ReorderArgs &g, const WindowLds &s, in
   }
 }
 
-template <bool KEPT>
-__global__ __launch_bounds__(kCellThreads) void k_reorder(ReorderArgs g) {
+template <bool FINISH>
+__global__ __launch_bounds__(kCellThreads, 4) void k_reorder(ReorderArgs g) {
   extern __shared__ __align__(16) unsigned char lds[];
   const int64_t tile = xcd_tile(blockIdx.x, gridDim.x);
   if (tile >= g.tile_start[g.nsets]) return;
-  reorder_tile<KEPT>(g, carve_window(lds, g.nl), tile, false);
+  reorder_tile<FINISH>(g, carve_window(lds, g.nl), tile, false);
 }
 
 // The tiles the first launch listed.
-template <bool KEPT>
 __global__ __launch_bounds__(kCellThreads) void k_reorder_again(ReorderArgs g) {
   extern __shared__ __align__(16) unsigned char lds[];
   const uint32_t n = *g.n_run_tiles;
   for (uint32_t q = blockIdx.x; q < n; q += gridDim.x) {
-    reorder_tile<KEPT>(g, carve_window(lds, g.nl), g.run_tiles[q], true);
+    reorder_tile<true>(g, carve_window(lds, g.nl), g.run_tiles[q], true);
     __syncthreads();
   }
 }
@@ -979,7 +943,7 @@ __global__ __launch_bounds__(kCellThreads) void k_cell_emit(
         // first child: this particle's cell one depth down (emitted next)
         const uint32_t fc = s.lvl[d + 1] + s.off[(d + 1) * kCellThreads + threadIdx.x];
         reinterpret_cast<int2 *>(child_ptr)[ci] = make_int2((int32_t)fc, 0);
-        if ((int64_t)fc < c_max) head_parent[fc] = (int32_t)ci;
+        if (head_parent && (int64_t)fc < c_max) head_parent[fc] = (int32_t)ci;
       } else {
         reinterpret_cast<int2 *>(child_ptr)[ci] = make_int2(-1, 0);
         s.leaf[leaf_slot] = (uint32_t)li | ((uint32_t)dl << 11) | (rel << 16);
@@ -1154,7 +1118,7 @@ static ReorderArgs reorder_args(const Plan &p, const Work &w, const tb_tree &out
 }
 
 hipError_t launch_reorder(const Plan &p, const Work &w, const tb_tree &out, hipStream_t s) {
-  auto k = window_kept(p.n_leaf) ? k_reorder<true> : k_reorder<false>;
+  auto k = reorder_finishes(p.n_leaf) ? k_reorder<true> : k_reorder<false>;
   k<<<(unsigned)p.cell_tiles, kCellThreads, window_lds_bytes(p.n_leaf), s>>>(
       reorder_args(p, w, out));
   return hipGetLastError();
@@ -1163,13 +1127,13 @@ hipError_t launch_reorder(const Plan &p, const Work &w, const tb_tree &out, hipS
 hipError_t launch_runs(const Plan &p, const Work &w, const tb_tree &out, hipStream_t s) {
   const ReorderArgs g = reorder_args(p, w, out);
   const int64_t most = p.n / (kRunCap + 1);
-  if (most == 0) return hipSuccess;  // too few particles for a run that long
+  // too few particles for a run that long, or sorted by their whole keys
+  if (most == 0 || !reorder_finishes(p.n_leaf)) return hipSuccess;
   // small grids, which return at once in the common case that nothing is listed
   k_sort_runs<<<(unsigned)(most < 256 ? most : 256), kCellThreads, 0, s>>>(
       g, reinterpret_cast<int32_t *>(w.vals1), w.keys0, w.keys1);
-  auto k = window_kept(p.n_leaf) ? k_reorder_again<true> : k_reorder_again<false>;
-  k<<<(unsigned)(p.cell_tiles < 512 ? p.cell_tiles : 512), kCellThreads,
-      window_lds_bytes(p.n_leaf), s>>>(g);
+  k_reorder_again<<<(unsigned)(p.cell_tiles < 512 ? p.cell_tiles : 512), kCellThreads,
+                    window_lds_bytes(p.n_leaf), s>>>(g);
   return hipGetLastError();
 }
 
@@ -1191,8 +1155,7 @@ size_t cell_lds_limit() {
                               hipFuncAttributeMaxDynamicSharedMemorySize, opt);
     for (const void *k : {reinterpret_cast<const void *>(k_reorder<true>),
                           reinterpret_cast<const void *>(k_reorder<false>),
-                          reinterpret_cast<const void *>(k_reorder_again<true>),
-                          reinterpret_cast<const void *>(k_reorder_again<false>)})
+                          reinterpret_cast<const void *>(k_reorder_again)})
       (void)hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, opt);
     cached = (size_t)v;
     cached_dev = dev;
@@ -1206,7 +1169,8 @@ hipError_t launch_cell_emit(const Plan &p, const Work &w, const tb_tree &out, hi
   k<<<(unsigned)p.cell_tiles, kCellThreads, lds, s>>>(
       sorted_keys(p, w), w.ad, p.n_leaf, w.cell_excl, p.cell_tiles, w.tile_start, w.tile_set,
       w.set_off, p.nsets, w.lvl_off, w.box, w.sorted, out.cell_key, out.cell_level,
-      out.cell_first, out.cell_count, out.child_ptr, out.com, out.quad, w.m_lo, w.head_parent,
+      out.cell_first, out.cell_count, out.child_ptr, out.com, out.quad, w.m_lo,
+      owned_parents(p) ? nullptr : w.head_parent,
       p.c_max, (p.flags & TB_HILBERT) ? 1 : 0, out.status);
   return hipGetLastError();
 }

@@ -236,11 +236,14 @@ hipError_t launch_reorder(const Plan &p, const Work &w, const tb_tree &out, hipS
 hipError_t launch_runs(const Plan &p, const Work &w, const tb_tree &out, hipStream_t s);
 size_t cell_lds_limit();
 size_t cell_reorder_lds(int nl);
+bool reorder_finishes(int nl);
 hipError_t launch_cell_emit(const Plan &p, const Work &w, const tb_tree &out, hipStream_t s);
 size_t cell_emit_lds(int nl);
 // tb_parents.hip
 hipError_t launch_parents(const Plan &p, const Work &w, int depth, const tb_tree &out,
                           hipStream_t s);
+bool owned_parents(const Plan &p);
+hipError_t launch_owned_parents(const Plan &p, const Work &w, const tb_tree &out, hipStream_t s);
 // tb_blocks.hip
 hipError_t launch_blocks(const Plan &p, const Work &w, hipStream_t s);
 hipError_t launch_block_build(const Plan &p, const Work &w, const tb_tree &out, hipStream_t s);

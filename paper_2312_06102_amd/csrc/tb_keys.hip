@@ -511,7 +511,10 @@ __device__ inline void sample_keys(const float *__restrict__ pos, int64_t n,
 
 // Samples that may agree with an earlier one before the low bits are sorted as well:
 // what runs of kRunMean particles each would give.
-static uint32_t sample_limit(int64_t n) {
+// (None, if the reorder does not finish the sort.)
+static uint32_t sample_limit(const Plan &p) {
+  if (!reorder_finishes(p.n_leaf)) return 0u;
+  const int64_t n = p.n;
   constexpr double kRunMean = 12.0;
   const double s = (double)(n < sample_count(n) ? n : sample_count(n));
   const double per_run = kRunMean * s / (double)n;  // samples in a run
@@ -785,7 +788,7 @@ hipError_t launch_keygen(const Plan &p, const Work &w, const float *pos, const f
 #define TB_KEYGEN(B)                                                                           \
   k_keygen<B><<<blocks + 1, kKeygenThreads, 0, s>>>(                                           \
       pos, mass, p.n, w.box, w.keys0, w.packed, (p.counted & 1u) ? w.dig : nullptr, w.hist_part, \
-      passes, p.skip_bits, hil, few, sample_limit(p.n), w.counters + kFullSortCounter, out.status)
+      passes, p.skip_bits, hil, few, sample_limit(p), w.counters + kFullSortCounter, out.status)
     switch (p.sort.bits) {
       case 8: TB_KEYGEN(8); break;
       case 9: TB_KEYGEN(9); break;
@@ -799,7 +802,7 @@ hipError_t launch_keygen(const Plan &p, const Work &w, const float *pos, const f
   k_keygen_sets<B><<<(unsigned)blocks + 1, kKeygenThreads, 0, s>>>(                            \
       pos, mass, p.n, w.set_off, p.nsets, w.box, w.keys0, w.packed,                            \
       (p.counted & 1u) ? w.dig : nullptr, w.seg_base, passes, passes + p.low_passes,           \
-      p.skip_bits, hil, few, sample_limit(p.n), w.counters + kFullSortCounter, out.status)
+      p.skip_bits, hil, few, sample_limit(p), w.counters + kFullSortCounter, out.status)
     switch (p.sort.bits) {
       case 8: TB_KEYGEN_SETS(8); break;
       case 9: TB_KEYGEN_SETS(9); break;

@@ -8,7 +8,10 @@
 // are all registered.  In the (depth, key)-ordered array the children of a
 // depth-d cell are one contiguous run at depth d+1, and the cell placement pass
 // already recorded each internal cell's first child and, for that first child,
-// the slot of its parent.  One launch per depth: the depth-(d+1) cells (and the
+// the slot of its parent.  Two ways to go up the tree (owned_parents has the rule
+// between them):  a few launches in which every tile of particles, then every group of
+// tiles, builds the cells it holds entirely (second half of this file), and, for very
+// small leaves, one launch per depth: the depth-(d+1) cells (and the
 // parent slots of their first children) are staged through LDS in key order; a
 // child whose key, shifted right by three, differs from its predecessor's --
 // the boundary test of Algorithm 2 -- opens the run of its siblings.  The
@@ -24,6 +27,7 @@
 // in a cell-relative frame.
 #include "tb_internal.h"
 #include "tb_moments.h"
+#include "tb_tiles.h"
 
 namespace tb {
 
@@ -372,6 +376,395 @@ __global__ __launch_bounds__(kParentThreads) void k_parents_mixed(
     __syncthreads();
   }
   if (__ballot(internal) != 0 && lane_id() == 0) atomicOr(status_word, TB_STATUS_INTERNAL);
+}
+
+// ---------------------------------------------------------------------------
+// parents by ownership: a few launches for all depths
+// ---------------------------------------------------------------------------
+// A cell belongs to the tile that holds its first particle, and a cell whose particles
+// all lie in its tile needs nothing from another one.  So one wave per tile builds
+// those, deepest first (k_tile_parents); what is left are the cells that reach past
+// their tile's end, at most one a depth and tile.  k_group_parents does the same with
+// groups of 32 tiles for the cells that end inside their group, then with groups of 32
+// groups, until one holds every tile.
+//
+// Eight lanes build a parent, one a child, so a step is one round of loads and not a
+// loop over the children (seven on average), and a wave's step is eight parents, about
+// what a tile has at a depth.  The lanes stage what they loaded in LDS, and each of the
+// first six sums one component over the children in key order, which gives exactly the
+// sums of a loop over them.
+//
+// A tile's steps follow from one another (a step is some 1.5 us), so few tiles are bound
+// by that latency and many by the bytes of the cells, once in and the parents out.  us
+// for all parents, by depth / so: 1000 particles 48 / 8, 65536 62 / 34, 2e6 (n_leaf 10)
+// 122 / 82, 2^24 217 / 188 (118 of it the tiles), 2^26 clustered, n_leaf 8, 985 / 917;
+// 300 small sets 124 / 50.
+constexpr int kGroupUnits = 32;
+constexpr int kGroupThreads = 8 * kGroupUnits;
+
+struct ParentArgs {
+  const uint64_t *key;
+  int32_t *count, *child;
+  void *com, *quad;
+  float *m_lo;
+  int64_t n_cells;
+  int hilbert;
+};
+
+template <bool MIXED>
+struct Combine;
+
+// What the 64 lanes of a wave stage of their children.
+template <>
+struct Combine<false> {
+  using T = double;
+  struct Lds {
+    double v[64][11];  // mass, com + shift, then the quadrupole's terms (one column of padding)
+  };
+};
+template <>
+struct Combine<true> {
+  using T = float;
+  struct Lds {
+    float v[64][11];  // the same, and the mass's compensation
+  };
+};
+
+__device__ __forceinline__ void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
+// The eight lanes of each group of eight build parent pc (< 0: nothing to do) at depth d
+// from its children, which start at cell fc.  A parent with key end_key >> (63 - 3 d)
+// (end: there is a particle past what this launch's unit owns, with that key) has
+// particles beyond and is left alone; returns whether this lane's is one.
+template <bool MIXED>
+__device__ inline bool combine_children(const ParentArgs &g, typename Combine<MIXED>::Lds &L,
+                                        int64_t pc, int64_t fc, int d, double side, bool end,
+                                        uint64_t end_key) {
+  using T = typename Combine<MIXED>::T;
+  const int lane = lane_id(), k = lane & 7, g0 = lane & ~7;
+  const int64_t c = fc + k;
+  const bool in = pc >= 0 && c < g.n_cells;
+  const int64_t cc = in ? c : 0;
+  const uint64_t key = g.key[cc];
+  const int32_t cnt = g.count[cc];
+  T cm[4], q[6], ml = T(0);
+  if constexpr (!MIXED) {
+    const double2 *com = reinterpret_cast<const double2 *>(static_cast<const double *>(g.com) + 4 * cc);
+    const double2 *quad = reinterpret_cast<const double2 *>(static_cast<const double *>(g.quad) + 6 * cc);
+    const double2 a = com[0], b = com[1], e = quad[0], f = quad[1], h = quad[2];
+    cm[0] = a.x, cm[1] = a.y, cm[2] = b.x, cm[3] = b.y;
+    q[0] = e.x, q[1] = e.y, q[2] = f.x, q[3] = f.y, q[4] = h.x, q[5] = h.y;
+  } else {
+    const float4 a = static_cast<const float4 *>(g.com)[cc];
+    const float2 *quad = reinterpret_cast<const float2 *>(static_cast<const float *>(g.quad) + 6 * cc);
+    const float2 e = quad[0], f = quad[1], h = quad[2];
+    ml = g.m_lo[cc];
+    cm[0] = a.x, cm[1] = a.y, cm[2] = a.z, cm[3] = a.w;
+    q[0] = e.x, q[1] = e.y, q[2] = f.x, q[3] = f.y, q[4] = h.x, q[5] = h.y;
+  }
+  // the children: the cells from the first on whose key, shifted right by three, is the
+  // first one's (the next depth's and the next set's first cells do not match)
+  const uint64_t pkey = __shfl(key, g0, 64) >> 3;
+  const uint64_t match = (__ballot(in && (key >> 3) == pkey) >> g0) & 0xffull;
+  const int nch = __ffsll((long long)~match) - 1;
+  const bool child = k < nch;
+  const bool beyond = pc >= 0 && end && pkey == end_key >> (63 - 3 * d);
+  const bool act = pc >= 0 && !beyond;
+  const uint32_t o = child_octant(key, d + 1, g.hilbert != 0);
+  T u[3];
+  if constexpr (!MIXED) {
+    const double sh = ldexp(side, -(d + 2));  // a quarter of the parent side
+    u[0] = cm[0] + ((o & 4u) ? sh : -sh);
+    u[1] = cm[1] + ((o & 2u) ? sh : -sh);
+    u[2] = cm[2] + ((o & 1u) ? sh : -sh);
+  } else {
+    // parent units: a child's frame maps by an exact halving and a shift of a quarter
+    const float lc = ldexpf((float)side, -(d + 1)), inv_lc = 1.0f / lc;
+    u[0] = 0.5f * (cm[0] * inv_lc) + ((o & 4u) ? 0.25f : -0.25f);
+    u[1] = 0.5f * (cm[1] * inv_lc) + ((o & 2u) ? 0.25f : -0.25f);
+    u[2] = 0.5f * (cm[2] * inv_lc) + ((o & 1u) ? 0.25f : -0.25f);
+  }
+  T *mine = L.v[lane];
+  mine[0] = cm[3];
+  mine[1] = u[0];
+  mine[2] = u[1];
+  mine[3] = u[2];
+  if (MIXED) mine[4] = ml;
+  wave_lds_fence();
+  // lane 0 of the eight sums the mass, lanes 1 to 3 the first moments; all terms are
+  // read before the first is added
+  T S = T(0), Sc = T(0);
+  {
+    T m[8], v[8];
+#pragma unroll
+    for (int x = 0; x < 8; ++x) {
+      m[x] = L.v[g0 + x][0];
+      v[x] = (MIXED || (k & 3) != 0) ? L.v[g0 + x][(MIXED && k == 0) ? 4 : (k & 3)] : T(1);
+    }
+#pragma unroll
+    for (int x = 0; x < 8; ++x) {
+      if constexpr (!MIXED) {
+        const double t = S + m[x] * v[x];
+        S = x < nch ? t : S;
+      } else {
+        float t = S, tc = Sc;
+        if (k == 0) {
+          kahan_add(t, tc, m[x]);
+          kahan_add(t, tc, v[x]);
+        } else {
+          kahan_add(t, tc, m[x] * v[x]);
+        }
+        S = x < nch ? t : S;
+        Sc = x < nch ? tc : Sc;
+      }
+    }
+  }
+  // (the number of particles: every lane its child's, added up)
+  int32_t n = child ? cnt : 0;
+  n += __shfl_xor(n, 1, 64);
+  n += __shfl_xor(n, 2, 64);
+  n += __shfl_xor(n, 4, 64);
+  const T M = __shfl(S, g0, 64);
+  const T cj = S / M;  // lanes 1 to 3
+  const T c0 = __shfl(cj, g0 + 1, 64), c1 = __shfl(cj, g0 + 2, 64), c2 = __shfl(cj, g0 + 3, 64);
+  const T mc = cm[3];
+  const T d0 = u[0] - c0, d1 = u[1] - c1, d2 = u[2] - c2;
+  const T dd = d0 * d0 + d1 * d1 + d2 * d2;
+  T qs = T(1);
+  if (MIXED) {
+    const float lc = ldexpf((float)side, -(d + 1)), inv_lc = 1.0f / lc;
+    qs = 0.25f * (inv_lc * inv_lc);  // child units -> parent units
+  }
+  const T three = T(3);
+  wave_lds_fence();  // the sums have read the masses
+  if constexpr (!MIXED) {
+    mine[0] = q[0] + mc * (three * d0 * d0 - dd);
+    mine[1] = q[1] + mc * (three * d0 * d1);
+    mine[2] = q[2] + mc * (three * d0 * d2);
+    mine[3] = q[3] + mc * (three * d1 * d1 - dd);
+    mine[4] = q[4] + mc * (three * d1 * d2);
+    mine[5] = q[5] + mc * (three * d2 * d2 - dd);
+  } else {
+    mine[0] = q[0] * qs + mc * (three * d0 * d0 - dd);
+    mine[1] = q[1] * qs + mc * (three * d0 * d1);
+    mine[2] = q[2] * qs + mc * (three * d0 * d2);
+    mine[3] = q[3] * qs + mc * (three * d1 * d1 - dd);
+    mine[4] = q[4] * qs + mc * (three * d1 * d2);
+    mine[5] = q[5] * qs + mc * (three * d2 * d2 - dd);
+  }
+  wave_lds_fence();
+  T Q = T(0), Qc = T(0);
+  {
+    T v[8];
+#pragma unroll
+    for (int x = 0; x < 8; ++x) v[x] = L.v[g0 + x][k < 6 ? k : 5];
+#pragma unroll
+    for (int x = 0; x < 8; ++x) {
+      if constexpr (!MIXED) {
+        Q = x < nch ? Q + v[x] : Q;
+      } else {
+        float t = Q, tc = Qc;
+        kahan_add(t, tc, v[x]);
+        Q = x < nch ? t : Q;
+        Qc = x < nch ? tc : Qc;
+      }
+    }
+  }
+  wave_lds_fence();  // the staged terms are consumed
+  if (act) {
+    T lp = T(1);
+    if (MIXED) lp = 2.0f * ldexpf((float)side, -(d + 1));  // parent side: absolute units
+    T *com = static_cast<T *>(g.com) + 4 * pc;
+    if (k == 0) com[3] = M;
+    if (k >= 1 && k < 4) com[k - 1] = MIXED ? cj * lp : cj;
+    if (k < 6) static_cast<T *>(g.quad)[6 * pc + k] = MIXED ? Q * (lp * lp) : Q;
+    if (k == 6) g.count[pc] = n;
+    if (k == 7) g.child[2 * pc + 1] = nch;
+    if (MIXED && k == 0) g.m_lo[pc] = (float)-Sc;
+  }
+  return beyond;
+}
+
+// Key of the particle past the end of a tile, if its set goes on there.
+struct UnitEnd {
+  bool end;
+  uint64_t key;
+};
+__device__ inline UnitEnd unit_end(const TileRange &tr, const uint64_t *__restrict__ keys) {
+  UnitEnd e;
+  e.end = tr.t1 < tr.E;
+  e.key = keys[e.end ? tr.t1 : tr.t0];
+  return e;
+}
+
+template <bool MIXED>
+__global__ __launch_bounds__(kParentThreads) void k_tile_parents(
+    ParentArgs g, const uint64_t *__restrict__ keys, const uint32_t *__restrict__ excl,
+    int64_t cell_tiles, const int64_t *__restrict__ tile_start,
+    const int32_t *__restrict__ tile_set, const int64_t *__restrict__ set_off, int32_t nsets,
+    const int64_t *__restrict__ lvl_off, const double *__restrict__ box,
+    const int64_t *__restrict__ n_cells, int32_t *__restrict__ left) {
+  constexpr int W = kParentThreads / 64;
+  __shared__ typename Combine<MIXED>::Lds s_lds[W];
+  typename Combine<MIXED>::Lds &L = s_lds[threadIdx.x / 64];
+  const int lane = lane_id();
+  const int64_t tile = (int64_t)xcd_tile(blockIdx.x, gridDim.x) * W + threadIdx.x / 64;
+  if (tile >= tile_start[nsets]) return;  // the whole wave; no barrier follows
+  g.n_cells = *n_cells;
+  const TileRange tr = tile_range(tile, tile_start, tile_set, set_off);
+  const double side = box[4 * tr.b + 3];
+  const UnitEnd ue = unit_end(tr, keys);
+  // lane d: the cells [r0, r0 + rn) of depth d that start in the tile
+  int32_t r0 = 0, rn = 0, mine = -1;
+  if (lane < kLevels) {
+    const int64_t *lo = lvl_off + tr.b * (kLevels + 1) + lane;
+    const uint32_t *ex = excl + lane * cell_tiles + tile;
+    const int64_t a = lo[0] + ex[0];
+    const int64_t b = tile + 1 < tile_start[tr.b + 1] ? lo[0] + ex[1] : lo[1];
+    r0 = (int32_t)a;
+    rn = (int32_t)(b - a);
+  }
+  // depths that have cells with children (their children start in the tile as well)
+  uint32_t depths = (uint32_t)__ballot(rn != 0);
+  depths &= depths >> 1;
+  auto first_child = [&](int d, int32_t x0) {
+    const int32_t a = __shfl(r0, d, 64), n = __shfl(rn, d, 64), x = x0 + lane;
+    return x < n ? g.child[2 * ((int64_t)a + x)] : -1;
+  };
+  int d = 31 - __clz((int)depths);  // deepest first
+  int32_t ahead = depths != 0 ? first_child(d, 0) : -1;
+  while (depths != 0) {
+    const int32_t a = __shfl(r0, d, 64), n = __shfl(rn, d, 64);
+    depths &= ~(1u << d);
+    const int next = depths != 0 ? 31 - __clz((int)depths) : 0;
+    int32_t fc = ahead;
+    if (depths != 0) ahead = first_child(next, 0);
+    for (int32_t x0 = 0; x0 < n; x0 += 64) {
+      if (x0 != 0) fc = first_child(d, x0);
+      uint64_t todo = __ballot(fc >= 0);
+      while (todo != 0) {
+        // the next eight internal cells, eight lanes each
+        int src = -1;
+        uint64_t rest = todo;
+#pragma unroll
+        for (int p = 0; p < 8; ++p) {
+          if (rest != 0) {
+            if (p == lane / 8) src = __ffsll((long long)rest) - 1;
+            rest &= rest - 1;
+          }
+        }
+        todo = rest;
+        const int32_t pf = __shfl(fc, src < 0 ? 0 : src, 64);
+        const int64_t pc = src < 0 ? -1 : (int64_t)a + x0 + src;
+        const uint64_t past = __ballot(
+            combine_children<MIXED>(g, L, pc, src < 0 ? 0 : pf, d, side, ue.end, ue.key));
+        if (past != 0) {
+          const int32_t slot = (int32_t)__shfl(pc, __ffsll((long long)past) - 1, 64);
+          if (lane == d) mine = slot;
+        }
+      }
+    }
+    // the next depth's loads see these stores: a wave's accesses stay in order
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    d = next;
+  }
+  if (lane < kMaxDepth) left[lane * cell_tiles + tile] = mine;
+}
+
+// The cells that reach past their unit (`unit` tiles), for kGroupUnits units: those that
+// end inside the group are built, the others go to left2.
+template <bool MIXED>
+__global__ __launch_bounds__(kGroupThreads) void k_group_parents(
+    ParentArgs g, const uint64_t *__restrict__ keys, int64_t unit,
+    const int64_t *__restrict__ tile_start, const int32_t *__restrict__ tile_set,
+    const int64_t *__restrict__ set_off, int32_t nsets, const double *__restrict__ box,
+    const int64_t *__restrict__ n_cells, const int32_t *__restrict__ left, int64_t units,
+    int32_t *__restrict__ left2, int64_t groups) {
+  __shared__ typename Combine<MIXED>::Lds s_lds[kGroupThreads / 64];
+  __shared__ int32_t s_pc[kMaxDepth][kGroupUnits], s_fc[kMaxDepth][kGroupUnits];
+  __shared__ int32_t s_left[kMaxDepth];
+  __shared__ uint32_t s_any;
+  typename Combine<MIXED>::Lds &L = s_lds[threadIdx.x / 64];
+  const int64_t tiles = tile_start[nsets], u0 = blockIdx.x * (int64_t)kGroupUnits;
+  g.n_cells = *n_cells;
+  if (threadIdx.x == 0) s_any = 0;
+  if (threadIdx.x < kMaxDepth) s_left[threadIdx.x] = -1;
+  __syncthreads();
+  for (int x = threadIdx.x; x < kMaxDepth * kGroupUnits; x += kGroupThreads) {
+    const int d = x / kGroupUnits, q = x % kGroupUnits;
+    const int32_t pc = (u0 + q) * unit < tiles ? left[d * units + u0 + q] : -1;
+    s_pc[d][q] = pc;
+    s_fc[d][q] = pc >= 0 ? g.child[2 * (int64_t)pc] : 0;
+    if (pc >= 0) atomicOr(&s_any, 1u << d);
+  }
+  __syncthreads();
+  const uint32_t any = s_any;
+  if (any != 0) {
+    const int q = threadIdx.x / 8;  // this lane's unit of the group
+    // the unit's and the group's last tile; a cell left over is of the set of the first
+    const int64_t last = min((u0 + kGroupUnits) * unit, tiles) - 1;
+    const int64_t tile = min((u0 + q + 1) * unit - 1, last);
+    const int b = tile_set[tile], bl = tile_set[last];
+    const double side = box[4 * b + 3];
+    const UnitEnd ue = unit_end(tile_range(last, tile_start, tile_set, set_off), keys);
+    for (int d = kMaxDepth - 1; d >= 0; --d) {
+      if (!((any >> d) & 1u)) continue;
+      const int64_t pc = s_pc[d][q];
+      if (combine_children<MIXED>(g, L, pc, s_fc[d][q], d, side, ue.end && b == bl, ue.key))
+        s_left[d] = (int32_t)pc;
+      __syncthreads();  // the next depth's loads see these stores
+    }
+  }
+  if (threadIdx.x < kMaxDepth) left2[threadIdx.x * groups + blockIdx.x] = s_left[threadIdx.x];
+}
+
+template <bool MIXED>
+static hipError_t owned_parents_t(const Plan &p, const Work &w, const tb_tree &out,
+                                  hipStream_t s) {
+  const ParentArgs g = {out.cell_key, out.cell_count, out.child_ptr, out.com, out.quad,
+                        w.m_lo,       0,              (p.flags & TB_HILBERT) ? 1 : 0};
+  const uint64_t *keys = sorted_keys(p, w);
+  // the cells left over lie in the space of the tiles' cell counts and then, of the
+  // groups, by turns in that of the two buffers of look-back words (84 bytes a group)
+  const int32_t *left = reinterpret_cast<int32_t *>(w.cell_cnt);
+  int32_t *space[2] = {reinterpret_cast<int32_t *>(w.status0),
+                       reinterpret_cast<int32_t *>(w.status1)};
+  constexpr int W = kParentThreads / 64;
+  k_tile_parents<MIXED><<<(unsigned)((p.cell_tiles + W - 1) / W), kParentThreads, 0, s>>>(
+      g, keys, w.cell_excl, p.cell_tiles, w.tile_start, w.tile_set, w.set_off, p.nsets, w.lvl_off,
+      w.box, out.n_cells, reinterpret_cast<int32_t *>(w.cell_cnt));
+  // every set is one tile, or units of more and more tiles until one holds them all
+  // (a batch's largest set may have all but one of the particles)
+  int64_t units = p.cell_tiles, unit = 1;
+  for (int level = 0; unit * kCellTile < p.n; ++level) {
+    const int64_t groups = (units + kGroupUnits - 1) / kGroupUnits;
+    k_group_parents<MIXED><<<(unsigned)groups, kGroupThreads, 0, s>>>(
+        g, keys, unit, w.tile_start, w.tile_set, w.set_off, p.nsets, w.box, out.n_cells, left,
+        units, space[level % 2], groups);
+    left = space[level % 2];
+    units = groups;
+    unit *= kGroupUnits;
+    if (units == 1) break;
+  }
+  return hipGetLastError();
+}
+
+// Whether the parents are built tile by tile or one launch a depth.  A wave goes through
+// its tile's cells one after the other, so where leaves are so small that a tile has
+// thousands, few tiles take longer than 21 launches.  us a build, by depth / by tile:
+// n_leaf 1, 65536 particles 252 / 374, 2^21 680 / 770, 2^24 4000 / 3840; n_leaf 4 234 /
+// 219 (clustered 238 / 254), 493 / 450, 2375 / 2119; n_leaf 8 229 / 187, 445 / 385,
+// 1991 / 1707 (the sort's gain included).
+bool owned_parents(const Plan &p) {
+  return p.n_leaf >= 6 || p.n * p.n_leaf >= (int64_t{1} << 23);
+}
+
+hipError_t launch_owned_parents(const Plan &p, const Work &w, const tb_tree &out, hipStream_t s) {
+  return (p.flags & 0xffu) == TB_MIXED ? owned_parents_t<true>(p, w, out, s)
+                                       : owned_parents_t<false>(p, w, out, s);
 }
 
 hipError_t launch_parents(const Plan &p, const Work &w, int depth, const tb_tree &out,
