@@ -26,6 +26,9 @@ static size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 // Internal plan flag: the root boxes are derived from the data.
 constexpr uint32_t kAutoBoxFlag = 0x10000u;
 
+// Most particles that are built in small cell tiles (make_plan).
+constexpr int64_t kSmallTileMaxN = 3 << 18;
+
 static int64_t max_cells(int64_t n, int32_t n_leaf) {
   if (n <= 0) return 0;
   return n + (int64_t)kMaxDepth * (n / ((int64_t)n_leaf + 1));
@@ -99,7 +102,13 @@ int make_plan(int64_t n, int32_t nsets, int32_t n_leaf, uint32_t flags, const So
       ((flags & TB_SORT_COUNTED) || (!p->seg && p->sort_tiles >= kCountedMinTiles)))
     p->counted = (1u << p->key_passes) - 1u;
   // tiles never straddle two sets: at most one partial tile per set
-  p->cell_tiles = (n + kCellTile - 1) / kCellTile + nsets;
+  // Cell tiles of 2048 particles, eight a thread, or of 512, two a thread, where 2048
+  // would leave most of the chip idle: a workgroup's chain of loads, counts and writes is
+  // what such a build waits for.  us a Plummer build, n_leaf 16, in tiles of 2048 /
+  // of 512: 2^14 164 / 129, 2^16 170 / 151, 2^18 215 / 179, 2^19 234 / 208, 2^20 273 / 276,
+  // 2^21 364 / 366.
+  p->cell_tile = (flags & TB_SUBTREES) || n > kSmallTileMaxN ? kCellTile : kSmallTile;
+  p->cell_tiles = (n + p->cell_tile - 1) / p->cell_tile + nsets;
   // the auto box works chunk by chunk of one set: about four workgroups a CU (2^21
   // particles: 118 us in 31 chunks of 65536, 12 us in 1024 of 2048), the chunks no
   // smaller than eight particles a thread
@@ -314,7 +323,7 @@ static int build_impl(const float *pos, const float *mass, int64_t n, int32_t ns
   make_plan(n, nsets, n_leaf, flags | (in.auto_box ? kAutoBoxFlag : 0u), sc, &p);
   if (!workspace || ws_bytes < p.total) return TB_ERR_WORKSPACE;
   // the cell kernels stage a tile plus an n_leaf halo in LDS
-  if (cell_emit_lds(n_leaf) > cell_lds_limit()) return TB_ERR_ARG;
+  if (cell_emit_lds(n_leaf, p.cell_tile) > cell_lds_limit()) return TB_ERR_ARG;
   const Work w = carve(p, workspace);
 
   hipError_t e = hipSuccess;

@@ -135,7 +135,7 @@ __global__ __launch_bounds__(kCellThreads) void k_blocks(
   __shared__ uint32_t s_red[kWaves];
   const int64_t tile = blockIdx.x;
   if (tile >= tile_start[nsets]) return;
-  const TileRange tr = tile_range(tile, tile_start, tile_set, set_off);
+  const TileRange tr = tile_range(tile, tile_start, tile_set, set_off, kCellTile);
   const int64_t base = tr.t0 - kSerial;
   const int T = (int)(tr.t1 - tr.t0);
   constexpr int KB = 3 * kSerial / kCellThreads;
@@ -301,7 +301,7 @@ __global__ __launch_bounds__(kCellThreads) void k_block_build(
 
   const int64_t tile = blockIdx.x;
   if (tile >= tile_start[nsets]) return;
-  const TileRange tr = tile_range(tile, tile_start, tile_set, set_off);
+  const TileRange tr = tile_range(tile, tile_start, tile_set, set_off, kCellTile);
   const int64_t t0 = tr.t0, S = tr.S, E = tr.E;
   const int T = (int)(tr.t1 - t0);
   const int W = (int)(min(tr.t1 + (int64_t)kSerial, E) - t0);

@@ -34,7 +34,6 @@
 
 namespace tb {
 
-constexpr int kMaxSpan = (kCellTile + TB_MAX_NLEAF + kCellThreads - 1) / kCellThreads;
 
 __host__ __device__ constexpr size_t round16(size_t x) { return (x + 15) & ~size_t(15); }
 
@@ -43,13 +42,16 @@ __host__ __device__ constexpr size_t round16(size_t x) { return (x + 15) & ~size
 __host__ __device__ constexpr int window_size(int tile, int nl, int ext) {
   return tile + 2 * nl + 1 + 2 * ext;
 }
-// The window's particles a thread gathers at once.  If that holds the window with the
-// ends of its runs (n_leaf <= 95) the reorder finishes the sort; larger windows get
-// particles that the radix passes have sorted by their whole keys (make_plan).
-constexpr int kWindowIpt = kCellIpt + 1;
+// A thread gathers IPT + 1 of the window's particles at once.  If that holds the window
+// with the ends of its runs (n_leaf <= 95 for either tile) the reorder finishes the sort;
+// larger windows get particles that the radix passes have sorted by their whole keys
+// (make_plan).
 __host__ __device__ constexpr int window_ext(int nl) {
-  return window_size(kCellTile, nl, kRunCap) <= kWindowIpt * kCellThreads ? kRunCap : 0;
+  return window_size(kCellTile, nl, kRunCap) <= (kCellIpt + 1) * kCellThreads ? kRunCap : 0;
 }
+static_assert((kCellIpt + 1) * kCellThreads - kCellTile ==
+                  (kSmallIpt + 1) * kCellThreads - kSmallTile,
+              "both tiles leave the same room beside them");
 bool reorder_finishes(int nl) { return window_ext(nl) != 0; }
 
 // Shared layout of the reorder pass (dynamic LDS, sized for the actual n_leaf).
@@ -64,31 +66,31 @@ struct WindowLds {
   uint32_t *wtot;  // [kWaves][kLevelWords]
 };
 
-__host__ __device__ inline size_t window_keys_bytes(int nl) {
-  return round16((size_t)window_size(kCellTile, nl, window_ext(nl)) * 8);
+__host__ __device__ inline size_t window_keys_bytes(int nl, int tile) {
+  return round16((size_t)window_size(tile, nl, window_ext(nl)) * 8);
 }
 
 // (rows of kCellThreads particles, kWaves words each)
-__host__ __device__ inline size_t window_heads_bytes(int nl) {
-  return window_ext(nl) ? round16((size_t)(kWindowIpt * kWaves + 2) * 8) : 0;
+__host__ __device__ inline size_t window_heads_bytes(int nl, int tile) {
+  return window_ext(nl) ? round16((size_t)((tile / kCellThreads + 1) * kWaves + 2) * 8) : 0;
 }
 
-__host__ __device__ inline size_t window_lds_bytes(int nl) {
-  return window_keys_bytes(nl) + window_heads_bytes(nl) + 2 * round16(kCellTile + nl) +
+__host__ __device__ inline size_t window_lds_bytes(int nl, int tile) {
+  return window_keys_bytes(nl, tile) + window_heads_bytes(nl, tile) + 2 * round16(tile + nl) +
          (size_t)kWaves * kLevelWords * 4;
 }
 
-__device__ inline WindowLds carve_window(unsigned char *base, int nl) {
+__device__ inline WindowLds carve_window(unsigned char *base, int nl, int tile) {
   WindowLds s;
   s.raw = reinterpret_cast<uint64_t *>(base);
   s.keys = s.raw + window_ext(nl);
-  base += window_keys_bytes(nl);
+  base += window_keys_bytes(nl, tile);
   s.heads = reinterpret_cast<uint64_t *>(base);
-  base += window_heads_bytes(nl);
+  base += window_heads_bytes(nl, tile);
   s.m = base;
-  base += round16(kCellTile + nl);
+  base += round16(tile + nl);
   s.a = base;
-  base += round16(kCellTile + nl);
+  base += round16(tile + nl);
   s.wtot = reinterpret_cast<uint32_t *>(base);
   return s;
 }
@@ -113,23 +115,23 @@ __host__ __device__ inline size_t emit_off_bytes() {
   return round16((size_t)kLevels * kCellThreads * 2);
 }
 
-__host__ __device__ inline size_t emit_union_bytes(int nl) {
-  const size_t cells = emit_off_bytes() + (size_t)kCellTile * 4;  // off, then leaf
-  const size_t rec = (size_t)(kCellTile + nl) * 16;
+__host__ __device__ inline size_t emit_union_bytes(int nl, int tile) {
+  const size_t cells = emit_off_bytes() + (size_t)tile * 4;  // off, then leaf
+  const size_t rec = (size_t)(tile + nl) * 16;
   return round16(cells > rec ? cells : rec);
 }
 
-__host__ __device__ inline size_t emit_lds_bytes(int nl) {
-  return round16(kCellTile + nl) + round16(kCellTile) + round16((size_t)kWaves * kLevelWords * 4) +
-         round16(kLevels * 4) + emit_union_bytes(nl) + kCellTile / 8 + 16;
+__host__ __device__ inline size_t emit_lds_bytes(int nl, int tile) {
+  return round16(tile + nl) + round16(tile) + round16((size_t)kWaves * kLevelWords * 4) +
+         round16(kLevels * 4) + emit_union_bytes(nl, tile) + tile / 8 + 16;
 }
 
-__device__ inline EmitLds carve_emit(unsigned char *base, int nl) {
+__device__ inline EmitLds carve_emit(unsigned char *base, int nl, int tile) {
   EmitLds s;
   s.a = base;
-  base += round16(kCellTile + nl);
+  base += round16(tile + nl);
   s.d = base;
-  base += round16(kCellTile);
+  base += round16(tile);
   s.wtot = reinterpret_cast<uint32_t *>(base);
   base += round16((size_t)kWaves * kLevelWords * 4);
   s.lvl = reinterpret_cast<uint32_t *>(base);
@@ -140,9 +142,9 @@ __device__ inline EmitLds carve_emit(unsigned char *base, int nl) {
   s.off = reinterpret_cast<uint16_t *>(base);
   s.leaf = reinterpret_cast<uint32_t *>(base + emit_off_bytes());
   s.rec = reinterpret_cast<float4 *>(base);
-  base += emit_union_bytes(nl);
+  base += emit_union_bytes(nl, tile);
   s.heads = base;
-  base += kCellTile / 8;
+  base += tile / 8;
   s.nleaf = reinterpret_cast<uint32_t *>(base);
   return s;
 }
@@ -151,9 +153,12 @@ __device__ inline EmitLds carve_emit(unsigned char *base, int nl) {
 // the set [S, E)): a_i and the windowed maximum, and (in A[], D[]) a_i and the
 // leaf depth of this thread's IPT consecutive particles.  The set's first
 // particle starts a root (a = 0) and windows never reach across the set's ends.
+template <int IPT>
 __device__ inline void depths_from_window(const WindowLds &s, int64_t S, int64_t E, int nl,
-                                          int64_t t0, int64_t t1, uint8_t A[kCellIpt],
-                                          uint8_t D[kCellIpt]) {
+                                          int64_t t0, int64_t t1, uint8_t (&A)[IPT],
+                                          uint8_t (&D)[IPT]) {
+  constexpr int kMaxSpan =
+      (IPT * kCellThreads + TB_MAX_NLEAF + kCellThreads - 1) / kCellThreads;
   const int T = (int)(t1 - t0);
   // a_i for i in [t0, t1 + nl)
   for (int i = threadIdx.x; i < T + nl; i += kCellThreads) {
@@ -196,8 +201,8 @@ __device__ inline void depths_from_window(const WindowLds &s, int64_t S, int64_t
   }
   // window [i - nl, i] = [i - nl, i - nl + pk - 1] u [i - pk + 1, i]
 #pragma unroll
-  for (int j = 0; j < kCellIpt; ++j) {
-    const int li = threadIdx.x * kCellIpt + j;  // particle t0 + li
+  for (int j = 0; j < IPT; ++j) {
+    const int li = threadIdx.x * IPT + j;  // particle t0 + li
     uint8_t d = 0, av = 23;
     if (li < T) {
       const int mx = max(s.m[li], s.m[li + nl + 1 - pk]);
@@ -324,13 +329,13 @@ __device__ inline bool run_places(const WindowLds &s, int i0, int wn, const uint
 
 // FINISH: the window's records stay with the threads that gathered them until the
 // particles' places are known.
-template <bool FINISH>
+template <bool FINISH, int IPT>
 __device__ inline void reorder_tile(const ReorderArgs &g, const WindowLds &s, int64_t tile,
                                     bool again) {
   // a batch set over the caller's index bound: every particle gets the root key
   const bool flat = g.oversize && *g.oversize != 0u;
   const int nl = g.nl;
-  const TileRange tr = tile_range(tile, g.tile_start, g.tile_set, g.set_off);
+  const TileRange tr = tile_range(tile, g.tile_start, g.tile_set, g.set_off, IPT * kCellThreads);
   const int64_t t0 = tr.t0, t1 = tr.t1;
   const double lo0 = g.box[4 * tr.b + 0], lo1 = g.box[4 * tr.b + 1], lo2 = g.box[4 * tr.b + 2];
   const double scale = 2097152.0 / g.box[4 * tr.b + 3];
@@ -338,7 +343,7 @@ __device__ inline void reorder_tile(const ReorderArgs &g, const WindowLds &s, in
   constexpr int kExt = FINISH ? kRunCap : 0;
   const int64_t ws = t0 - nl - 1 - kExt;  // window start (may be negative)
   const int wn = window_size(T, nl, kExt);
-  constexpr int kBatch = kWindowIpt;
+  constexpr int kBatch = IPT + 1;
   bool internal = false, bad = false;
   int32_t p[kBatch];
   float4 rec[kBatch];
@@ -444,11 +449,11 @@ __device__ inline void reorder_tile(const ReorderArgs &g, const WindowLds &s, in
   if (__ballot(internal) != 0 && lane_id() == 0) atomicOr(g.status_word, TB_STATUS_INTERNAL);
   __syncthreads();
 
-  uint8_t A[kCellIpt], D[kCellIpt];
+  uint8_t A[IPT], D[IPT];
   depths_from_window(s, tr.S, tr.E, nl, t0, t1, A, D);
 #pragma unroll
-  for (int j = 0; j < kCellIpt; ++j) {
-    const int li = threadIdx.x * kCellIpt + j;
+  for (int j = 0; j < IPT; ++j) {
+    const int li = threadIdx.x * IPT + j;
     if (li < T) g.ad[t0 + li] = (uint16_t)(A[j] | (D[j] << 8));
   }
   uint32_t c[kLevelWords], tot[kLevelWords];
@@ -464,20 +469,21 @@ __device__ inline void reorder_tile(const ReorderArgs &g, const WindowLds &s, in
   }
 }
 
-template <bool FINISH>
+template <bool FINISH, int IPT>
 __global__ __launch_bounds__(kCellThreads, 4) void k_reorder(ReorderArgs g) {
   extern __shared__ __align__(16) unsigned char lds[];
   const int64_t tile = xcd_tile(blockIdx.x, gridDim.x);
   if (tile >= g.tile_start[g.nsets]) return;
-  reorder_tile<FINISH>(g, carve_window(lds, g.nl), tile, false);
+  reorder_tile<FINISH, IPT>(g, carve_window(lds, g.nl, IPT * kCellThreads), tile, false);
 }
 
 // The tiles the first launch listed.
+template <int IPT>
 __global__ __launch_bounds__(kCellThreads) void k_reorder_again(ReorderArgs g) {
   extern __shared__ __align__(16) unsigned char lds[];
   const uint32_t n = *g.n_run_tiles;
   for (uint32_t q = blockIdx.x; q < n; q += gridDim.x) {
-    reorder_tile<true>(g, carve_window(lds, g.nl), g.run_tiles[q], true);
+    reorder_tile<true, IPT>(g, carve_window(lds, g.nl, IPT * kCellThreads), g.run_tiles[q], true);
     __syncthreads();
   }
 }
@@ -833,7 +839,7 @@ __device__ inline int64_t leaf_end_fast(const EmitLds &s, const uint64_t *__rest
 // ---------------------------------------------------------------------------
 // One workgroup per cell tile: a_i and D_i (from the reorder pass) give every
 // cell whose first particle lies in the tile; the per-depth prefix places it.
-template <bool MIXED>
+template <bool MIXED, int IPT>
 __global__ __launch_bounds__(kCellThreads) void k_cell_emit(
     const uint64_t *__restrict__ keys, const uint16_t *__restrict__ ad, int nl,
     const uint32_t *__restrict__ excl, int64_t cell_tiles, const int64_t *__restrict__ tile_start,
@@ -845,10 +851,11 @@ __global__ __launch_bounds__(kCellThreads) void k_cell_emit(
     void *__restrict__ quad_v, float *__restrict__ m_lo, int32_t *__restrict__ head_parent,
     int64_t c_max, int hilbert, int32_t *__restrict__ status_word) {
   extern __shared__ __align__(16) unsigned char lds[];
-  const EmitLds s = carve_emit(lds, nl);
+  constexpr int kTile = IPT * kCellThreads;
+  const EmitLds s = carve_emit(lds, nl, kTile);
   const int64_t tile = xcd_tile(blockIdx.x, gridDim.x);
   if (tile >= tile_start[nsets]) return;
-  const TileRange tr = tile_range(tile, tile_start, tile_set, set_off);
+  const TileRange tr = tile_range(tile, tile_start, tile_set, set_off, kTile);
   const int64_t t0 = tr.t0, t1 = tr.t1, n = tr.E;  // n: end of this tile's set
   const int T = (int)(t1 - t0);
 
@@ -861,16 +868,16 @@ __global__ __launch_bounds__(kCellThreads) void k_cell_emit(
   if (threadIdx.x == 0) *s.nleaf = 0;
   // this thread's particles t0 + 8t .. t0 + 8t + 7: their keys (issued first,
   // so that they travel with the batched loads below)
-  uint64_t kk[kCellIpt];
+  uint64_t kk[IPT];
 #pragma unroll
-  for (int j = 0; j < kCellIpt; ++j) {
-    const int li = threadIdx.x * kCellIpt + j;
+  for (int j = 0; j < IPT; ++j) {
+    const int li = threadIdx.x * IPT + j;
     kk[j] = keys[t0 + (li < T ? li : T - 1)];
   }
   // the (a, D) of the tile's particles and the n_leaf halo into LDS, in one
   // batch of loads
   const int span = (int)(min(t1 + (int64_t)nl, n) - t0);
-  constexpr int kRecBatch = kCellIpt + 1;  // covers span for n_leaf <= 256
+  constexpr int kRecBatch = IPT + 1;  // covers span for n_leaf <= 256
   for (int x0 = 0; x0 < span; x0 += kRecBatch * kCellThreads) {
     uint16_t v[kRecBatch];
 #pragma unroll
@@ -888,21 +895,27 @@ __global__ __launch_bounds__(kCellThreads) void k_cell_emit(
     }
   }
   __syncthreads();
-  uint8_t A[kCellIpt], D[kCellIpt];
+  uint8_t A[IPT], D[IPT];
 #pragma unroll
-  for (int j = 0; j < kCellIpt; ++j) {
-    const int li = threadIdx.x * kCellIpt + j;
+  for (int j = 0; j < IPT; ++j) {
+    const int li = threadIdx.x * IPT + j;
     A[j] = li < T ? s.a[li] : 23;  // 23: starts no cell
     D[j] = li < T ? s.d[li] : 0;
   }
   {
-    // the head mask holds one byte per thread: bit j of byte t is particle 8t + j
-    static_assert(kCellIpt == 8 && kCellThreads * kCellIpt == kCellTile,
-                  "the head mask layout needs 8 particles per thread");
+    // the head mask: bit li is particle t0 + li (none past the tile end), IPT bits a
+    // thread, a byte from 8 / IPT neighbours
+    static_assert(IPT == 8 || IPT == 2, "threads make up whole bytes of the head mask");
     uint32_t hb = 0;
 #pragma unroll
-    for (int j = 0; j < kCellIpt; ++j) hb |= (A[j] <= D[j] ? 1u : 0u) << j;
-    s.heads[threadIdx.x] = (uint8_t)hb;  // items 8t .. 8t+7 (none past the tile end)
+    for (int j = 0; j < IPT; ++j) hb |= (A[j] <= D[j] ? 1u : 0u) << j;
+    constexpr int kShare = 8 / IPT;
+    if constexpr (kShare > 1) {
+      hb <<= (threadIdx.x % kShare) * IPT;
+#pragma unroll
+      for (int o = 1; o < kShare; o <<= 1) hb |= __shfl_xor(hb, o, 64);
+    }
+    if (threadIdx.x % kShare == 0) s.heads[threadIdx.x / kShare] = (uint8_t)hb;
   }
   uint32_t c[kLevelWords], tot[kLevelWords];
   thread_level_counts(A, D, c);
@@ -912,7 +925,7 @@ __global__ __launch_bounds__(kCellThreads) void k_cell_emit(
   // this thread's leaves go to a contiguous run of the leaf list
   uint32_t my_leaves = 0;
 #pragma unroll
-  for (int j = 0; j < kCellIpt; ++j) my_leaves += (A[j] <= D[j]) ? 1u : 0u;
+  for (int j = 0; j < IPT; ++j) my_leaves += (A[j] <= D[j]) ? 1u : 0u;
   const uint32_t inc = wave_inclusive_scan(my_leaves);
   uint32_t wave_base = 0;
   if (lane_id() == 63) wave_base = atomicAdd(s.nleaf, inc);
@@ -922,10 +935,10 @@ __global__ __launch_bounds__(kCellThreads) void k_cell_emit(
   // cell structure; leaves are queued for the moment phase
   bool internal = false;
 #pragma unroll
-  for (int j = 0; j < kCellIpt; ++j) {
+  for (int j = 0; j < IPT; ++j) {
     const int a = A[j], dl = D[j];
     if (a > dl) continue;
-    const int li = threadIdx.x * kCellIpt + j;
+    const int li = threadIdx.x * IPT + j;
     const int64_t i = t0 + li;
     const uint64_t key = kk[j];
     for (int d = a; d <= dl; ++d) {
@@ -953,11 +966,11 @@ __global__ __launch_bounds__(kCellThreads) void k_cell_emit(
   }
   __syncthreads();
   // the leaf list shares its space with the records: each thread keeps its
-  // entries (at most kCellIpt: a tile starts at most one leaf a particle)
+  // entries (at most IPT: a tile starts at most one leaf a particle)
   const uint32_t nlv = *s.nleaf;
-  uint32_t my_leaf[kCellIpt];
+  uint32_t my_leaf[IPT];
 #pragma unroll
-  for (int k = 0; k < kCellIpt; ++k) {
+  for (int k = 0; k < IPT; ++k) {
     const uint32_t x = threadIdx.x + (uint32_t)k * kCellThreads;
     my_leaf[k] = x < nlv ? s.leaf[x] : 0u;
   }
@@ -984,12 +997,12 @@ __global__ __launch_bounds__(kCellThreads) void k_cell_emit(
   const double lo[3] = {box[4 * tr.b + 0], box[4 * tr.b + 1], box[4 * tr.b + 2]};
   const double side = box[4 * tr.b + 3];
 #pragma unroll 1
-  for (int k = 0; k < kCellIpt; ++k) {
+  for (int k = 0; k < IPT; ++k) {
     if (threadIdx.x + (uint32_t)k * kCellThreads >= nlv) break;
     // this thread's next entry; the rest move down (constant register indices)
     const uint32_t le = my_leaf[0];
 #pragma unroll
-    for (int j = 0; j + 1 < kCellIpt; ++j) my_leaf[j] = my_leaf[j + 1];
+    for (int j = 0; j + 1 < IPT; ++j) my_leaf[j] = my_leaf[j + 1];
     const int li = le & 0x7ff;
     const int dl = (le >> 11) & 31;
     if (dl > kMaxDepth || li >= T) {  // cannot happen: entries come from the loop above
@@ -1117,11 +1130,17 @@ static ReorderArgs reorder_args(const Plan &p, const Work &w, const tb_tree &out
   return g;
 }
 
-hipError_t launch_reorder(const Plan &p, const Work &w, const tb_tree &out, hipStream_t s) {
-  auto k = reorder_finishes(p.n_leaf) ? k_reorder<true> : k_reorder<false>;
-  k<<<(unsigned)p.cell_tiles, kCellThreads, window_lds_bytes(p.n_leaf), s>>>(
+template <int IPT>
+static hipError_t reorder_t(const Plan &p, const Work &w, const tb_tree &out, hipStream_t s) {
+  auto k = reorder_finishes(p.n_leaf) ? k_reorder<true, IPT> : k_reorder<false, IPT>;
+  k<<<(unsigned)p.cell_tiles, kCellThreads, window_lds_bytes(p.n_leaf, p.cell_tile), s>>>(
       reorder_args(p, w, out));
   return hipGetLastError();
+}
+
+hipError_t launch_reorder(const Plan &p, const Work &w, const tb_tree &out, hipStream_t s) {
+  return p.cell_tile == kCellTile ? reorder_t<kCellIpt>(p, w, out, s)
+                                  : reorder_t<kSmallIpt>(p, w, out, s);
 }
 
 hipError_t launch_runs(const Plan &p, const Work &w, const tb_tree &out, hipStream_t s) {
@@ -1132,8 +1151,9 @@ hipError_t launch_runs(const Plan &p, const Work &w, const tb_tree &out, hipStre
   // small grids, which return at once in the common case that nothing is listed
   k_sort_runs<<<(unsigned)(most < 256 ? most : 256), kCellThreads, 0, s>>>(
       g, reinterpret_cast<int32_t *>(w.vals1), w.keys0, w.keys1);
-  k_reorder_again<<<(unsigned)(p.cell_tiles < 512 ? p.cell_tiles : 512), kCellThreads,
-                    window_lds_bytes(p.n_leaf), s>>>(g);
+  auto k = p.cell_tile == kCellTile ? k_reorder_again<kCellIpt> : k_reorder_again<kSmallIpt>;
+  k<<<(unsigned)(p.cell_tiles < 512 ? p.cell_tiles : 512), kCellThreads,
+      window_lds_bytes(p.n_leaf, p.cell_tile), s>>>(g);
   return hipGetLastError();
 }
 
@@ -1147,15 +1167,20 @@ size_t cell_lds_limit() {
   if (dev != cached_dev) {
     int v = 0;
     if (hipDeviceGetAttribute(&v, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) != hipSuccess) return 0;
-    const int want = (int)cell_emit_lds(TB_MAX_NLEAF);
+    const int want = (int)cell_emit_lds(TB_MAX_NLEAF, kCellTile);
     const int opt = v < want ? v : want;
-    (void)hipFuncSetAttribute(reinterpret_cast<const void *>(k_cell_emit<false>),
-                              hipFuncAttributeMaxDynamicSharedMemorySize, opt);
-    (void)hipFuncSetAttribute(reinterpret_cast<const void *>(k_cell_emit<true>),
-                              hipFuncAttributeMaxDynamicSharedMemorySize, opt);
-    for (const void *k : {reinterpret_cast<const void *>(k_reorder<true>),
-                          reinterpret_cast<const void *>(k_reorder<false>),
-                          reinterpret_cast<const void *>(k_reorder_again)})
+    const void *kernels[] = {
+        reinterpret_cast<const void *>(k_cell_emit<false, kCellIpt>),
+        reinterpret_cast<const void *>(k_cell_emit<true, kCellIpt>),
+        reinterpret_cast<const void *>(k_cell_emit<false, kSmallIpt>),
+        reinterpret_cast<const void *>(k_cell_emit<true, kSmallIpt>),
+        reinterpret_cast<const void *>(k_reorder<true, kCellIpt>),
+        reinterpret_cast<const void *>(k_reorder<false, kCellIpt>),
+        reinterpret_cast<const void *>(k_reorder<true, kSmallIpt>),
+        reinterpret_cast<const void *>(k_reorder<false, kSmallIpt>),
+        reinterpret_cast<const void *>(k_reorder_again<kCellIpt>),
+        reinterpret_cast<const void *>(k_reorder_again<kSmallIpt>)};
+    for (const void *k : kernels)
       (void)hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, opt);
     cached = (size_t)v;
     cached_dev = dev;
@@ -1164,8 +1189,11 @@ size_t cell_lds_limit() {
 }
 
 hipError_t launch_cell_emit(const Plan &p, const Work &w, const tb_tree &out, hipStream_t s) {
-  const size_t lds = emit_lds_bytes(p.n_leaf);
-  auto k = (p.flags & 0xffu) == TB_MIXED ? k_cell_emit<true> : k_cell_emit<false>;
+  const size_t lds = emit_lds_bytes(p.n_leaf, p.cell_tile);
+  const bool mixed = (p.flags & 0xffu) == TB_MIXED;
+  auto k = p.cell_tile == kCellTile
+               ? (mixed ? k_cell_emit<true, kCellIpt> : k_cell_emit<false, kCellIpt>)
+               : (mixed ? k_cell_emit<true, kSmallIpt> : k_cell_emit<false, kSmallIpt>);
   k<<<(unsigned)p.cell_tiles, kCellThreads, lds, s>>>(
       sorted_keys(p, w), w.ad, p.n_leaf, w.cell_excl, p.cell_tiles, w.tile_start, w.tile_set,
       w.set_off, p.nsets, w.lvl_off, w.box, w.sorted, out.cell_key, out.cell_level,
@@ -1175,12 +1203,9 @@ hipError_t launch_cell_emit(const Plan &p, const Work &w, const tb_tree &out, hi
   return hipGetLastError();
 }
 
-// Dynamic LDS of the reorder pass for this n_leaf.
-size_t cell_reorder_lds(int nl) { return window_lds_bytes(nl); }
-
-// The larger of the two cell kernels' LDS needs for this n_leaf.
-size_t cell_emit_lds(int nl) {
-  const size_t a = emit_lds_bytes(nl), b = window_lds_bytes(nl);
+// The larger of the two cell kernels' LDS needs for this n_leaf and tile.
+size_t cell_emit_lds(int nl, int cell_tile) {
+  const size_t a = emit_lds_bytes(nl, cell_tile), b = window_lds_bytes(nl, cell_tile);
   return a > b ? a : b;
 }
 

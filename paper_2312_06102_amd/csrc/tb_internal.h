@@ -29,6 +29,9 @@ constexpr int kLevelWords = (kLevels + 1) / 2;  // 16-bit level counters packed 
 constexpr int kCellThreads = 256;
 constexpr int kCellIpt = 8;
 constexpr int kCellTile = kCellThreads * kCellIpt;  // 2048 particles
+// Sets too small to fill the chip with such tiles take smaller ones.
+constexpr int kSmallIpt = 2;
+constexpr int kSmallTile = kCellThreads * kSmallIpt;  // 512 particles
 
 
 // The chip's eight XCDs each have their own L2, and workgroups of a launch are
@@ -114,6 +117,7 @@ struct Plan {
   bool seg;         // batch of several sets: every radix pass sorts each set in place
                     // (tiles never straddle a set; each set has its own digit bases)
   int64_t sort_tiles;
+  int cell_tile;        // particles of a cell tile: kCellTile or kSmallTile
   int64_t cell_tiles;   // upper bound of the cell tiles of all sets
   int32_t bbox_chunk;   // particles of a bounding-box chunk
   int64_t bbox_chunks;  // upper bound of the bounding-box chunks of all sets
@@ -235,10 +239,9 @@ hipError_t launch_cell_scan(const Plan &p, const Work &w, const tb_tree &out,
 hipError_t launch_reorder(const Plan &p, const Work &w, const tb_tree &out, hipStream_t s);
 hipError_t launch_runs(const Plan &p, const Work &w, const tb_tree &out, hipStream_t s);
 size_t cell_lds_limit();
-size_t cell_reorder_lds(int nl);
 bool reorder_finishes(int nl);
 hipError_t launch_cell_emit(const Plan &p, const Work &w, const tb_tree &out, hipStream_t s);
-size_t cell_emit_lds(int nl);
+size_t cell_emit_lds(int nl, int cell_tile);
 // tb_parents.hip
 hipError_t launch_parents(const Plan &p, const Work &w, int depth, const tb_tree &out,
                           hipStream_t s);

@@ -41,7 +41,7 @@ __global__ __launch_bounds__(kInitThreads) void k_init(
     int n_low, uint32_t *__restrict__ counters, int32_t *__restrict__ status_word, int64_t n, int32_t nsets,
     const int64_t *__restrict__ set_off_in, int64_t *__restrict__ set_off,
     const tb_box *__restrict__ boxes_in, double *__restrict__ box, int host_box, double lo0,
-    double lo1, double lo2, double side, int single, int chunk,
+    double lo1, double lo2, double side, int single, int cell_tile, int chunk,
     int64_t *__restrict__ tile_start,
     int32_t *__restrict__ tile_set, int64_t *__restrict__ chunk_start,
     int32_t *__restrict__ chunk_set) {
@@ -52,7 +52,7 @@ __global__ __launch_bounds__(kInitThreads) void k_init(
   if (single) {
     // one set given by the host: its tables need no validation or scan (the
     // chunk table exists only when the box comes from the data: chunk > 0)
-    const int64_t nt = (n + kCellTile - 1) / kCellTile;
+    const int64_t nt = (n + cell_tile - 1) / cell_tile;
     const int64_t nc = chunk ? (n + chunk - 1) / chunk : 0;
     for (int64_t t = tid; t < nt; t += stride) tile_set[t] = 0;
     for (int64_t c = tid; c < nc; c += stride) chunk_set[c] = 0;
@@ -108,7 +108,8 @@ hipError_t launch_init(const Plan &p, const Work &w, const BatchIn &in, const tb
                                          in.set_off, w.set_off, in.dev_boxes, w.box, hb ? 1 : 0,
                                          hb ? hb->lo[0] : 0.0, hb ? hb->lo[1] : 0.0,
                                          hb ? hb->lo[2] : 0.0, hb ? hb->side : 1.0,
-                                         single_set(p, in) ? 1 : 0, in.auto_box ? p.bbox_chunk : 0,
+                                         single_set(p, in) ? 1 : 0, p.cell_tile,
+                                         in.auto_box ? p.bbox_chunk : 0,
                                          w.tile_start, w.tile_set,
                                          w.chunk_start, w.chunk_set);
   return hipGetLastError();
@@ -128,7 +129,7 @@ __device__ __forceinline__ bool box_valid(const double *b) {
 __global__ __launch_bounds__(kSetupThreads) void k_setup(
     int64_t *__restrict__ set_off, int32_t nsets, int64_t n, int64_t *__restrict__ tile_start,
     int64_t *__restrict__ chunk_start, int64_t *__restrict__ sort_tile_start, int sort_tile_keys,
-    int chunk, double *__restrict__ box, int check_boxes, int max_set_bits,
+    int cell_tile, int chunk, double *__restrict__ box, int check_boxes, int max_set_bits,
     uint32_t *__restrict__ oversize, int32_t *__restrict__ status_word) {
   __shared__ uint32_t s_w[3][kSetupThreads / 64];
   __shared__ uint64_t s_carry[3];
@@ -181,7 +182,7 @@ __global__ __launch_bounds__(kSetupThreads) void k_setup(
     const int b = r0 + threadIdx.x;
     int64_t nb = 0;
     if (b < nsets) nb = set_off[b + 1] - set_off[b];
-    const uint32_t nt = (uint32_t)((nb + kCellTile - 1) / kCellTile);
+    const uint32_t nt = (uint32_t)((nb + cell_tile - 1) / cell_tile);
     const uint32_t nc = chunk ? (uint32_t)((nb + chunk - 1) / chunk) : 0u;
     const uint32_t ns = sort_tile_start ? (uint32_t)((nb + sort_tile_keys - 1) / sort_tile_keys)
                                         : 0u;
@@ -260,7 +261,7 @@ hipError_t launch_setup(const Plan &p, const Work &w, const BatchIn &in, int32_t
   const bool with_chunks = in.auto_box;
   k_setup<<<1, kSetupThreads, 0, s>>>(w.set_off, p.nsets, p.n, w.tile_start, w.chunk_start,
                                       p.seg ? w.seg_tile_start : nullptr, p.sort.tile(),
-                                      with_chunks ? p.bbox_chunk : 0, w.box, in.dev_boxes ? 1 : 0,
+                                      p.cell_tile, with_chunks ? p.bbox_chunk : 0, w.box, in.dev_boxes ? 1 : 0,
                                       p.set_index_bits, w.counters + kOversizeCounter, status);
   const int64_t n_counts =
       p.seg ? (int64_t)p.nsets * (p.key_passes + p.low_passes) * p.sort.radix() : 0;

@@ -605,7 +605,7 @@ __global__ __launch_bounds__(kParentThreads) void k_tile_parents(
     ParentArgs g, const uint64_t *__restrict__ keys, const uint32_t *__restrict__ excl,
     int64_t cell_tiles, const int64_t *__restrict__ tile_start,
     const int32_t *__restrict__ tile_set, const int64_t *__restrict__ set_off, int32_t nsets,
-    const int64_t *__restrict__ lvl_off, const double *__restrict__ box,
+    int cell_tile, const int64_t *__restrict__ lvl_off, const double *__restrict__ box,
     const int64_t *__restrict__ n_cells, int32_t *__restrict__ left) {
   constexpr int W = kParentThreads / 64;
   __shared__ typename Combine<MIXED>::Lds s_lds[W];
@@ -614,7 +614,7 @@ __global__ __launch_bounds__(kParentThreads) void k_tile_parents(
   const int64_t tile = (int64_t)xcd_tile(blockIdx.x, gridDim.x) * W + threadIdx.x / 64;
   if (tile >= tile_start[nsets]) return;  // the whole wave; no barrier follows
   g.n_cells = *n_cells;
-  const TileRange tr = tile_range(tile, tile_start, tile_set, set_off);
+  const TileRange tr = tile_range(tile, tile_start, tile_set, set_off, cell_tile);
   const double side = box[4 * tr.b + 3];
   const UnitEnd ue = unit_end(tr, keys);
   // lane d: the cells [r0, r0 + rn) of depth d that start in the tile
@@ -680,8 +680,9 @@ template <bool MIXED>
 __global__ __launch_bounds__(kGroupThreads) void k_group_parents(
     ParentArgs g, const uint64_t *__restrict__ keys, int64_t unit,
     const int64_t *__restrict__ tile_start, const int32_t *__restrict__ tile_set,
-    const int64_t *__restrict__ set_off, int32_t nsets, const double *__restrict__ box,
-    const int64_t *__restrict__ n_cells, const int32_t *__restrict__ left, int64_t units,
+    const int64_t *__restrict__ set_off, int32_t nsets, int cell_tile,
+    const double *__restrict__ box, const int64_t *__restrict__ n_cells,
+    const int32_t *__restrict__ left, int64_t units,
     int32_t *__restrict__ left2, int64_t groups) {
   __shared__ typename Combine<MIXED>::Lds s_lds[kGroupThreads / 64];
   __shared__ int32_t s_pc[kMaxDepth][kGroupUnits], s_fc[kMaxDepth][kGroupUnits];
@@ -709,7 +710,7 @@ __global__ __launch_bounds__(kGroupThreads) void k_group_parents(
     const int64_t tile = min((u0 + q + 1) * unit - 1, last);
     const int b = tile_set[tile], bl = tile_set[last];
     const double side = box[4 * b + 3];
-    const UnitEnd ue = unit_end(tile_range(last, tile_start, tile_set, set_off), keys);
+    const UnitEnd ue = unit_end(tile_range(last, tile_start, tile_set, set_off, cell_tile), keys);
     for (int d = kMaxDepth - 1; d >= 0; --d) {
       if (!((any >> d) & 1u)) continue;
       const int64_t pc = s_pc[d][q];
@@ -734,16 +735,16 @@ static hipError_t owned_parents_t(const Plan &p, const Work &w, const tb_tree &o
                        reinterpret_cast<int32_t *>(w.status1)};
   constexpr int W = kParentThreads / 64;
   k_tile_parents<MIXED><<<(unsigned)((p.cell_tiles + W - 1) / W), kParentThreads, 0, s>>>(
-      g, keys, w.cell_excl, p.cell_tiles, w.tile_start, w.tile_set, w.set_off, p.nsets, w.lvl_off,
-      w.box, out.n_cells, reinterpret_cast<int32_t *>(w.cell_cnt));
+      g, keys, w.cell_excl, p.cell_tiles, w.tile_start, w.tile_set, w.set_off, p.nsets, p.cell_tile,
+      w.lvl_off, w.box, out.n_cells, reinterpret_cast<int32_t *>(w.cell_cnt));
   // every set is one tile, or units of more and more tiles until one holds them all
   // (a batch's largest set may have all but one of the particles)
   int64_t units = p.cell_tiles, unit = 1;
-  for (int level = 0; unit * kCellTile < p.n; ++level) {
+  for (int level = 0; unit * p.cell_tile < p.n; ++level) {
     const int64_t groups = (units + kGroupUnits - 1) / kGroupUnits;
     k_group_parents<MIXED><<<(unsigned)groups, kGroupThreads, 0, s>>>(
-        g, keys, unit, w.tile_start, w.tile_set, w.set_off, p.nsets, w.box, out.n_cells, left,
-        units, space[level % 2], groups);
+        g, keys, unit, w.tile_start, w.tile_set, w.set_off, p.nsets, p.cell_tile, w.box,
+        out.n_cells, left, units, space[level % 2], groups);
     left = space[level % 2];
     units = groups;
     unit *= kGroupUnits;

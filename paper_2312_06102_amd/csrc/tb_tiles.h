@@ -14,12 +14,13 @@ constexpr int kWaves = kCellThreads / 64;
 
 // Per-thread packed per-depth counts of the cells started by this thread's
 // particles (particle i starts the cells at depths A_i .. D_i).
-__device__ inline void thread_level_counts(const uint8_t A[kCellIpt], const uint8_t D[kCellIpt],
+template <int IPT>
+__device__ inline void thread_level_counts(const uint8_t (&A)[IPT], const uint8_t (&D)[IPT],
                                            uint32_t c[kLevelWords]) {
 #pragma unroll
   for (int wi = 0; wi < kLevelWords; ++wi) c[wi] = 0;
 #pragma unroll
-  for (int j = 0; j < kCellIpt; ++j) {
+  for (int j = 0; j < IPT; ++j) {
     const int a = A[j], d = D[j];
 #pragma unroll
     for (int wi = 0; wi < kLevelWords; ++wi) {
@@ -60,7 +61,7 @@ __device__ __forceinline__ uint32_t unpack(const uint32_t w[kLevelWords], int d)
   return (w[d >> 1] >> ((d & 1) * 16)) & 0xffffu;
 }
 
-// Tile t of set b covers [t0, t1) inside the set's range [S, E).
+// Tile t (of `tile` particles) of set b covers [t0, t1) inside the set's range [S, E).
 struct TileRange {
   int b;
   int64_t S, E, t0, t1;
@@ -68,13 +69,14 @@ struct TileRange {
 
 __device__ __forceinline__ TileRange tile_range(int64_t t, const int64_t *__restrict__ tile_start,
                                                 const int32_t *__restrict__ tile_set,
-                                                const int64_t *__restrict__ set_off) {
+                                                const int64_t *__restrict__ set_off,
+                                                int tile) {
   TileRange r;
   r.b = tile_set[t];
   r.S = set_off[r.b];
   r.E = set_off[r.b + 1];
-  r.t0 = r.S + (t - tile_start[r.b]) * (int64_t)kCellTile;
-  r.t1 = min(r.t0 + (int64_t)kCellTile, r.E);
+  r.t0 = r.S + (t - tile_start[r.b]) * (int64_t)tile;
+  r.t1 = min(r.t0 + (int64_t)tile, r.E);
   return r;
 }
 

@@ -1,5 +1,5 @@
-"""Parents built by the owners of their particles: tiles of 2048, groups of 32 tiles,
-groups of groups.  Sizes at the edges of each, both sides of the rule that picks this
+"""Parents built by the owners of their particles: tiles of 512 or 2048, groups of 32
+tiles, groups of groups.  Sizes at the edges of each, both sides of the rule that picks this
 path, precisions and curves, and batches whose sets straddle groups; structure exactly
 and moments to the suite's tolerances against the oracle."""
 import numpy as np
@@ -26,8 +26,9 @@ def check(pos, mass, n_leaf, precision="fp64"):
     assert max(errs) <= (1e-12 if precision == "fp64" else 1e-5), errs
 
 
-@pytest.mark.parametrize("n", [2, 17, 2047, 2048, 2049, 4097, 65535, 65536, 65537, 131073,
-                               2 ** 21, 2 ** 21 + 1])
+@pytest.mark.parametrize("n", [2, 17, 511, 512, 513, 2047, 2048, 2049, 4097, 16383, 16384, 16385,
+                               65535, 65536, 65537, 131073, 524289, 3 * 2 ** 18,
+                               3 * 2 ** 18 + 1, 2 ** 21, 2 ** 21 + 1])
 def test_edges_of_tiles_and_groups(n):
     pos, mass = dg.plummer(n, seed=n, masses="lognormal")
     check(pos, mass, 16)
