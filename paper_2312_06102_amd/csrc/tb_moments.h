@@ -144,6 +144,14 @@ __device__ __forceinline__ void kahan_add(float &sum, float &comp, float x) {
   sum = t;
 }
 
+// The same of a b, which is not rounded before it meets the compensation.
+__device__ __forceinline__ void kahan_add_product(float &sum, float &comp, float a, float b) {
+  const float y = fmaf(a, b, -comp);
+  const float t = sum + y;
+  comp = (t - sum) - y;
+  sum = t;
+}
+
 struct LeafSumsF {
   float s[10], c[10];  // m, m u (3), m u u (6): sums and Kahan compensations
 };

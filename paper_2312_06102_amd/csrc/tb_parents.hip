@@ -515,7 +515,7 @@ __device__ inline bool combine_children(const ParentArgs &g, typename Combine<MI
           kahan_add(t, tc, m[x]);
           kahan_add(t, tc, v[x]);
         } else {
-          kahan_add(t, tc, m[x] * v[x]);
+          kahan_add_product(t, tc, m[x], v[x]);
         }
         S = x < nch ? t : S;
         Sc = x < nch ? tc : Sc;
@@ -548,12 +548,14 @@ __device__ inline bool combine_children(const ParentArgs &g, typename Combine<MI
     mine[4] = q[4] + mc * (three * d1 * d2);
     mine[5] = q[5] + mc * (three * d2 * d2 - dd);
   } else {
-    mine[0] = q[0] * qs + mc * (three * d0 * d0 - dd);
-    mine[1] = q[1] * qs + mc * (three * d0 * d1);
-    mine[2] = q[2] * qs + mc * (three * d0 * d2);
-    mine[3] = q[3] * qs + mc * (three * d1 * d1 - dd);
-    mine[4] = q[4] * qs + mc * (three * d1 * d2);
-    mine[5] = q[5] * qs + mc * (three * d2 * d2 - dd);
+    // (fused products spelled out: the same roundings as in k_parents_mixed)
+    const float s2 = fmaf(d2, d2, fmaf(d0, d0, d1 * d1));
+    mine[0] = fmaf(q[0], qs, mc * fmaf(three * d0, d0, -s2));
+    mine[1] = fmaf(q[1], qs, mc * (three * d0 * d1));
+    mine[2] = fmaf(q[2], qs, mc * (three * d0 * d2));
+    mine[3] = fmaf(q[3], qs, mc * fmaf(three * d1, d1, -s2));
+    mine[4] = fmaf(mc, three * d1 * d2, q[4] * qs);
+    mine[5] = fmaf(q[5], qs, mc * fmaf(three * d2, d2, -s2));
   }
   wave_lds_fence();
   T Q = T(0), Qc = T(0);
