@@ -146,6 +146,7 @@ __device__ __forceinline__ void kahan_add(float &sum, float &comp, float x) {
 
 // The same of a b, which is not rounded before it meets the compensation.
 __device__ __forceinline__ void kahan_add_product(float &sum, float &comp, float a, float b) {
+#pragma clang fp contract(off)
   const float y = fmaf(a, b, -comp);
   const float t = sum + y;
   comp = (t - sum) - y;
