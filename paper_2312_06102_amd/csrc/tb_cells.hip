@@ -456,17 +456,12 @@ __device__ inline void reorder_tile(const ReorderArgs &g, const WindowLds &s, in
     const int li = threadIdx.x * IPT + j;
     if (li < T) g.ad[t0 + li] = (uint16_t)(A[j] | (D[j] << 8));
   }
-  uint32_t c[kLevelWords], tot[kLevelWords];
+  uint32_t c[kLevelWords], inc[kLevelWords];
   thread_level_counts(A, D, c);
-  block_level_scan(s.wtot, c, tot);
+  wave_level_scan(s.wtot, c, inc);
+  __syncthreads();
   const int d = threadIdx.x;
-  if (d < kLevels) {
-    uint32_t cnt = 0;
-#pragma unroll
-    for (int wi = 0; wi < kLevelWords; ++wi)
-      if (wi == (d >> 1)) cnt = (tot[wi] >> ((d & 1) * 16)) & 0xffffu;
-    g.tile_cnt[d * g.cell_tiles + tile] = cnt;
-  }
+  if (d < kLevels) g.tile_cnt[d * g.cell_tiles + tile] = block_level_total(s.wtot, d);
 }
 
 template <bool FINISH, int IPT>
@@ -917,9 +912,9 @@ __global__ __launch_bounds__(kCellThreads) void k_cell_emit(
     }
     if (threadIdx.x % kShare == 0) s.heads[threadIdx.x / kShare] = (uint8_t)hb;
   }
-  uint32_t c[kLevelWords], tot[kLevelWords];
+  uint32_t c[kLevelWords];
   thread_level_counts(A, D, c);
-  block_level_scan(s.wtot, c, tot);  // its barrier also publishes s.heads
+  block_level_scan(s.wtot, c);  // its barrier also publishes s.heads
 #pragma unroll
   for (int d = 0; d < kLevels; ++d) s.off[d * kCellThreads + threadIdx.x] = (uint16_t)unpack(c, d);
   // this thread's leaves go to a contiguous run of the leaf list

@@ -448,14 +448,17 @@ __device__ __forceinline__ int min_depth(uint64_t a, uint64_t b) {
   return (z + 2) / 3;
 }
 
-// Inclusive wave64 scan of a u32 (shuffle-based).
+// Inclusive sum over the wave's lanes by data-parallel primitives in the vector unit:
+// the rows of 16 lanes, then lane 15 of a row into the next row, then lane 31 into the
+// upper half (lanes and rows a step does not reach add 0).
 __device__ __forceinline__ uint32_t wave_inclusive_scan(uint32_t v) {
-  const int l = lane_id();
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    uint32_t t = __shfl_up(v, o, 64);
-    if (l >= o) v += t;
-  }
+  constexpr int kRowShr = 0x110, kRowBcast15 = 0x142, kRowBcast31 = 0x143;
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, kRowShr + 1, 0xf, 0xf, true);
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, kRowShr + 2, 0xf, 0xf, true);
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, kRowShr + 4, 0xf, 0xf, true);
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, kRowShr + 8, 0xf, 0xf, true);
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, kRowBcast15, 0xa, 0xf, false);
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, kRowBcast31, 0xc, 0xf, false);
   return v;
 }
 
