@@ -100,12 +100,12 @@ struct EmitLds {
   uint8_t *a;          // [T + NL]        a_i, i in [t0, t1 + NL)
   uint8_t *d;          // [T]             D_i, i in [t0, t1)
   uint32_t *wtot;      // [kWaves][kLevelWords]
-  uint32_t *lvl;       // [kLevels]       per-depth base of this tile
-  uint16_t *off;       // [kLevels][kCellThreads] next cell slot per depth per thread
+  uint32_t *lvl;       // [kLevels]       first slot of the depth's cells of this tile, less
+                       //                 the tile's cells at smaller depths
+  uint16_t *off;       // [kLevels][kCellThreads] next cell per depth per thread
   float4 *rec;         // [T + NL]        sorted (x, y, z, m) of [t0, t1 + NL); stored once
-                       //                 the cells are placed, over the dead `off` and `leaf`
-  uint32_t *leaf;      // [T]             leaf starting in the tile: local first particle |
-                       //                 depth << 11 | slot within its depth << 16; beside
+                       //                 the cells are listed, over the dead `off` and `list`
+  uint32_t *list;      // [T]             cells starting in the tile (k_cell_emit); beside
                        //                 `off`, and read into registers before `rec` is stored
   uint8_t *heads;      // [T / 8]         bit li: particle t0 + li starts a leaf
   uint32_t *nleaf;     // [1]
@@ -116,7 +116,7 @@ __host__ __device__ inline size_t emit_off_bytes() {
 }
 
 __host__ __device__ inline size_t emit_union_bytes(int nl, int tile) {
-  const size_t cells = emit_off_bytes() + (size_t)tile * 4;  // off, then leaf
+  const size_t cells = emit_off_bytes() + (size_t)tile * 4;  // off, then list
   const size_t rec = (size_t)(tile + nl) * 16;
   return round16(cells > rec ? cells : rec);
 }
@@ -136,11 +136,11 @@ __device__ inline EmitLds carve_emit(unsigned char *base, int nl, int tile) {
   base += round16((size_t)kWaves * kLevelWords * 4);
   s.lvl = reinterpret_cast<uint32_t *>(base);
   base += round16(kLevels * 4);
-  // the per-depth cursors and the leaf list are dead once the cells are placed
-  // (each thread keeps its leaf entries in registers); the particle records
+  // the per-depth cursors and the list are dead once the cells are listed
+  // (each thread keeps its entries in registers); the particle records
   // take their place for the moment phase
   s.off = reinterpret_cast<uint16_t *>(base);
-  s.leaf = reinterpret_cast<uint32_t *>(base + emit_off_bytes());
+  s.list = reinterpret_cast<uint32_t *>(base + emit_off_bytes());
   s.rec = reinterpret_cast<float4 *>(base);
   base += emit_union_bytes(nl, tile);
   s.heads = base;
@@ -834,6 +834,17 @@ __device__ inline int64_t leaf_end_fast(const EmitLds &s, const uint64_t *__rest
 // ---------------------------------------------------------------------------
 // One workgroup per cell tile: a_i and D_i (from the reorder pass) give every
 // cell whose first particle lies in the tile; the per-depth prefix places it.
+//
+// The tile's cells are listed in LDS in the order of the output (depth, then place), and
+// then written one a lane: neighbouring lanes write neighbouring cells.  Each thread
+// writing the cells of its own particles sent 1.7 times the write requests, in three times
+// the store instructions, and kept the address units busy 3/4 of the time: 2^26 clustered
+// particles 1570 us, 1211 us from the list (4.5 GB at 3.7 TB/s); 2^24 255 and 232 us.  A
+// list entry is local first particle |
+// depth << 11 | (internal cells) (first child's place in the list + 2^15) << 16.  A tile
+// with more cells than particles (n_leaf of 1, or coincident pairs) has no room for the
+// list: there each thread writes its cells as it finds them, and lists the leaves as
+// local first particle | depth << 11 | place among the tile's cells << 16.
 template <bool MIXED, int IPT>
 __global__ __launch_bounds__(kCellThreads) void k_cell_emit(
     const uint64_t *__restrict__ keys, const uint16_t *__restrict__ ad, int nl,
@@ -853,22 +864,24 @@ __global__ __launch_bounds__(kCellThreads) void k_cell_emit(
   const TileRange tr = tile_range(tile, tile_start, tile_set, set_off, kTile);
   const int64_t t0 = tr.t0, t1 = tr.t1, n = tr.E;  // n: end of this tile's set
   const int T = (int)(t1 - t0);
+  // the structure of cell ci at depth d, from its first particle i and that one's key;
+  // fc: its first child, or -1
+  auto put_cell = [&](uint32_t ci, uint64_t key, int d, int64_t i, int32_t fc) {
+    cell_key[ci] = key >> (63 - 3 * d);
+    cell_level[ci] = (uint8_t)d;
+    cell_first[ci] = (int32_t)i;
+    reinterpret_cast<int2 *>(child_ptr)[ci] = make_int2(fc, 0);
+    if (head_parent && fc >= 0 && (int64_t)fc < c_max) head_parent[fc] = (int32_t)ci;
+  };
 
   // per-depth base of this tile: the set's first cell of the depth plus the
   // cells of the set's earlier tiles
+  uint32_t base = 0;
   if (threadIdx.x < kLevels) {
     const int d = threadIdx.x;
-    s.lvl[d] = (uint32_t)(lvl_off[tr.b * (kLevels + 1) + d] + excl[d * cell_tiles + tile]);
+    base = (uint32_t)(lvl_off[tr.b * (kLevels + 1) + d] + excl[d * cell_tiles + tile]);
   }
   if (threadIdx.x == 0) *s.nleaf = 0;
-  // this thread's particles t0 + 8t .. t0 + 8t + 7: their keys (issued first,
-  // so that they travel with the batched loads below)
-  uint64_t kk[IPT];
-#pragma unroll
-  for (int j = 0; j < IPT; ++j) {
-    const int li = threadIdx.x * IPT + j;
-    kk[j] = keys[t0 + (li < T ? li : T - 1)];
-  }
   // the (a, D) of the tile's particles and the n_leaf halo into LDS, in one
   // batch of loads
   const int span = (int)(min(t1 + (int64_t)nl, n) - t0);
@@ -915,63 +928,95 @@ __global__ __launch_bounds__(kCellThreads) void k_cell_emit(
   uint32_t c[kLevelWords];
   thread_level_counts(A, D, c);
   block_level_scan(s.wtot, c);  // its barrier also publishes s.heads
+  // the tile's cells at smaller depths (lane d: before depth d)
+  const uint32_t cnt = lane_id() < kLevels ? block_level_total(s.wtot, lane_id()) : 0u;
+  const uint32_t upto = wave_inclusive_scan(cnt);
+  const int ncells = __builtin_amdgcn_readlane((int)upto, 63);
+  const bool listed = ncells <= kTile;
+  if (threadIdx.x < kLevels) s.lvl[threadIdx.x] = base - (upto - cnt);
 #pragma unroll
-  for (int d = 0; d < kLevels; ++d) s.off[d * kCellThreads + threadIdx.x] = (uint16_t)unpack(c, d);
-  // this thread's leaves go to a contiguous run of the leaf list
-  uint32_t my_leaves = 0;
-#pragma unroll
-  for (int j = 0; j < IPT; ++j) my_leaves += (A[j] <= D[j]) ? 1u : 0u;
-  const uint32_t inc = wave_inclusive_scan(my_leaves);
-  uint32_t wave_base = 0;
-  if (lane_id() == 63) wave_base = atomicAdd(s.nleaf, inc);
-  wave_base = __shfl(wave_base, 63, 64);
-  uint32_t leaf_slot = wave_base + inc - my_leaves;
+  for (int d = 0; d < kLevels; ++d)
+    s.off[d * kCellThreads + threadIdx.x] =
+        (uint16_t)(unpack(c, d) + (uint32_t)__builtin_amdgcn_readlane((int)(upto - cnt), d));
 
-  // cell structure; leaves are queued for the moment phase
   bool internal = false;
+  int nlist = ncells;
+  if (listed) {
 #pragma unroll
-  for (int j = 0; j < IPT; ++j) {
-    const int a = A[j], dl = D[j];
-    if (a > dl) continue;
-    const int li = threadIdx.x * IPT + j;
-    const int64_t i = t0 + li;
-    const uint64_t key = kk[j];
-    for (int d = a; d <= dl; ++d) {
-      const uint32_t rel = s.off[d * kCellThreads + threadIdx.x];
-      s.off[d * kCellThreads + threadIdx.x] = (uint16_t)(rel + 1);
-      const uint32_t ci = s.lvl[d] + rel;
-      if ((int64_t)ci >= c_max) {  // cannot happen with consistent counts
-        internal = true;
-        continue;
+    for (int j = 0; j < IPT; ++j) {
+      const int a = A[j], dl = D[j];
+      if (a > dl) continue;
+      const uint32_t li = threadIdx.x * IPT + j;
+      uint32_t x = s.off[a * kCellThreads + threadIdx.x];
+      for (int d = a; d < dl; ++d) {
+        s.off[d * kCellThreads + threadIdx.x] = (uint16_t)(x + 1);
+        // first child: this particle's cell one depth down
+        const uint32_t xc = s.off[(d + 1) * kCellThreads + threadIdx.x];
+        if (x < (uint32_t)kTile) s.list[x] = li | ((uint32_t)d << 11) | ((xc | 0x8000u) << 16);
+        x = xc;
       }
-      cell_key[ci] = key >> (63 - 3 * d);
-      cell_level[ci] = (uint8_t)d;
-      cell_first[ci] = (int32_t)i;
-      if (d < dl) {
-        // first child: this particle's cell one depth down (emitted next)
-        const uint32_t fc = s.lvl[d + 1] + s.off[(d + 1) * kCellThreads + threadIdx.x];
-        reinterpret_cast<int2 *>(child_ptr)[ci] = make_int2((int32_t)fc, 0);
-        if (head_parent && (int64_t)fc < c_max) head_parent[fc] = (int32_t)ci;
-      } else {
-        reinterpret_cast<int2 *>(child_ptr)[ci] = make_int2(-1, 0);
-        s.leaf[leaf_slot] = (uint32_t)li | ((uint32_t)dl << 11) | (rel << 16);
-        ++leaf_slot;
+      s.off[dl * kCellThreads + threadIdx.x] = (uint16_t)(x + 1);
+      if (x < (uint32_t)kTile) s.list[x] = li | ((uint32_t)dl << 11);
+    }
+  } else {
+    // this thread's leaves go to a contiguous run of the list
+    uint64_t kk[IPT];
+    uint32_t my_leaves = 0;
+#pragma unroll
+    for (int j = 0; j < IPT; ++j) {
+      const int li = threadIdx.x * IPT + j;
+      kk[j] = keys[t0 + (li < T ? li : T - 1)];
+      my_leaves += (A[j] <= D[j]) ? 1u : 0u;
+    }
+    const uint32_t inc = wave_inclusive_scan(my_leaves);
+    uint32_t wave_base = 0;
+    if (lane_id() == 63) wave_base = atomicAdd(s.nleaf, inc);
+    wave_base = __shfl(wave_base, 63, 64);
+    uint32_t leaf_slot = wave_base + inc - my_leaves;
+    __syncthreads();  // s.lvl
+#pragma unroll
+    for (int j = 0; j < IPT; ++j) {
+      const int a = A[j], dl = D[j];
+      if (a > dl) continue;
+      const int li = threadIdx.x * IPT + j;
+      for (int d = a; d <= dl; ++d) {
+        const uint32_t x = s.off[d * kCellThreads + threadIdx.x];
+        s.off[d * kCellThreads + threadIdx.x] = (uint16_t)(x + 1);
+        const uint32_t ci = s.lvl[d] + x;
+        if ((int64_t)ci >= c_max) {  // cannot happen with consistent counts
+          internal = true;
+          continue;
+        }
+        int32_t fc = -1;
+        if (d < dl) {
+          fc = (int32_t)(s.lvl[d + 1] + s.off[(d + 1) * kCellThreads + threadIdx.x]);
+        } else {
+          s.list[leaf_slot] = (uint32_t)li | ((uint32_t)dl << 11) | (x << 16);
+          ++leaf_slot;
+        }
+        put_cell(ci, kk[j], d, t0 + li, fc);
       }
     }
   }
   __syncthreads();
-  // the leaf list shares its space with the records: each thread keeps its
-  // entries (at most IPT: a tile starts at most one leaf a particle)
-  const uint32_t nlv = *s.nleaf;
-  uint32_t my_leaf[IPT];
+  if (!listed) nlist = (int)*s.nleaf;
+  // the list shares its space with the records: each thread keeps its entries (at most
+  // IPT: a tile starts at most one leaf a particle) and the keys they start at
+  uint32_t mine[IPT];
+  uint64_t my_key[IPT];
 #pragma unroll
   for (int k = 0; k < IPT; ++k) {
-    const uint32_t x = threadIdx.x + (uint32_t)k * kCellThreads;
-    my_leaf[k] = x < nlv ? s.leaf[x] : 0u;
+    const int x = threadIdx.x + k * kCellThreads;
+    mine[k] = x < nlist ? s.list[x] : 0u;
+  }
+#pragma unroll
+  for (int k = 0; k < IPT; ++k) {
+    const int x = threadIdx.x + k * kCellThreads, li = mine[k] & 0x7ff;
+    my_key[k] = x < nlist && li < T ? keys[t0 + li] : 0ull;
   }
   __syncthreads();
 
-  // the cursors and the leaf list are dead: the particle records (tile and
+  // the cursors and the list are dead: the particle records (tile and
   // halo) take their place, in batched loads
   for (int x0 = 0; x0 < span; x0 += kRecBatch * kCellThreads) {
     float4 r[kRecBatch];
@@ -988,29 +1033,40 @@ __global__ __launch_bounds__(kCellThreads) void k_cell_emit(
   }
   __syncthreads();
 
-  // leaf moments: one lane per leaf, particles read from LDS
+  // one lane per cell (leaf, if they are not all listed); particles read from LDS
   const double lo[3] = {box[4 * tr.b + 0], box[4 * tr.b + 1], box[4 * tr.b + 2]};
   const double side = box[4 * tr.b + 3];
 #pragma unroll 1
   for (int k = 0; k < IPT; ++k) {
-    if (threadIdx.x + (uint32_t)k * kCellThreads >= nlv) break;
+    const int x0 = threadIdx.x + k * kCellThreads;
+    if (x0 >= nlist) break;
     // this thread's next entry; the rest move down (constant register indices)
-    const uint32_t le = my_leaf[0];
+    const uint32_t le = mine[0];
+    const uint64_t key = my_key[0];
 #pragma unroll
-    for (int j = 0; j + 1 < IPT; ++j) my_leaf[j] = my_leaf[j + 1];
+    for (int j = 0; j + 1 < IPT; ++j) {
+      mine[j] = mine[j + 1];
+      my_key[j] = my_key[j + 1];
+    }
     const int li = le & 0x7ff;
     const int dl = (le >> 11) & 31;
-    if (dl > kMaxDepth || li >= T) {  // cannot happen: entries come from the loop above
+    if (dl > kMaxDepth || li >= T) {  // cannot happen: entries come from the loops above
       internal = true;
       continue;
     }
-    const uint32_t ci = s.lvl[dl] + (le >> 16);
+    const uint32_t ci = s.lvl[dl] + (listed ? (uint32_t)x0 : le >> 16);
     if ((int64_t)ci >= c_max) {
       internal = true;
       continue;
     }
     const int64_t i = t0 + li;
-    const uint64_t key = keys[i];
+    if (listed) {
+      const bool leaf = (le >> 31) == 0;
+      // (an internal cell's depth is below kMaxDepth)
+      put_cell(ci, key, dl, i,
+               leaf ? -1 : (int32_t)(s.lvl[min(dl + 1, kMaxDepth)] + ((le >> 16) & 0x7fffu)));
+      if (!leaf) continue;
+    }
     const int64_t e = leaf_end_fast(s, keys, n, nl, t0, T, li, dl);
     cell_count[ci] = (int32_t)(e - i);
     const int sh = kMaxDepth - dl;
