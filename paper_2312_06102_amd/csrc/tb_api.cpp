@@ -346,7 +346,7 @@ static int build_impl(const float *pos, const float *mass, int64_t n, int32_t ns
     run("block_build", [&] { return launch_block_build(p, w, *out, s); });
     run("upper", [&] { return launch_upper(p, w, *out, s); });
   } else {
-    run("cell_emit", [&] { return launch_cell_emit(p, w, *out, s); });
+    run("cell_emit", [&] { return launch_cell_emit(p, w, *out, cell_offsets, s); });
     if (owned_parents(p))
       run("parents", [&] { return launch_owned_parents(p, w, *out, s); });
     else

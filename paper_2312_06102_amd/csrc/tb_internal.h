@@ -240,7 +240,8 @@ hipError_t launch_reorder(const Plan &p, const Work &w, const tb_tree &out, hipS
 hipError_t launch_runs(const Plan &p, const Work &w, const tb_tree &out, hipStream_t s);
 size_t cell_lds_limit();
 bool reorder_finishes(int nl);
-hipError_t launch_cell_emit(const Plan &p, const Work &w, const tb_tree &out, hipStream_t s);
+hipError_t launch_cell_emit(const Plan &p, const Work &w, const tb_tree &out,
+                            int64_t *cell_offsets, hipStream_t s);
 size_t cell_emit_lds(int nl, int cell_tile);
 // tb_parents.hip
 hipError_t launch_parents(const Plan &p, const Work &w, int depth, const tb_tree &out,
