@@ -28,15 +28,33 @@ constexpr uint32_t kAutoBoxFlag = 0x10000u;
 
 // Most particles that are built in small cell tiles (make_plan).
 constexpr int64_t kSmallTileMaxN = 3 << 18;
+// Most particles that are sorted in tiles of 2048 and of 4096 keys (pick_shape).
+constexpr int64_t kShortTileMaxN = 1 << 17, kWideTileMaxN = 1 << 20;
 
 static int64_t max_cells(int64_t n, int32_t n_leaf) {
   if (n <= 0) return 0;
   return n + (int64_t)kMaxDepth * (n / ((int64_t)n_leaf + 1));
 }
 
-int make_plan(int64_t n, int32_t nsets, int32_t n_leaf, uint32_t flags, const SortConfig &sc,
-              Plan *p) {
+// Shape of the radix passes.  The default one is for many tiles; a build that has few
+// waits for one tile's chain of load, ranking and look-back a pass, which is shorter the
+// fewer keys a wave ranks.  us a build, n_leaf 16, tiles of 5632 / 4096 (1024 threads) /
+// 2048: Plummer 1000 88 / 84 / 80, 2^14 108 / 101 / 100, 2^16 129 / 122 / 121,
+// 2^17 144 / 137 / 138, 300007 179 / 172 / 177, 2^20 251 / 247 / 254 (2^21 with its box
+// 365 / 368); 256 sets of 300 146 / 139 / 134.  Batches with more particles keep the
+// default (1024 sets of 16384 1259 / 1281 / 1428).
+static SortConfig pick_shape(const SortConfig &sc, int64_t n, int32_t nsets) {
+  const SortConfig &d = kSortTable[0];
+  if (sc.bits != d.bits || sc.ipt != d.ipt || sc.threads != d.threads) return sc;
+  if (n <= kShortTileMaxN) return {8, 4, 512};
+  if (nsets == 1 && n <= kWideTileMaxN) return {8, 4, 1024};
+  return sc;
+}
+
+int make_plan(int64_t n, int32_t nsets, int32_t n_leaf, uint32_t flags,
+              const SortConfig &asked, Plan *p) {
   std::memset(p, 0, sizeof(*p));
+  const SortConfig sc = pick_shape(asked, n, nsets);
   p->n = n;
   p->n_leaf = n_leaf;
   p->flags = flags;

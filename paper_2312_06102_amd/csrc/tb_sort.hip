@@ -665,7 +665,7 @@ static hipError_t launch_low_t(const Plan &p, const Work &w, const tb_tree &out,
 
 #define TB_SORT_SHAPES(CASE)                                                        \
   CASE(8, 11, 512) CASE(8, 12, 512) CASE(8, 10, 512) CASE(8, 16, 256) CASE(9, 16, 256) \
-  CASE(8, 12, 256) CASE(8, 8, 512)
+  CASE(8, 12, 256) CASE(8, 8, 512) CASE(8, 4, 512) CASE(8, 4, 1024)
 
 hipError_t launch_sort_pass(const Plan &p, const Work &w, int pass, const tb_tree &out,
                             hipStream_t s) {
