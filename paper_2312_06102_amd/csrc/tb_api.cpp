@@ -352,10 +352,14 @@ static int build_impl(const float *pos, const float *mass, int64_t n, int32_t ns
   run("setup", [&] { return launch_setup(p, w, in, out->status, s); });
   if (in.auto_box) run("bbox", [&] { return launch_bbox(p, w, pos, s); });
   run("keygen", [&] { return launch_keygen(p, w, pos, mass, *out, s); });
-  run("hist_reduce", [&] { return launch_hist_reduce(p, w, s); });
-  run("sort_low", [&] { return launch_low_passes(p, w, *out, s); });
-  for (int pass = 0; pass < p.key_passes; ++pass)
-    run("sort_pass", [&] { return launch_sort_pass(p, w, pass, *out, s); });
+  if (one_tile(p)) {
+    run("sort_pass", [&] { return launch_sort_one(p, w, s); });
+  } else {
+    run("hist_reduce", [&] { return launch_hist_reduce(p, w, s); });
+    run("sort_low", [&] { return launch_low_passes(p, w, *out, s); });
+    for (int pass = 0; pass < p.key_passes; ++pass)
+      run("sort_pass", [&] { return launch_sort_pass(p, w, pass, *out, s); });
+  }
   run("reorder", [&] { return launch_reorder(p, w, *out, s); });
   run("runs", [&] { return launch_runs(p, w, *out, s); });
   run("cell_scan", [&] { return launch_cell_scan(p, w, *out, cell_offsets, s); });

@@ -1290,8 +1290,9 @@ hipError_t launch_reorder(const Plan &p, const Work &w, const tb_tree &out, hipS
 hipError_t launch_runs(const Plan &p, const Work &w, const tb_tree &out, hipStream_t s) {
   const ReorderArgs g = reorder_args(p, w, out);
   const int64_t most = p.n / (kRunCap + 1);
-  // too few particles for a run that long, or sorted by their whole keys
-  if (most == 0 || !reorder_finishes(p.n_leaf)) return hipSuccess;
+  // too few particles for a run that long, or sorted by their whole keys (or no run that
+  // long is left)
+  if (most == 0 || !reorder_finishes(p.n_leaf) || one_tile(p)) return hipSuccess;
   // small grids, which return at once in the common case that nothing is listed
   k_sort_runs<<<(unsigned)(most < 256 ? most : 256), kCellThreads, 0, s>>>(
       g, reinterpret_cast<int32_t *>(w.vals1), w.keys0, w.keys1);

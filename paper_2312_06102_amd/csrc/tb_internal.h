@@ -233,6 +233,9 @@ hipError_t launch_sort_pass(const Plan &p, const Work &w, int pass, const tb_tre
                             hipStream_t s);
 hipError_t launch_low_passes(const Plan &p, const Work &w, const tb_tree &out, hipStream_t s);
 bool sort_config_supported(const SortConfig &c);
+// Whether the sort is one launch of one workgroup.
+bool one_tile(const Plan &p);
+hipError_t launch_sort_one(const Plan &p, const Work &w, hipStream_t s);
 // tb_cells.hip
 hipError_t launch_cell_scan(const Plan &p, const Work &w, const tb_tree &out,
                             int64_t *cell_offsets, hipStream_t s);

@@ -51,3 +51,23 @@ def test_batches(total):
         o = oracle.build(pos[s], mass[s], 16)
         assert np.array_equal(perm[s] - int(off[b]), o["perm"]), b
         assert np.array_equal(keys[co[b]:co[b + 1]], o["cell_key"]), b
+
+
+@pytest.mark.parametrize("n_leaf", [1, 16, 200])
+@pytest.mark.parametrize("n", [1, 2, 33, 64, 1023, 1024, 1025, 2048, 2049, 4095, 4096, 4097,
+                               8191, 8192, 8193])
+def test_one_workgroup(n, n_leaf):
+    pos, mass = dg.clustered(n, seed=n, n_halos=3)
+    compare_structure(gpu_build(pos, mass, n_leaf, BOX), oracle.build(pos, mass, n_leaf))
+
+
+@pytest.mark.parametrize("run", [32, 33, 34, 1000])
+def test_one_workgroup_runs(run):
+    """Runs that agree in the upper 32 key bits: the longest that the reorder finishes, and
+    longer ones, among spread particles."""
+    rng = np.random.default_rng(run)
+    near = 0.5 + 2.0 ** -13 * rng.random((run, 3))
+    pos = np.concatenate([rng.random((1500, 3)) * 0.4, near]).astype(np.float32)
+    pos = pos[rng.permutation(len(pos))]
+    mass = np.ones(len(pos), np.float32)
+    compare_structure(gpu_build(pos, mass, 8, BOX), oracle.build(pos, mass, 8))
