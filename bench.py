@@ -159,7 +159,9 @@ def _short_kernel(name: str) -> str:
     return n.replace("tb::", "").strip()
 
 
-STAGE_OF = [("k_onesweep", "sort_pass"), ("k_tile_count", "sort_pass"),
+STAGE_OF = [("k_onesweep", "sort_pass"), ("k_sort_one", "sort_pass"), ("k_sort_runs", "runs"),
+            ("k_reorder_again", "runs"), ("k_low_counts", "hist_reduce"),
+            ("k_tile_parents", "parents"), ("k_group_parents", "parents"), ("k_tile_count", "sort_pass"),
             ("k_tile_scan", "sort_pass"), ("k_keygen", "keygen"), ("k_hist_reduce", "hist_reduce"),
             ("k_set_base", "hist_reduce"), ("k_set_sums", "cell_scan"),
             ("k_reorder", "reorder"), ("k_cell_emit", "cell_emit"), ("k_cell_scan", "cell_scan"),
@@ -169,6 +171,9 @@ STAGE_OF = [("k_onesweep", "sort_pass"), ("k_tile_count", "sort_pass"),
 
 
 def _stage(kernel: str):
+    # the conditional passes read and write 64-bit keys (element format 2)
+    if kernel.startswith("k_onesweep<") and kernel.split(", ")[3:5] == ["2", "2"]:
+        return "sort_low"
     for prefix, st in STAGE_OF:
         if kernel.startswith(prefix):
             return st
@@ -428,7 +433,8 @@ def kernel_bytes(n: int, cells: int, leaves: int, key_passes: int, precision: st
     compulsory traffic), per build.
 
     keygen      read pos 12 + mass 4; write key 8 + packed (x, y, z, m) record 16
-    sort_pass   per pass, what its element format moves in and out (sort_forms):
+    sort_pass   of a sort by all 63 bits (upper_sort_bytes: of the passes that run);
+                per pass, what its element format moves in and out (sort_forms):
                 key 8 + index 4 while the key is 64-bit (pass 0 reads the key alone:
                 its index is the position), then one packed word of 8 or 4 bytes;
                 the last pass writes the index alone, 4
@@ -437,9 +443,8 @@ def kernel_bytes(n: int, cells: int, leaves: int, key_passes: int, precision: st
     reorder     read perm 4 + gathered record 16; write the record in key order 16, its
                 key 8 and its (a_i, D_i) 2
     cell_emit   read sorted keys 8 + sorted records 16 + (a_i, D_i) 2 per particle; write
-                key 8, depth 1, first 4, child link 8, head_parent 4 per cell, count 4 +
-                moments per leaf
-    parents     per child cell read key 8 + count 4 + moments; per parent read head 4,
+                key 8, depth 1, first 4, child link 8 per cell, count 4 + moments per leaf
+    parents     per child cell read key 8 + count 4 + moments; per parent read its link 4,
                 write count 4 + child count 4 + moments
     (with TB_SUBTREES, in place of cell_emit and parents:)
     blocks      read sorted keys 8; write the block-start byte 1
@@ -460,7 +465,7 @@ def kernel_bytes(n: int, cells: int, leaves: int, key_passes: int, precision: st
         "keygen": 40 * n,
         "sort_pass": sort,
         "reorder": 46 * n,
-        "cell_emit": 26 * n + 25 * cells + (4 + mom) * leaves,
+        "cell_emit": 26 * n + 21 * cells + (4 + mom) * leaves,
         "parents": (12 + mom) * max(cells - 1, 0) + (12 + mom) * inner,
         "blocks": 9 * n,
         "block_build": 25 * n + (25 + mom) * cells,
@@ -491,9 +496,25 @@ def sort_forms(n: int, bits: int, index_bits: int = 0) -> list:
     return forms
 
 
+def upper_sort_bytes(n: int, bits: int, passes: int, index_bits: int = 0) -> int:
+    """Bytes the `passes` radix passes over the upper key bits move, in the element formats
+    the library plans: the first reads the 64-bit key, 8 (the index is its position), and
+    packs the bits still to be sorted above the index (ib = bits(n - 1) bits, or a batch's
+    set-size bound, index_bits, when smaller) in a word of 8, of 4 once they fit; the last
+    writes the index alone, 4."""
+    ib = max(1, (n - 1).bit_length())
+    if 0 < index_bits < ib:
+        ib = index_bits
+    size = [8]
+    for k in range(1, passes):
+        size.append(4 if k > 1 and (passes - k) * bits + ib <= 32 else 8)
+    size.append(4)
+    return n * sum(a + b for a, b in zip(size, size[1:]))
+
+
 def method_bytes(n: int, cells: int, key_passes: int, precision: str) -> float:
-    """What the method must move per build (the whole-build algorithmic bytes):
-    keys 20 B, sort 8 + 24 P, gather 20, structure 8 + 25 c, moments 2 x 80 c
+    """What the method must move per build (the whole-build algorithmic bytes), with the
+    P radix passes that run (those over the upper key bits): keys 20 B, sort 8 + 24 P, gather 20, structure 8 + 25 c, moments 2 x 80 c
     (FP64) or 2 x 40 c (mixed) per particle, with c = cells / N."""
     c = cells / max(n, 1)
     mom = 160 if precision == "fp64" else 80
@@ -639,9 +660,10 @@ def run_single(args, tb, dg, torch, np):
     res = b.result()
     cells = res["n_cells"]
     leaves = int((res["child_ptr"][:, 0] < 0).sum().item())
-    key_passes = (63 + tb.tb_sort_configs()[k][0] - 1) // tb.tb_sort_configs()[k][0]
     trace = traced_kernels(run, args.steps, tb)
+    key_passes = trace["sort_pass"][0] // args.steps
     alg = kernel_bytes(n, cells, leaves, key_passes, precision)
+    alg["sort_pass"] = upper_sort_bytes(n, tb.tb_sort_configs()[k][0], key_passes)
     total_method = method_bytes(n, cells, key_passes, precision)
     line = {
         "metric": METRIC, "value": n / sec, "unit": "particles/s", "n_gpus": 1,
@@ -734,9 +756,9 @@ def run_batched(args, tb, dg, torch, np):
     eager = lambda: bb.launch(pos, mass, off, boxes)
     sec_eager = time_steps(eager, args.steps, 1)
     trace = traced_kernels(eager, args.steps, tb)
-    bits = tb.tb_sort_configs()[k][0]
-    key_passes = (63 + bits - 1) // bits
+    key_passes = trace["sort_pass"][0] // args.steps
     alg = kernel_bytes(n, cells, leaves, key_passes, precision, set_bits)
+    alg["sort_pass"] = upper_sort_bytes(n, tb.tb_sort_configs()[k][0], key_passes, set_bits)
     total_method = method_bytes(n, cells, key_passes, precision)
     line = {
         "metric": METRIC, "value": n / sec, "unit": "particles/s", "n_gpus": 1,

@@ -314,8 +314,7 @@ int tb_build_batched_sync(const float *pos, const float *mass, int64_t n_total, 
  *   stats       [2] int64, DEVICE, or NULL: number of groups, and number of
  *               interactions (cell terms plus particle pairs) over all particles
  *   workspace   DEVICE, at least tb_gravity_workspace_bytes(c_max) bytes
- * Asynchronous on `stream`.  A group whose walk outgrows the kernel's 4096-cell
- * LDS stack sets TB_STATUS_INTERNAL in tree->status.
+ * Asynchronous on `stream`.
  * Errors (synchronous): TB_ERR_ARG, TB_ERR_WORKSPACE, TB_ERR_HIP. */
 #define TB_GRAV_QUADRUPOLE 1u
 

@@ -107,12 +107,11 @@ int make_plan(int64_t n, int32_t nsets, int32_t n_leaf, uint32_t flags,
   // The passes of a single set with at least kCountedMinTiles tiles count their
   // tiles' digits first (reduce, then scan) instead of chaining the tiles
   // through the look-back.  The count reads one digit byte an element, which the
-  // previous pass (or the key kernel) leaves behind: at N = 2^24 the sort takes
-  // 779 us counted against 865 us with look-back, at 2^26 2.99 ms against
-  // 3.25 ms; a whole build at 2^22 (745 tiles) 0.636 against 0.649 ms.  Smaller
-  // grids look back: a counted pass is three launches where a look-back pass is
-  // one (2^21, 373 tiles: 0.443 against 0.419 ms).  A batch looks back too (its
-  // 31,180 set-aligned tiles: 7.0 ms against 8.7 ms counted).  TB_SORT_COUNTED
+  // previous pass (or the key kernel) leaves behind.  us a build with look-back / counted:
+  // 2^22 (745 tiles) 529 / 520, 2^24 1493 / 1458, 2^26 5669 / 5448.  Smaller grids look
+  // back: a counted pass is three launches where a look-back pass is one (2^20 in 256
+  // tiles 249 / 257, 2^21 in 373 tiles 336 / 353).  A batch looks back too (its 31,180
+  // set-aligned tiles, sorted by all 63 bits: 7.0 ms against 8.7 ms counted).  TB_SORT_COUNTED
   // counts every pass of any build, a batch's too (there a tile's offsets start
   // again at its set's first tile); TB_SORT_LOOKBACK looks back everywhere.
   p->counted = 0;
@@ -123,8 +122,8 @@ int make_plan(int64_t n, int32_t nsets, int32_t n_leaf, uint32_t flags,
   // Cell tiles of 2048 particles, eight a thread, or of 512, two a thread, where 2048
   // would leave most of the chip idle: a workgroup's chain of loads, counts and writes is
   // what such a build waits for.  us a Plummer build, n_leaf 16, in tiles of 2048 /
-  // of 512: 2^14 164 / 129, 2^16 170 / 151, 2^18 215 / 179, 2^19 234 / 208, 2^20 273 / 276,
-  // 2^21 364 / 366.
+  // of 512: 2^14 129 / 99, 2^16 138 / 123, 2^18 187 / 158, 2^19 211 / 184, 2^20 250 / 253,
+  // 2^21 337 / 341.
   p->cell_tile = (flags & TB_SUBTREES) || n > kSmallTileMaxN ? kCellTile : kSmallTile;
   p->cell_tiles = (n + p->cell_tile - 1) / p->cell_tile + nsets;
   // the auto box works chunk by chunk of one set: about four workgroups a CU (2^21

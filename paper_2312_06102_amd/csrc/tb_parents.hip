@@ -757,12 +757,14 @@ static hipError_t owned_parents_t(const Plan &p, const Work &w, const tb_tree &o
 
 // Whether the parents are built tile by tile or one launch a depth.  A wave goes through
 // its tile's cells one after the other, so where leaves are so small that a tile has
-// thousands, few tiles take longer than 21 launches.  us a build, by depth / by tile:
-// n_leaf 1, 65536 particles 252 / 374, 2^21 680 / 770, 2^24 4000 / 3840; n_leaf 4 234 /
-// 219 (clustered 238 / 254), 493 / 450, 2375 / 2119; n_leaf 8 229 / 187, 445 / 385,
-// 1991 / 1707 (the sort's gain included).
+// thousands, that takes longer than 21 launches; tiles of 512 have fewer.  us a build, by
+// depth / by tile, Plummer (clustered): tiles of 512, n_leaf 1, 4096 particles 123 / 123
+// (127 / 142), 65536 174 / 178 (177 / 197); n_leaf 4 116 / 84 (117 / 93), 159 / 135
+// (164 / 141).  Tiles of 2048, n_leaf 1, 2^21 615 / 728, 2^24 3687 / 3704; n_leaf 4
+// 413 / 418, 1922 / 1944; n_leaf 6 390 / 376, 1719 / 1719; n_leaf 16 358 / 339,
+// 1470 / 1458.
 bool owned_parents(const Plan &p) {
-  return p.n_leaf >= 6 || p.n * p.n_leaf >= (int64_t{1} << 23);
+  return p.n_leaf >= (p.cell_tile == kSmallTile ? 4 : 6);
 }
 
 hipError_t launch_owned_parents(const Plan &p, const Work &w, const tb_tree &out, hipStream_t s) {

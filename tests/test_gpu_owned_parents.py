@@ -34,11 +34,17 @@ def test_edges_of_tiles_and_groups(n):
     check(pos, mass, 16)
 
 
-@pytest.mark.parametrize("n_leaf", [1, 5, 6, 7, 95, 96])
+@pytest.mark.parametrize("n_leaf", [1, 3, 4, 5, 6, 7, 95, 96])
 @pytest.mark.parametrize("precision", ["fp64", "mixed"])
 def test_both_paths(n_leaf, precision):
     pos, mass = dg.clustered(70_001, seed=n_leaf, n_halos=50, masses="lognormal")
     check(pos, mass, n_leaf, precision)
+
+
+@pytest.mark.parametrize("n_leaf", [5, 6])
+def test_both_paths_large_tiles(n_leaf):
+    pos, mass = dg.clustered(3 * 2 ** 18 + 1, seed=n_leaf, n_halos=50, masses="lognormal")
+    check(pos, mass, n_leaf)
 
 
 def test_chains_of_single_children():
