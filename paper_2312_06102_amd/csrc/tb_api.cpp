@@ -29,7 +29,8 @@ constexpr uint32_t kAutoBoxFlag = 0x10000u;
 // Most particles that are built in small cell tiles (make_plan).
 constexpr int64_t kSmallTileMaxN = 3 << 18;
 // Most particles that are sorted in tiles of 2048 and of 4096 keys (pick_shape).
-constexpr int64_t kShortTileMaxN = 1 << 17, kWideTileMaxN = 1 << 20;
+constexpr int64_t kShortTileMaxN = 1 << 17, kShortTileSetsMaxN = 1 << 19;
+constexpr int64_t kWideTileMaxN = 1 << 20;
 
 static int64_t max_cells(int64_t n, int32_t n_leaf) {
   if (n <= 0) return 0;
@@ -38,16 +39,19 @@ static int64_t max_cells(int64_t n, int32_t n_leaf) {
 
 // Shape of the radix passes.  The default one is for many tiles; a build that has few
 // waits for one tile's chain of load, ranking and look-back a pass, which is shorter the
-// fewer keys a wave ranks.  us a build, n_leaf 16, tiles of 5632 / 4096 (1024 threads) /
-// 2048: Plummer 1000 88 / 84 / 80, 2^14 108 / 101 / 100, 2^16 129 / 122 / 121,
-// 2^17 144 / 137 / 138, 300007 179 / 172 / 177, 2^20 251 / 247 / 254 (2^21 with its box
-// 365 / 368); 256 sets of 300 146 / 139 / 134.  Batches with more particles keep the
-// default (1024 sets of 16384 1259 / 1281 / 1428).
+// fewer keys a wave ranks; sets smaller than a tile leave most of it empty.  us a build,
+// n_leaf 16, tiles of 5632 / 4096 (1024 threads) / 2048: Plummer 1000 88 / 84 / 80,
+// 2^14 108 / 101 / 100, 2^16 129 / 122 / 121, 2^17 144 / 137 / 138, 300007 179 / 172 / 177,
+// 2^20 251 / 247 / 254 (2^21 with its box 365 / 368).  Sets x particles: 300 x 300
+// 150 / 144 / 138, 300 x 1057 192 / 184 / 180, 64 x 4096 143 / 135 / 136, 1024 x 1000
+// 284 / 276 / 276, 16 x 65536 230 / 225 / 240, 300 x 4096 263 / 256 / 272, 4096 x 1000
+// 749 / 756 / 800, 1024 x 16384 1259 / 1281 / 1428.
 static SortConfig pick_shape(const SortConfig &sc, int64_t n, int32_t nsets) {
   const SortConfig &d = kSortTable[0];
   if (sc.bits != d.bits || sc.ipt != d.ipt || sc.threads != d.threads) return sc;
-  if (n <= kShortTileMaxN) return {8, 4, 512};
-  if (nsets == 1 && n <= kWideTileMaxN) return {8, 4, 1024};
+  const int64_t mean = n / (nsets > 0 ? nsets : 1);
+  if (n <= kShortTileMaxN || (mean <= 2048 && n <= kShortTileSetsMaxN)) return {8, 4, 512};
+  if (n <= kWideTileMaxN) return {8, 4, 1024};
   return sc;
 }
 

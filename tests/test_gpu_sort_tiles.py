@@ -34,9 +34,11 @@ def test_every_key_bit(n, n_leaf):
     compare_structure(gpu_build(pos, mass, n_leaf, BOX), oracle.build(pos, mass, n_leaf))
 
 
-@pytest.mark.parametrize("total", [2 ** 17, 2 ** 17 + 7])
-def test_batches(total):
-    sizes = np.array([2048, 1, 2049, 0, 5632, 40_000], np.int64)
+@pytest.mark.parametrize("total,small", [(2 ** 17, 0), (2 ** 17 + 7, 0), (2 ** 19, 400),
+                                         (2 ** 19 + 1, 400), (2 ** 20 + 1, 0)])
+def test_batches(total, small):
+    """(small: sets of a few particles, which lower the mean size of a set)"""
+    sizes = np.array([2048, 1, 2049, 0, 4097, 5632, 40_000] + [3] * small, np.int64)
     sizes = np.append(sizes, total - sizes.sum())
     pos, mass, off = dg.batched_plummer(sizes, seed=3)
     boxes = torch.tensor([[0.0, 0.0, 0.0, 1.0]] * len(sizes), dtype=torch.float64, device="cuda")
