@@ -170,7 +170,8 @@ int make_plan(int64_t n, int32_t nsets, int32_t n_leaf, uint32_t flags,
   p->set_tot = take(4 * (size_t)nsets * kLevels);
   p->set_cells = take(8 * B1);
   p->lvl_off = take(8 * (size_t)nsets * (kLevels + 1));
-  p->set_wg = take(8 * (size_t)((nsets + 255) / 256) * kLevels);
+  const int scan_sets = nsets <= kFewSets ? 64 : 256;
+  p->set_wg = take(8 * (size_t)((nsets + scan_sets - 1) / scan_sets) * kLevels);
   p->par_start = take(8 * (size_t)kLevels * B1);
   p->seg_tile_start = take(p->seg ? 8 * B1 : 0);
   p->seg_tile_set = take(p->seg ? 4 * (size_t)p->sort_tiles : 0);

@@ -732,18 +732,20 @@ __global__ __launch_bounds__(64) void k_set_scan_wave(
                     n_cells, par_start);
 }
 
-// More sets: kSetScanThreads sets per workgroup over G workgroups, in two
-// launches.  k_set_sums writes the row sums of each workgroup's sets,
-// wg_sum[g][r]; k_set_scan_wg adds the sums of the earlier workgroups to its own
-// block scan.
-constexpr int kSetScanThreads = 256;
-
-__global__ __launch_bounds__(kSetScanThreads) void k_set_sums(
+// More sets: THREADS sets per workgroup over G workgroups, in two launches.
+// k_set_sums writes the row sums of each workgroup's sets, wg_sum[g][r];
+// k_set_scan_wg adds the sums of the earlier workgroups to its own block scan.
+// A set's row is read and written by one thread, some 70 scattered words, so a few
+// sets are spread over more CUs: 64 a workgroup up to kFewSets (300 sets: 9.2 us in 2
+// workgroups, 7.0 us in 5), but 256 beyond, where each workgroup's sum over the
+// earlier ones would be long.
+template <int THREADS>
+__global__ __launch_bounds__(THREADS) void k_set_sums(
     const uint32_t *__restrict__ set_tot, int32_t nsets, int64_t *__restrict__ wg_sum) {
-  constexpr int W = kSetScanThreads / 64;
+  constexpr int W = THREADS / 64;
   __shared__ uint32_t s_w[kLevels][W];
   uint32_t t[kLevels], v[kLevels];
-  set_rows(set_tot, nsets, blockIdx.x * kSetScanThreads + threadIdx.x, t, v);
+  set_rows(set_tot, nsets, blockIdx.x * THREADS + threadIdx.x, t, v);
 #pragma unroll
   for (int r = 0; r < kLevels; ++r) {
     const uint32_t inc = wave_inclusive_scan(v[r]);
@@ -757,13 +759,14 @@ __global__ __launch_bounds__(kSetScanThreads) void k_set_sums(
   }
 }
 
-__global__ __launch_bounds__(kSetScanThreads) void k_set_scan_wg(
+template <int THREADS>
+__global__ __launch_bounds__(THREADS) void k_set_scan_wg(
     const uint32_t *__restrict__ set_tot, int32_t nsets, const int64_t *__restrict__ wg_sum,
     int64_t *__restrict__ set_cells, int64_t *__restrict__ lvl_off,
     int64_t *__restrict__ level_offset, int64_t *__restrict__ cell_offsets,
     int64_t *__restrict__ n_cells, int64_t *__restrict__ par_start,
     const double *__restrict__ box, double *__restrict__ box_out) {
-  constexpr int W = kSetScanThreads / 64;
+  constexpr int W = THREADS / 64;
   __shared__ uint32_t s_w[kLevels][W];
   __shared__ int64_t s_carry[kLevels];
   if (threadIdx.x < kLevels) {
@@ -772,7 +775,7 @@ __global__ __launch_bounds__(kSetScanThreads) void k_set_scan_wg(
     s_carry[threadIdx.x] = c;
   }
   __syncthreads();
-  set_scan_block<kSetScanThreads>(blockIdx.x * kSetScanThreads, set_tot, nsets, set_cells,
+  set_scan_block<THREADS>(blockIdx.x * THREADS, set_tot, nsets, set_cells,
                                   lvl_off, level_offset, cell_offsets, par_start, box, box_out,
                                   s_w, s_carry);
   __syncthreads();
@@ -1231,11 +1234,11 @@ hipError_t launch_cell_scan(const Plan &p, const Work &w, const tb_tree &out,
     k_set_scan_wave<<<1, 64, 0, s>>>(w.set_tot, p.nsets, w.set_cells, w.lvl_off, out.level_offset,
                                      cell_offsets, out.n_cells, w.par_start, w.box, out.box_out);
   } else {
-    const int g = (p.nsets + kSetScanThreads - 1) / kSetScanThreads;
-    k_set_sums<<<g, kSetScanThreads, 0, s>>>(w.set_tot, p.nsets, w.set_wg);
-    k_set_scan_wg<<<g, kSetScanThreads, 0, s>>>(w.set_tot, p.nsets, w.set_wg, w.set_cells,
-                                                w.lvl_off, out.level_offset, cell_offsets,
-                                                out.n_cells, w.par_start, w.box, out.box_out);
+    const int t = p.nsets <= kFewSets ? 64 : 256, g = (p.nsets + t - 1) / t;
+    (t == 64 ? k_set_sums<64> : k_set_sums<256>)<<<g, t, 0, s>>>(w.set_tot, p.nsets, w.set_wg);
+    (t == 64 ? k_set_scan_wg<64> : k_set_scan_wg<256>)<<<g, t, 0, s>>>(
+        w.set_tot, p.nsets, w.set_wg, w.set_cells, w.lvl_off, out.level_offset, cell_offsets,
+        out.n_cells, w.par_start, w.box, out.box_out);
   }
   return hipGetLastError();
 }

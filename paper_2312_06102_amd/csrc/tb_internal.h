@@ -34,10 +34,12 @@ constexpr int kSmallIpt = 2;
 constexpr int kSmallTile = kCellThreads * kSmallIpt;  // 512 particles
 
 
-// The chip's eight XCDs each have their own L2, and workgroups of a launch are
-// dispatched to them in turn (workgroup b to XCD b mod 8).
 // Smallest radix grid whose passes count their tiles rather than look back.
 constexpr int64_t kCountedMinTiles = 512;
+// Most sets whose scan takes workgroups of 64.
+constexpr int32_t kFewSets = 1024;
+// The chip's eight XCDs each have their own L2, and workgroups of a launch are
+// dispatched to them in turn (workgroup b to XCD b mod 8).
 constexpr uint32_t kXcds = 8;
 
 // Parent kernel: children staged per workgroup step.
@@ -147,7 +149,7 @@ struct Plan {
   size_t set_tot;       // u32 [B][kLevels] cells of each set and depth
   size_t set_cells;     // i64 [B + 1] first cell of each set; [B] = all cells
   size_t lvl_off;       // i64 [B][kLevels + 1] first cell of each depth of each set
-  size_t set_wg;        // i64 [ceil(B / 256)][kLevels] row sums of each set-scan workgroup
+  size_t set_wg;        // i64 [ceil(B / 64 or 256)][kLevels] row sums of each set-scan workgroup
   size_t par_start;     // i64 [kLevels][B + 1] parent-pass chunks per depth and set
   size_t seg_tile_start;  // i64 [B + 1] first radix tile of each set (seg)
   size_t seg_tile_set;    // i32 [sort_tiles] set of each radix tile (seg)
