@@ -440,8 +440,8 @@ def kernel_bytes(n: int, cells: int, leaves: int, key_passes: int, precision: st
                 the last pass writes the index alone, 4
                 (counted passes also read their elements a second time to count
                 their tiles' digits, not counted here)
-    reorder     read perm 4 + gathered record 16; write the record in key order 16, its
-                key 8 and its (a_i, D_i) 2
+    reorder     read the passes' index 4 + gathered record 16; write the record in key
+                order 16, its key 8, perm 4 and its (a_i, D_i) 2
     cell_emit   read sorted keys 8 + sorted records 16 + (a_i, D_i) 2 per particle; write
                 key 8, depth 1, first 4, child link 8 per cell, count 4 + moments per leaf
     parents     per child cell read key 8 + count 4 + moments; per parent read its link 4,
@@ -464,7 +464,7 @@ def kernel_bytes(n: int, cells: int, leaves: int, key_passes: int, precision: st
     return {
         "keygen": 40 * n,
         "sort_pass": sort,
-        "reorder": 46 * n,
+        "reorder": 50 * n,
         "cell_emit": 26 * n + 21 * cells + (4 + mom) * leaves,
         "parents": (12 + mom) * max(cells - 1, 0) + (12 + mom) * inner,
         "blocks": 9 * n,
