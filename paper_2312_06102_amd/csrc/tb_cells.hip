@@ -23,7 +23,8 @@
 //                the keys of its tile plus an n_leaf halo, a_i and D_i of every
 //                particle and the tile's per-depth cell counts;
 // k_cell_scan  : per-depth prefix over the tiles of each set;
-// k_set_scan_* : first cell of every set and depth;
+// k_set_scan_* : first cell of every set and depth (one set of few tiles: both in
+//                k_cell_emit);
 // k_cell_emit  : writes key, depth, first particle and first-child slot of
 //                every cell, and count plus moments of every leaf.
 // (With TB_SUBTREES the cells are written block by block instead:

@@ -21,7 +21,7 @@
 // writes perm.  Passes over the low bits come first when the key kernel's sample has
 // found that the keys crowd; they are launched in any case and return at once if not.
 //
-// By default the passes of a single set are "counted" instead (reduce, then
+// By default the passes of a large single set are "counted" instead (reduce, then
 // scan; a batch with TB_SORT_COUNTED too): a first kernel reads each element's
 // digit (one byte, left behind by the previous pass or the key kernel) and
 // writes every tile's digit counts, a second turns them into exclusive
@@ -29,6 +29,9 @@
 // instead of waiting on its predecessors.  Reading that byte again costs less
 // than the look-back chain across the chip; TB_SORT_LOOKBACK keeps the
 // look-back.
+//
+// A single set of up to 8192 particles is sorted by one workgroup in one launch
+// (k_sort_one).
 //
 // A batch sorts every set in place: a set's tiles never straddle it, its tiles'
 // look-back chain starts at its own first tile, and its digit runs start at
