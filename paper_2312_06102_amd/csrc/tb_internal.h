@@ -252,6 +252,7 @@ size_t cell_emit_lds(int nl, int cell_tile);
 hipError_t launch_parents(const Plan &p, const Work &w, int depth, const tb_tree &out,
                           hipStream_t s);
 bool owned_parents(const Plan &p);
+int group_levels(const Plan &p);
 hipError_t launch_owned_parents(const Plan &p, const Work &w, const tb_tree &out, hipStream_t s);
 // tb_blocks.hip
 hipError_t launch_blocks(const Plan &p, const Work &w, hipStream_t s);

@@ -724,6 +724,22 @@ __global__ __launch_bounds__(kGroupThreads) void k_group_parents(
   if (threadIdx.x < kMaxDepth) left2[threadIdx.x * groups + blockIdx.x] = s_left[threadIdx.x];
 }
 
+// Launches of k_group_parents, each with units of kGroupUnits times the tiles.  Tiles are
+// numbered through all sets, so a set of a batch may lie over the end of any unit, however
+// few particles it has: a batch goes on until one unit holds every tile (none if every
+// set is one tile: n at most a tile's).  A single set's units start where it does, so it
+// stops at the unit that reaches its n particles, without the tile the plan has to spare.
+int group_levels(const Plan &p) {
+  int levels = 0;
+  int64_t units = p.cell_tiles, unit = 1;
+  while (p.nsets > 1 ? p.n > p.cell_tile && units > 1 : unit * p.cell_tile < p.n) {
+    units = (units + kGroupUnits - 1) / kGroupUnits;
+    unit *= kGroupUnits;
+    ++levels;
+  }
+  return levels;
+}
+
 template <bool MIXED>
 static hipError_t owned_parents_t(const Plan &p, const Work &w, const tb_tree &out,
                                   hipStream_t s) {
@@ -739,10 +755,8 @@ static hipError_t owned_parents_t(const Plan &p, const Work &w, const tb_tree &o
   k_tile_parents<MIXED><<<(unsigned)((p.cell_tiles + W - 1) / W), kParentThreads, 0, s>>>(
       g, keys, w.cell_excl, p.cell_tiles, w.tile_start, w.tile_set, w.set_off, p.nsets, p.cell_tile,
       w.lvl_off, w.box, out.n_cells, reinterpret_cast<int32_t *>(w.cell_cnt));
-  // every set is one tile, or units of more and more tiles until one holds them all
-  // (a batch's largest set may have all but one of the particles)
   int64_t units = p.cell_tiles, unit = 1;
-  for (int level = 0; unit * p.cell_tile < p.n; ++level) {
+  for (int level = 0, levels = group_levels(p); level < levels; ++level) {
     const int64_t groups = (units + kGroupUnits - 1) / kGroupUnits;
     k_group_parents<MIXED><<<(unsigned)groups, kGroupThreads, 0, s>>>(
         g, keys, unit, w.tile_start, w.tile_set, w.set_off, p.nsets, p.cell_tile, w.box,
@@ -750,7 +764,6 @@ static hipError_t owned_parents_t(const Plan &p, const Work &w, const tb_tree &o
     left = space[level % 2];
     units = groups;
     unit *= kGroupUnits;
-    if (units == 1) break;
   }
   return hipGetLastError();
 }

@@ -1,0 +1,26 @@
+// plan_driver.cpp -- prints the plans of the library it is linked to, for the CPU tests.
+// A line "n nsets n_leaf flags" of the input gives one of the output: the fields of the
+// plan as "name value" pairs.  No GPU is touched.
+#include <cstdio>
+#include <cstdlib>
+
+#include "tb_internal.h"
+
+int main() {
+  int32_t shapes[3 * 64];
+  int count = 0;
+  if (tb_sort_configs(shapes, 64, &count) != TB_OK) return 1;
+  long long n, nsets, n_leaf;
+  unsigned long flags;
+  while (std::scanf("%lld %lld %lld %lu", &n, &nsets, &n_leaf, &flags) == 4) {
+    const int k = (int)((flags >> 8) & 0xffu);
+    if (k >= count) return 1;
+    const tb::SortConfig asked = {shapes[3 * k], shapes[3 * k + 1], shapes[3 * k + 2]};
+    tb::Plan p;
+    if (tb::make_plan(n, (int32_t)nsets, (int32_t)n_leaf, (uint32_t)flags, asked, &p) != TB_OK)
+      return 1;
+    std::printf("cell_tile %d cell_tiles %lld group_levels %d\n", p.cell_tile,
+                (long long)p.cell_tiles, tb::group_levels(p));
+  }
+  return 0;
+}

@@ -1,0 +1,68 @@
+"""The host's plan of a build, read from the built library by a small driver
+(tests/plan/plan_driver.cpp), against rules restated here.  CPU only."""
+import os
+import subprocess
+
+import numpy as np
+import pytest
+
+from paper_2312_06102_amd import build_lib
+from paper_2312_06102_amd import treebuild as tb
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+
+
+@pytest.fixture(scope="module")
+def plans(tmp_path_factory):
+    """plans([(n, nsets, n_leaf, flags), ...]) -> a dict of numbers each."""
+    exe = str(tmp_path_factory.mktemp("plan") / "plan_driver")
+    lib_dir = os.path.dirname(tb.LIB_PATH)
+    cmd = [build_lib.HIPCC, f"--offload-arch={build_lib.ARCH}", "-O1", "-std=c++17", "-x", "hip",
+           "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+           f"-I{build_lib.INCLUDE}", f"-I{build_lib.CSRC}",
+           os.path.join(HERE, "plan", "plan_driver.cpp"), f"-L{lib_dir}", "-ltreebuild",
+           f"-Wl,-rpath,{lib_dir}", "-o", exe]
+    subprocess.run(cmd, check=True, capture_output=True, text=True, timeout=300)
+
+    def ask(rows):
+        text = "\n".join(" ".join(str(int(v)) for v in r) for r in rows)
+        r = subprocess.run([exe], input=text, check=True, capture_output=True, text=True,
+                           timeout=300)
+        out = []
+        for line in r.stdout.splitlines():
+            w = line.split()
+            out.append({k: int(v) for k, v in zip(w[::2], w[1::2])})
+        assert len(out) == len(rows)
+        return out
+    return ask
+
+
+def _unfinished(sizes, cell_tile, levels):
+    """Whether some set lies over the end of a unit after `levels` rounds of 32 units to
+    one: its root has then been built by nobody."""
+    tiles = (sizes + cell_tile - 1) // cell_tile
+    end = np.cumsum(tiles)
+    first, last = (end - tiles)[sizes > 0], (end - 1)[sizes > 0]
+    unit = 32 ** levels
+    return bool(np.any(first // unit != last // unit))
+
+
+def test_parents_of_every_set_are_reached(plans):
+    """Groups of 32 tiles, then of 32 groups, go on until no set is left over a group's
+    end.  Tiles are numbered through all sets, so a small set may lie over any end."""
+    rng = np.random.default_rng(31)
+    layouts = [[10] * 31 + [1000], [10] * 1023 + [1000, 40], [100] * 1023 + [30_000, 40],
+               [500] * 1020 + [400_000, 7], [1] * 16_383, [513], [16_384], [16_385], [600, 5]]
+    for _ in range(3000):
+        nsets = int(np.exp(rng.uniform(0, np.log(3000))))
+        lo = int(np.exp(rng.uniform(np.log(2), np.log(2000))))
+        hi = lo * int(rng.choice([2, 16, 128]))
+        sizes = np.exp(rng.uniform(np.log(lo), np.log(hi), nsets)).astype(np.int64)
+        sizes[rng.random(nsets) < 0.05] = 0
+        if sizes.sum() > 0:
+            layouts.append(sizes)
+    layouts = [np.asarray(s, np.int64) for s in layouts]
+    got = plans([(s.sum(), s.size, 16, 0) for s in layouts])
+    bad = [(s.size, int(s.sum())) for s, p in zip(layouts, got)
+           if _unfinished(s, p["cell_tile"], p["group_levels"])]
+    assert not bad, (len(bad), bad[:5])
