@@ -304,7 +304,8 @@ int tb_build_batched_sync(const float *pos, const float *mass, int64_t n_total, 
  *               order (tb_build's pos_sorted / mass_sorted outputs)
  *   tree        host pointer to the tb_tree of that build (TB_FP64 moments);
  *               box_out must have been filled; n_cells is read on the device
- *   c_max       tb_max_cells() of that build (bounds the cells examined)
+ *   c_max       tb_max_cells() of that build, or any bound of its number of cells;
+ *               below N large groups are not shared out over workgroups (slower)
  *   theta       opening angle (>= 0; 0 opens everything: direct summation)
  *   n_crit      group size (>= 1)
  *   eps         Plummer softening of the particle terms (>= 0)

@@ -93,12 +93,12 @@ __global__ void k_grav_init(uint32_t *__restrict__ counts, unsigned long long *_
   if (stats && threadIdx.x < 2) stats[threadIdx.x] = 0;
 }
 
-// A group of more than `part` particles is several items of work: its first slot
-// holds the cell, the k-th after it -k.
+// A group of more than `part` particles is several items of work (one, if the groups stay
+// whole): its first slot holds the cell, the k-th after it -k.
 __device__ __forceinline__ void list_group(int32_t *__restrict__ items,
                                            uint32_t *__restrict__ n_items, int32_t cell,
-                                           int32_t count, int32_t part) {
-  const uint32_t k = (uint32_t)((count + (int64_t)part - 1) / part);
+                                           int32_t count, int32_t part, int whole) {
+  const uint32_t k = whole ? 1u : (uint32_t)((count + (int64_t)part - 1) / part);
   const uint32_t at = atomicAdd(n_items, k);
   items[at] = cell;
   for (uint32_t q = 1; q < k; ++q) items[at + q] = -(int32_t)q;
@@ -106,19 +106,19 @@ __device__ __forceinline__ void list_group(int32_t *__restrict__ items,
 
 __global__ __launch_bounds__(256) void k_find_groups(
     const int64_t *__restrict__ n_cells, const int32_t *__restrict__ count,
-    const int32_t *__restrict__ child, int32_t n_crit, int32_t part, int32_t *__restrict__ items,
-    uint32_t *__restrict__ n_items) {
+    const int32_t *__restrict__ child, int32_t n_crit, int32_t part, int whole,
+    int32_t *__restrict__ items, uint32_t *__restrict__ n_items) {
   const int64_t C = *n_cells;
   for (int64_t c = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; c < C;
        c += (int64_t)gridDim.x * blockDim.x) {
     const bool leaf = child[2 * c] < 0;
-    if (c == 0 && (leaf || count[0] <= n_crit)) list_group(items, n_items, 0, count[0], part);
+    if (c == 0 && (leaf || count[0] <= n_crit)) list_group(items, n_items, 0, count[0], part, whole);
     if (leaf || count[c] <= n_crit) continue;
     const int32_t f = child[2 * c], nch = child[2 * c + 1];
     for (int k = 0; k < nch; ++k) {
       const int32_t ch = f + k;
       if (child[2 * ch] < 0 || count[ch] <= n_crit)
-        list_group(items, n_items, ch, count[ch], part);
+        list_group(items, n_items, ch, count[ch], part, whole);
     }
   }
 }
@@ -510,7 +510,9 @@ __device__ __forceinline__ void walk_pass(const GravArgs &g, WalkLds<T> &L, uint
 // them FP64), 90 % of the lanes in use.  2^21 Plummer particles, theta 0.75, n_crit
 // 512, 4.2e9 interactions: 8.0 ms (1.9e-12 s each) against 15.6 ms with one thread a
 // particle, a square root and a division; the traversal alone is 0.5 ms of it.
-template <int T, bool QUAD>
+// WHOLE: an item is a group, taken part by part (an instance of its own: the loop costs the
+// other 1 %).
+template <int T, bool QUAD, bool WHOLE>
 __global__ __launch_bounds__(T, kWalkWaves) void k_walk(GravArgs g, const int32_t *__restrict__ items,
                                                uint32_t *__restrict__ counts, int32_t part,
                                                double *__restrict__ acc,
@@ -535,35 +537,40 @@ __global__ __launch_bounds__(T, kWalkWaves) void k_walk(GravArgs g, const int32_
     const int32_t gf = uniform(g.first[grp]);
     const int32_t gn = uniform(g.count[grp]);
     const int32_t p0 = (int32_t)nth * part;  // below gn: the parts cover the group
-    const int P = min(part, gn - p0);
-    // particles per lane: the fewest idle lanes, then the fewest LDS reads
-    int best = -1, U = kWalkPpt;
-#pragma unroll
-    for (int u = kWalkPpt; u >= 1; --u) {
-      const int Q = (P + u - 1) / u;
-      if (Q > T) continue;
-      // lanes in use out of T * u, in 1/1024ths, less what a source's reads cost
-      const int used = max((P * (T / Q) * 1024) / (T * u) - kReadCost / u, 0);
-      if (used > best) {
-        best = used;
-        U = u;
-      }
-    }
     const int64_t f0 = (int64_t)gf + p0;
     int64_t cells = 0, pairs = 0;
-    switch (uniform(U)) {
-      case 1:
-        walk_pass<T, 1, QUAD>(g, L, gkey, gd, gc, gh, gf, gn, f0, P, acc, &cells, &pairs);
-        break;
-      case 2:
-        walk_pass<T, 2, QUAD>(g, L, gkey, gd, gc, gh, gf, gn, f0, P, acc, &cells, &pairs);
-        break;
-      case 3:
-        walk_pass<T, 3, QUAD>(g, L, gkey, gd, gc, gh, gf, gn, f0, P, acc, &cells, &pairs);
-        break;
-      default:
-        walk_pass<T, 4, QUAD>(g, L, gkey, gd, gc, gh, gf, gn, f0, P, acc, &cells, &pairs);
-        break;
+    // one part, or a whole group part by part
+    const int32_t todo = WHOLE ? gn : min(part, gn - p0);
+    for (int32_t done = 0;; done += part) {
+      const int P = min(part, todo - done);
+      // particles per lane: the fewest idle lanes, then the fewest LDS reads
+      int best = -1, U = kWalkPpt;
+#pragma unroll
+      for (int u = kWalkPpt; u >= 1; --u) {
+        const int Q = (P + u - 1) / u;
+        if (Q > T) continue;
+        // lanes in use out of T * u, in 1/1024ths, less what a source's reads cost
+        const int used = max((P * (T / Q) * 1024) / (T * u) - kReadCost / u, 0);
+        if (used > best) {
+          best = used;
+          U = u;
+        }
+      }
+      switch (uniform(U)) {
+        case 1:
+          walk_pass<T, 1, QUAD>(g, L, gkey, gd, gc, gh, gf, gn, f0 + done, P, acc, &cells, &pairs);
+          break;
+        case 2:
+          walk_pass<T, 2, QUAD>(g, L, gkey, gd, gc, gh, gf, gn, f0 + done, P, acc, &cells, &pairs);
+          break;
+        case 3:
+          walk_pass<T, 3, QUAD>(g, L, gkey, gd, gc, gh, gf, gn, f0 + done, P, acc, &cells, &pairs);
+          break;
+        default:
+          walk_pass<T, 4, QUAD>(g, L, gkey, gd, gc, gh, gf, gn, f0 + done, P, acc, &cells, &pairs);
+          break;
+      }
+      if (!WHOLE || todo - done <= part) break;
     }
     if (threadIdx.x == 0 && stats && nth == 0) {
       // every group particle meets every listed cell and every listed particle
@@ -584,22 +591,26 @@ size_t gravity_workspace_bytes(int64_t c_max) { return 4 * (size_t)c_max + 256; 
 // 32 / 64 / 128 / 256: 2^14 160 / 183 / 252 / 340, 2^16 423 / 408 / 467 / 692,
 // 1.3e5 528 / 475 / 483 / 563, 3e5 1215 / 1020 / 1004 / 1098, 2^21 10552 / 8765 /
 // 8062 / 8080.
-static int32_t walk_part(int64_t n) {
-  if (n < (int64_t{1} << 15)) return 32;
-  return n < (int64_t{1} << 18) ? 64 : 128;
+//
+// A list of parts has up to n entries, which the workspace holds if c_max is n or more, as
+// tb_max_cells() is.  With a smaller c_max, the number of cells of the tree say, there is
+// room for the groups alone: they stay whole, and a workgroup goes through one part by part.
+WalkItems walk_items(int64_t n, int64_t c_max) {
+  if (c_max < n) return {kWalkThreads * kWalkPpt, true};
+  if (n < (int64_t{1} << 15)) return {32, false};
+  return {n < (int64_t{1} << 18) ? 64 : 128, false};
 }
 
 // A grid that fills the chip takes the items in turn.
 template <int T>
 static void launch_walk(const GravArgs &g, const GravIn &in, const int32_t *items,
-                        uint32_t *counts, int32_t part, hipStream_t s) {
+                        uint32_t *counts, const WalkItems &it, hipStream_t s) {
   int64_t wg = 256 * kWalkWaves * 256 / T;
   if (wg > in.n) wg = in.n;  // an item holds at least one particle
   auto *stats = reinterpret_cast<unsigned long long *>(in.stats);
-  if (in.quadrupole)
-    k_walk<T, true><<<(unsigned)wg, T, 0, s>>>(g, items, counts, part, in.acc, stats);
-  else
-    k_walk<T, false><<<(unsigned)wg, T, 0, s>>>(g, items, counts, part, in.acc, stats);
+  auto k = in.quadrupole ? (it.whole ? k_walk<T, true, true> : k_walk<T, true, false>)
+                         : (it.whole ? k_walk<T, false, true> : k_walk<T, false, false>);
+  k<<<(unsigned)wg, T, 0, s>>>(g, items, counts, it.part, in.acc, stats);
 }
 
 hipError_t launch_gravity(const GravIn &in, hipStream_t s) {
@@ -616,16 +627,16 @@ hipError_t launch_gravity(const GravIn &in, hipStream_t s) {
   g.theta2 = in.theta * in.theta;
   g.eps2 = in.eps * in.eps;
   g.hilbert = in.hilbert ? 1 : 0;
-  int32_t *items = static_cast<int32_t *>(in.workspace);  // at most n <= c_max of them
+  int32_t *items = static_cast<int32_t *>(in.workspace);  // at most c_max of them
   uint32_t *counts = reinterpret_cast<uint32_t *>(items + in.c_max);
-  const int32_t part = walk_part(in.n);
-  static_assert(kWalkThreads * kWalkPpt >= 128, "an item fits one pass");
+  const WalkItems it = walk_items(in.n, in.c_max);
+  static_assert(kWalkThreads * kWalkPpt >= 128, "a part fits one pass");
   k_grav_init<<<1, 64, 0, s>>>(counts, reinterpret_cast<unsigned long long *>(in.stats));
   int64_t blocks = (in.c_max + 255) / 256;
   if (blocks > 4096) blocks = 4096;
   k_find_groups<<<(unsigned)blocks, 256, 0, s>>>(in.tree->n_cells, g.count, g.child, in.n_crit,
-                                                 part, items, counts);
-  launch_walk<kWalkThreads>(g, in, items, counts, part, s);
+                                                 it.part, it.whole, items, counts);
+  launch_walk<kWalkThreads>(g, in, items, counts, it, s);
   return hipGetLastError();
 }
 

@@ -272,9 +272,16 @@ struct GravIn {
   bool hilbert;             // the tree was built on Peano-Hilbert keys
   double *acc;              // [n][4] device: ax, ay, az, phi in key order
   int64_t *stats;           // [2] device or NULL: groups, interactions
-  void *workspace;          // int32 [c_max] groups + u32 counter
+  void *workspace;          // int32 [c_max] items of work + u32 counters
 };
 hipError_t launch_gravity(const GravIn &in, hipStream_t s);
+// The walk's items of work: parts of a group of at most `part` particles, or whole groups
+// taken in such parts.
+struct WalkItems {
+  int32_t part;
+  bool whole;
+};
+WalkItems walk_items(int64_t n, int64_t c_max);
 // tb_sim.hip
 hipError_t launch_kick_drift(const int32_t *perm, const double *acc, int64_t n, double dt_kick,
                              double dt_drift, float *pos, float *vel, int32_t *status,

@@ -1,12 +1,22 @@
 // plan_driver.cpp -- prints the plans of the library it is linked to, for the CPU tests.
 // A line "n nsets n_leaf flags" of the input gives one of the output: the fields of the
-// plan as "name value" pairs.  No GPU is touched.
+// plan as "name value" pairs.  With the argument "walk" a line "n c_max" gives the walk's
+// items of work.  No GPU is touched.
 #include <cstdio>
 #include <cstdlib>
+#include <cstring>
 
 #include "tb_internal.h"
 
-int main() {
+int main(int argc, char **argv) {
+  if (argc > 1 && std::strcmp(argv[1], "walk") == 0) {
+    long long n, c_max;
+    while (std::scanf("%lld %lld", &n, &c_max) == 2) {
+      const tb::WalkItems it = tb::walk_items(n, c_max);
+      std::printf("part %d whole %d\n", (int)it.part, it.whole ? 1 : 0);
+    }
+    return 0;
+  }
   int32_t shapes[3 * 64];
   int count = 0;
   if (tb_sort_configs(shapes, 64, &count) != TB_OK) return 1;

@@ -14,7 +14,8 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 
 @pytest.fixture(scope="module")
 def plans(tmp_path_factory):
-    """plans([(n, nsets, n_leaf, flags), ...]) -> a dict of numbers each."""
+    """plans([(n, nsets, n_leaf, flags), ...]) -> a dict of numbers each; with "walk",
+    [(n, c_max), ...]."""
     exe = str(tmp_path_factory.mktemp("plan") / "plan_driver")
     lib_dir = os.path.dirname(tb.LIB_PATH)
     cmd = [build_lib.HIPCC, f"--offload-arch={build_lib.ARCH}", "-O1", "-std=c++17", "-x", "hip",
@@ -24,9 +25,9 @@ def plans(tmp_path_factory):
            f"-Wl,-rpath,{lib_dir}", "-o", exe]
     subprocess.run(cmd, check=True, capture_output=True, text=True, timeout=300)
 
-    def ask(rows):
+    def ask(rows, *mode):
         text = "\n".join(" ".join(str(int(v)) for v in r) for r in rows)
-        r = subprocess.run([exe], input=text, check=True, capture_output=True, text=True,
+        r = subprocess.run([exe, *mode], input=text, check=True, capture_output=True, text=True,
                            timeout=300)
         out = []
         for line in r.stdout.splitlines():
@@ -66,3 +67,26 @@ def test_parents_of_every_set_are_reached(plans):
     bad = [(s.size, int(s.sum())) for s, p in zip(layouts, got)
            if _unfinished(s, p["cell_tile"], p["group_levels"])]
     assert not bad, (len(bad), bad[:5])
+
+
+def test_walk_lists_no_more_items_than_the_workspace_holds(plans):
+    """The walk's workspace holds c_max items, and every c_max that bounds the cells is
+    accepted: particles in groups (the leaves, say), with c_max from the number of groups
+    on."""
+    rng = np.random.default_rng(32)
+    rows, groups = [], []
+    for _ in range(500):
+        n = int(np.exp(rng.uniform(0, np.log(10 ** 7))))
+        k = max(1, n // int(rng.integers(1, 2000)))
+        sizes = np.bincount(rng.integers(0, k, n), minlength=k)
+        sizes = sizes[sizes > 0]
+        for c_max in {sizes.size, sizes.size + 1, (sizes.size + n) // 2, n, n + 1, 3 * n}:
+            if c_max >= sizes.size:
+                rows.append((n, c_max))
+                groups.append(sizes)
+    for (n, c_max), sizes, it in zip(rows, groups, plans(rows, "walk")):
+        items = sizes.size if it["whole"] else int(((sizes + it["part"] - 1) // it["part"]).sum())
+        assert items <= c_max, (n, c_max, sizes.size, items)
+        assert it["part"] <= 1024  # what a workgroup takes in one pass
+        if c_max >= n:
+            assert not it["whole"]
