@@ -269,8 +269,8 @@ __device__ __forceinline__ void add_cells(const GravArgs &g, WalkLds<T> &L, int 
 }
 
 // Particle terms of one staged batch.  SELF: the batch holds particles of the
-// group, so a particle may meet itself, which gives no term (or there is no
-// softening, and coincident particles are at distance zero).
+// group, so a particle may meet itself, which gives no term (or eps^2 is zero, and
+// coincident particles are at distance zero, or infinite, as every distance is then).
 template <int T, int U, bool SELF>
 __device__ __forceinline__ void add_batch(const WalkLds<T> &L, double eps2, int nb,
                                           const float (&xf)[U][3], const int32_t (&si)[U],
@@ -363,7 +363,8 @@ __device__ __forceinline__ int add_leaves(const GravArgs &g, WalkLds<T> &L, int 
       L.pidx[x] = (int32_t)s;
       own |= s >= gf && s - gf < gn;
     }
-    const bool self = __syncthreads_or(own ? 1 : 0) != 0 || !(g.eps2 > 0.0);
+    const bool self = __syncthreads_or(own ? 1 : 0) != 0 ||
+                      !(g.eps2 > 0.0 && g.eps2 < INFINITY);
     if (idle) continue;
     if (self)
       add_batch<T, U, true>(L, g.eps2, nb, xf, si, ai, slice, S);
