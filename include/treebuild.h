@@ -178,7 +178,8 @@ typedef struct {
  * or c_max == NULL. */
 int tb_max_cells(int64_t n, int32_t n_leaf, int64_t *c_max);
 
-/* Bytes of device workspace that tb_build() needs for these arguments.  On the
+/* Bytes of device workspace that tb_build() needs for these arguments, and for any
+ * smaller n with the others the same (the size never falls as n grows).  On the
  * current device it also opts the cell kernels in to their full LDS size (a
  * per-device kernel attribute, set once per process); a caller that captures
  * builds into a HIP graph should size the workspace, or run one build, before
@@ -222,7 +223,7 @@ int tb_build_sync(const float *pos, const float *mass, int64_t n, int32_t n_leaf
  *     cleared itself.
  *   - The caller still owns pos, mass and every output buffer of `out`.
  * Errors: as tb_build(), plus TB_ERR_SCRATCH (synchronous, before any launch)
- * when tb_workspace_bytes() for these arguments exceeds
+ * when the workspace of a build of exactly these arguments exceeds
  * TB_NOALLOC_SCRATCH_BYTES (64 MiB: about 10^6 particles at n_leaf 16). */
 #define TB_NOALLOC_SCRATCH_BYTES (64u << 20)
 

@@ -30,6 +30,7 @@ constexpr uint32_t kAutoBoxFlag = 0x10000u;
 constexpr int64_t kSmallTileMaxN = 3 << 18;
 // Most particles that are sorted in tiles of 2048 and of 4096 keys (pick_shape).
 constexpr int64_t kShortTileMaxN = 1 << 17, kShortTileSetsMaxN = 1 << 19;
+constexpr int64_t kShortTileMean = 2048;
 constexpr int64_t kWideTileMaxN = 1 << 20;
 
 static int64_t max_cells(int64_t n, int32_t n_leaf) {
@@ -50,7 +51,7 @@ static SortConfig pick_shape(const SortConfig &sc, int64_t n, int32_t nsets) {
   const SortConfig &d = kSortTable[0];
   if (sc.bits != d.bits || sc.ipt != d.ipt || sc.threads != d.threads) return sc;
   const int64_t mean = n / (nsets > 0 ? nsets : 1);
-  if (n <= kShortTileMaxN || (mean <= 2048 && n <= kShortTileSetsMaxN)) return {8, 4, 512};
+  if (n <= kShortTileMaxN || (mean <= kShortTileMean && n <= kShortTileSetsMaxN)) return {8, 4, 512};
   if (n <= kWideTileMaxN) return {8, 4, 1024};
   return sc;
 }
@@ -153,7 +154,8 @@ int make_plan(int64_t n, int32_t nsets, int32_t n_leaf, uint32_t flags,
   p->keys1 = take(8 * (size_t)n);
   p->vals1 = take(4 * (size_t)n);
   p->hist = take(4 * (size_t)P * R);
-  p->hist_part = take(4 * (size_t)keygen_blocks(n) * p->key_passes * R);
+  // (one pass less past 2^28 particles, but no less space for more particles)
+  p->hist_part = take(4 * (size_t)keygen_blocks(n) * ((40 + sc.bits - 1) / sc.bits) * R);
   p->status0 = take(8 * (size_t)p->sort_tiles * R);
   p->status1 = take(8 * (size_t)p->sort_tiles * R);
   p->counters = take(4 * 64);
@@ -177,12 +179,12 @@ int make_plan(int64_t n, int32_t nsets, int32_t n_leaf, uint32_t flags,
   p->seg_tile_set = take(p->seg ? 4 * (size_t)p->sort_tiles : 0);
   p->seg_base = take(p->seg ? 4 * (size_t)nsets * P * R : 0);
   p->packed = take(16 * (size_t)n);
-  p->sorted = take(16 * (size_t)n);
   // the boxes are known before the particles are sorted: the chunks' tables lie in
-  // the space of the sorted records (unless empty sets outnumber the particles)
+  // the space of the sorted records, which is no smaller than they are
   const size_t part_bytes = align256(8 * 6 * (size_t)p->bbox_chunks);
-  const size_t set_bytes = align256(4 * (size_t)p->bbox_chunks);
-  p->bbox_part = part_bytes + set_bytes <= 16 * (size_t)n ? p->sorted : take(part_bytes + set_bytes);
+  const size_t box_bytes = part_bytes + 4 * (size_t)p->bbox_chunks;
+  p->sorted = take(16 * (size_t)n > box_bytes ? 16 * (size_t)n : box_bytes);
+  p->bbox_part = p->sorted;
   p->chunk_set = p->bbox_part + part_bytes;
   p->ad = take(2 * (size_t)n);
   if (flags & TB_SUBTREES) {
@@ -197,6 +199,24 @@ int make_plan(int64_t n, int32_t nsets, int32_t n_leaf, uint32_t flags,
   p->m_lo = take((flags & 0xffu) == TB_MIXED ? 4 * (size_t)p->c_max : 0);
   p->total = off;
   return TB_OK;
+}
+
+// The workspace for up to n particles: larger tiles past a size need less of it, so it is
+// what the largest n of each tile needs, up to the one asked for.
+static size_t workspace_up_to(int64_t n, int32_t nsets, int32_t n_leaf, uint32_t flags,
+                              const SortConfig &sc) {
+  const int64_t mean_end = (kShortTileMean + 1) * nsets - 1;
+  const int64_t ends[] = {n, kShortTileMaxN,
+                          mean_end < kShortTileSetsMaxN ? mean_end : kShortTileSetsMaxN,
+                          kWideTileMaxN, kSmallTileMaxN};
+  size_t most = 0;
+  for (int64_t e : ends) {
+    if (e > n) continue;
+    Plan p;
+    make_plan(e, nsets, n_leaf, flags, sc, &p);
+    if (p.total > most) most = p.total;
+  }
+  return most;
 }
 
 Work carve(const Plan &p, void *base) {
@@ -426,6 +446,35 @@ static int wait_status(const tb_tree *out, hipStream_t s) {
 
 }  // namespace tb
 
+// Bytes of a build's workspace; `up_to`: of every build of at most n particles.
+static int workspace_bytes(int64_t n, int32_t nsets, int32_t n_leaf, uint32_t flags, bool up_to,
+                           size_t *bytes) {
+  int rc = tb::check_sizes(n, n_leaf);
+  if (rc) return rc;
+  if (nsets < 1 || nsets > tb::kMaxSetsLds) return TB_ERR_ARG;
+  tb::SortConfig sc;
+  rc = tb::config_from_flags(flags, &sc);
+  if (rc) return rc;
+  if (n == 0) {
+    *bytes = 0;
+    return TB_OK;
+  }
+  // The cell kernels' LDS opt-in is a per-device attribute set once, here as
+  // well as on the first build, so that a caller who sizes the workspace before
+  // capturing a build into a graph makes no attribute call during the capture.
+  (void)tb::cell_lds_limit();
+  // sized for data-derived boxes, so one workspace serves both kinds of call
+  flags |= tb::kAutoBoxFlag;
+  if (up_to) {
+    *bytes = tb::workspace_up_to(n, nsets, n_leaf, flags, sc);
+    return TB_OK;
+  }
+  tb::Plan p;
+  tb::make_plan(n, nsets, n_leaf, flags, sc, &p);
+  *bytes = p.total;
+  return TB_OK;
+}
+
 // ---------------------------------------------------------------------------
 // C ABI
 // ---------------------------------------------------------------------------
@@ -442,25 +491,7 @@ int tb_max_cells(int64_t n, int32_t n_leaf, int64_t *c_max) {
 int tb_workspace_bytes_batched(int64_t n_total, int32_t nsets, int32_t n_leaf, uint32_t flags,
                                size_t *bytes) {
   if (!bytes) return TB_ERR_ARG;
-  int rc = tb::check_sizes(n_total, n_leaf);
-  if (rc) return rc;
-  if (nsets < 1 || nsets > tb::kMaxSetsLds) return TB_ERR_ARG;
-  tb::SortConfig sc;
-  rc = tb::config_from_flags(flags, &sc);
-  if (rc) return rc;
-  if (n_total == 0) {
-    *bytes = 0;
-    return TB_OK;
-  }
-  // The cell kernels' LDS opt-in is a per-device attribute set once, here as
-  // well as on the first build, so that a caller who sizes the workspace before
-  // capturing a build into a graph makes no attribute call during the capture.
-  (void)tb::cell_lds_limit();
-  // sized for data-derived boxes, so one workspace serves both kinds of call
-  tb::Plan p;
-  tb::make_plan(n_total, nsets, n_leaf, flags | tb::kAutoBoxFlag, sc, &p);
-  *bytes = p.total;
-  return TB_OK;
+  return workspace_bytes(n_total, nsets, n_leaf, flags, true, bytes);
 }
 
 int tb_workspace_bytes(int64_t n, int32_t n_leaf, uint32_t flags, size_t *bytes) {
@@ -487,7 +518,7 @@ int tb_build_noalloc(const float *pos, const float *mass, int64_t n, int32_t n_l
   // sizes first: a build that does not fit the array is refused before any
   // HIP call
   size_t need = 0;
-  const int rc = tb_workspace_bytes(n, n_leaf, flags, &need);
+  const int rc = workspace_bytes(n, 1, n_leaf, flags, false, &need);
   if (rc) return rc;
   if (need > (size_t)TB_NOALLOC_SCRATCH_BYTES) return TB_ERR_SCRATCH;
   void *ws = nullptr;

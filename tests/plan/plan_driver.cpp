@@ -29,8 +29,8 @@ int main(int argc, char **argv) {
     tb::Plan p;
     if (tb::make_plan(n, (int32_t)nsets, (int32_t)n_leaf, (uint32_t)flags, asked, &p) != TB_OK)
       return 1;
-    std::printf("cell_tile %d cell_tiles %lld group_levels %d\n", p.cell_tile,
-                (long long)p.cell_tiles, tb::group_levels(p));
+    std::printf("cell_tile %d cell_tiles %lld group_levels %d total %zu\n", p.cell_tile,
+                (long long)p.cell_tiles, tb::group_levels(p), p.total);
   }
   return 0;
 }

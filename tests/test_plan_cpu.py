@@ -90,3 +90,38 @@ def test_walk_lists_no_more_items_than_the_workspace_holds(plans):
         assert it["part"] <= 1024  # what a workgroup takes in one pass
         if c_max >= n:
             assert not it["whole"]
+
+
+AUTO_BOX = 0x10000  # the plan's own flag: boxes from the data
+
+
+@pytest.mark.parametrize("flags", [0, tb.TB_MIXED, tb.TB_SUBTREES, tb.TB_SORT_COUNTED,
+                                   tb.TB_SORT_CONFIG(4), tb.TB_SORT_CONFIG(2),
+                                   tb.TB_SET_INDEX_BITS(14)])
+@pytest.mark.parametrize("nsets", [1, 2, 7, 60, 300, 1000, 16_383])
+def test_one_workspace_serves_every_smaller_build(plans, nsets, flags):
+    """tb_workspace_bytes never falls as n grows, and no build of n particles needs more
+    than it says (with boxes given or from the data)."""
+    rng = np.random.default_rng(nsets)
+    edges = [2 ** k for k in range(0, 30)] + [3 * 2 ** 18, 2049 * nsets, 32_769 * nsets,
+                                              1000 * 1024, 65_536 * 1024]
+    sizes = {int(e) + d for e in edges for d in (-2, -1, 0, 1, 2, 4096)}
+    sizes |= {int(x) for x in np.exp(rng.uniform(0, np.log(2 ** 29), 400))}
+    sizes |= set(range(1, 70)) | set(range(nsets, nsets + 1500, 7))
+    sizes = sorted(s for s in sizes if 0 < s <= 2 ** 29)
+    for n_leaf in (16, 64, 300):
+        said = [tb.tb_workspace_bytes_batched(n, nsets, n_leaf, flags) for n in sizes]
+        falls = [(a, b) for a, b, x, y in zip(sizes, sizes[1:], said, said[1:]) if y < x]
+        assert not falls, falls[:5]
+        for extra in (0, AUTO_BOX):
+            need = plans([(n, nsets, n_leaf, flags | extra) for n in sizes])
+            for n, x, p in zip(sizes, said, need):
+                assert p["total"] <= x, (n, p["total"], x)
+
+
+def test_what_fits_the_fixed_scratch(plans):
+    """tb_build_noalloc goes by the build's own need: just past a size at which the tiles
+    grow a build still fits where the largest one before did not."""
+    n, n_leaf = 2 ** 20 + 1, 40
+    need = plans([(n, 1, n_leaf, AUTO_BOX), (2 ** 20, 1, n_leaf, AUTO_BOX)])
+    assert need[0]["total"] < need[1]["total"] <= tb.tb_workspace_bytes(n, n_leaf)
