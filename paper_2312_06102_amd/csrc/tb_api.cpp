@@ -76,38 +76,52 @@ int make_plan(int64_t n, int32_t nsets, int32_t n_leaf, uint32_t flags,
   // caller may bound the set size (TB_SET_INDEX_BITS), which k_setup checks
   p->set_index_bits = p->seg ? (int)((flags >> 24) & 0x1fu) : 0;
   if (p->set_index_bits > 0 && p->set_index_bits < p->idx_bits) p->idx_bits = p->set_index_bits;
-  // Which key bits the radix passes sort.  Deep enough down the tree hardly two
-  // particles share a cell, so the passes take only the upper 32 or 40 of the 63 key bits, and the reorder, which has every particle's whole key anyway, orders the
-  // particles that agree in those (runs of at most kRunCap; longer ones go through
-  // k_sort_runs).  In the core of a Plummer sphere that spans its box a run holds about
-  // n 2^(18 - bits) particles: mean run (by particle) 3.5 for 2^18 in 32 bits, 1.7 for
-  // 2^24 in 40, and 0.1 % of the particles in runs past 32 for 2^26 clustered ones in
-  // 40.  Data that is denser than that is seen by a sample of the keys, which turns on
-  // the passes over the low bits (as does n_leaf > 95, whose windows the reorder cannot
-  // hold twice).  Sort of 2^24
-  // with all that goes with it: 470 us against 788 in all 63 bits.
-  const int64_t typical =
-      p->set_index_bits > 0 ? int64_t{1} << p->set_index_bits : p->seg ? 8 * (n / nsets) : n;
-  const int64_t dense = typical < n ? typical : n;
-  const int sorted_bits = dense <= (int64_t{1} << 18) ? 32 : 40;
-  p->key_passes = (sorted_bits + sc.bits - 1) / sc.bits;
-  // the first pass packs what is left of the key above the index (9-bit digits and more
-  // than 2^28 particles: one pass less)
-  if ((p->key_passes - 1) * sc.bits + p->idx_bits > 64) --p->key_passes;
-  p->skip_bits = 63 - p->key_passes * sc.bits;
-  // (at least two: they leave and return to one array)
-  p->low_passes = (p->skip_bits + sc.bits - 1) / sc.bits;
-  if (p->low_passes < 2) p->low_passes = 2;
-  // Element formats.  The first pass reads 64-bit keys and packs the key bits still to
-  // be sorted above the index in one 64-bit word (at most 32 + 31 bits with 8-bit digits);
-  // once they fit in 32 bits the word has 32.  With N = 2^24 the passes move 8 + 8, 8 + 8,
-  // 8 + 8, 8 + 4 and 4 + 4 bytes an element in and out.
+  if (reorder_finishes(n_leaf)) {
+    // Which key bits the radix passes sort.  Deep enough down the tree hardly two
+    // particles share a cell, so the passes take only the upper 32 or 40 of the 63 key
+    // bits, and the reorder, which has every particle's whole key anyway, orders the
+    // particles that agree in those (runs of at most kRunCap; longer ones go through
+    // k_sort_runs).  In the core of a Plummer sphere that spans its box a run holds about
+    // n 2^(18 - bits) particles: mean run (by particle) 3.5 for 2^18 in 32 bits, 1.7 for
+    // 2^24 in 40, and 0.1 % of the particles in runs past 32 for 2^26 clustered ones in
+    // 40.  Data that is denser than that is seen by a sample of the keys, which turns on
+    // the passes over the low bits.  Sort of 2^24 with all that goes with it: 470 us
+    // against 788 in all 63 bits.
+    const int64_t typical =
+        p->set_index_bits > 0 ? int64_t{1} << p->set_index_bits : p->seg ? 8 * (n / nsets) : n;
+    const int64_t dense = typical < n ? typical : n;
+    const int sorted_bits = dense <= (int64_t{1} << 18) ? 32 : 40;
+    p->key_passes = (sorted_bits + sc.bits - 1) / sc.bits;
+    // the first pass packs what is left of the key above the index (9-bit digits and more
+    // than 2^28 particles: one pass less)
+    if ((p->key_passes - 1) * sc.bits + p->idx_bits > 64) --p->key_passes;
+    p->skip_bits = 63 - p->key_passes * sc.bits;
+    // (at least two: they leave and return to one array)
+    p->low_passes = (p->skip_bits + sc.bits - 1) / sc.bits;
+    if (p->low_passes < 2) p->low_passes = 2;
+  } else {
+    // The windows of a larger n_leaf (above 95) leave the reorder no room to finish: every
+    // key bit is sorted.  Through the passes over the low bits and then the upper ones, as
+    // crowded data is, 2^24 particles with n_leaf 128 take 1875 us, so 1694 (before there
+    // were upper bits to sort by 1767).
+    p->key_passes = (63 + sc.bits - 1) / sc.bits;
+    p->skip_bits = p->low_passes = 0;
+  }
+  // Element formats.  The first pass reads 64-bit keys.  A pass packs the key bits still to
+  // be sorted above the index in one 64-bit word, in 32 bits once they fit, and else writes
+  // the key whole and the index beside it.  By the upper bits that is only ever the first
+  // pass's input (at most 32 + 31 bits with 8-bit digits): with N = 2^24 the passes move
+  // 8 + 8, 8 + 8, 8 + 8, 8 + 4 and 4 + 4 bytes an element in and out.  By all bits, where
+  // the leading 1 stays in the word (the key kernel's counts of the last 8-bit digit include
+  // it), 8 + 12, 12 + 12, 12 + 8, three times 8 + 8, 8 + 4 and 4 + 4.
+  const int top = p->skip_bits > 0 ? 63 : 64;
   p->form[0] = kFormKey64;
   for (int k = 0; k < p->key_passes; ++k) {
-    const int rem = 63 - p->skip_bits - (k + 1) * sc.bits;  // key bits left after pass k
+    const int rem = top - p->skip_bits - (k + 1) * sc.bits;  // key bits left after pass k
     p->form[k + 1] = k + 1 == p->key_passes                  ? kFormIdx
                      : k > 0 && rem + p->idx_bits <= 32 ? kFormPack32
-                                                             : kFormPack64;
+                     : rem + p->idx_bits <= 64          ? kFormPack64
+                                                        : kFormKey64;
   }
   // The passes of a single set with at least kCountedMinTiles tiles count their
   // tiles' digits first (reduce, then scan) instead of chaining the tiles
@@ -155,7 +169,9 @@ int make_plan(int64_t n, int32_t nsets, int32_t n_leaf, uint32_t flags,
   p->vals1 = take(4 * (size_t)n);
   p->hist = take(4 * (size_t)P * R);
   // (one pass less past 2^28 particles, but no less space for more particles)
-  p->hist_part = take(4 * (size_t)keygen_blocks(n) * ((40 + sc.bits - 1) / sc.bits) * R);
+  const size_t passes_counted =
+      reorder_finishes(n_leaf) ? (40 + sc.bits - 1) / sc.bits : p->key_passes;
+  p->hist_part = take(4 * (size_t)keygen_blocks(n) * passes_counted * R);
   p->status0 = take(8 * (size_t)p->sort_tiles * R);
   p->status1 = take(8 * (size_t)p->sort_tiles * R);
   p->counters = take(4 * 64);
@@ -377,10 +393,10 @@ static int build_impl(const float *pos, const float *mass, int64_t n, int32_t ns
   if (in.auto_box) run("bbox", [&] { return launch_bbox(p, w, pos, s); });
   run("keygen", [&] { return launch_keygen(p, w, pos, mass, *out, s); });
   if (one_tile(p)) {
-    run("sort_pass", [&] { return launch_sort_one(p, w, s); });
+    run("sort_pass", [&] { return launch_sort_one(p, w, *out, s); });
   } else {
     run("hist_reduce", [&] { return launch_hist_reduce(p, w, s); });
-    run("sort_low", [&] { return launch_low_passes(p, w, *out, s); });
+    if (p.low_passes) run("sort_low", [&] { return launch_low_passes(p, w, *out, s); });
     for (int pass = 0; pass < p.key_passes; ++pass)
       run("sort_pass", [&] { return launch_sort_pass(p, w, pass, *out, s); });
   }

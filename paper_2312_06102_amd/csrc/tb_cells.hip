@@ -45,7 +45,7 @@ __host__ __device__ constexpr int window_size(int tile, int nl, int ext) {
 }
 // A thread gathers IPT + 1 of the window's particles at once.  If that holds the window
 // with the ends of its runs (n_leaf <= 95 for either tile) the reorder finishes the sort;
-// larger windows get particles that the radix passes have sorted by their whole keys
+// larger windows get particles that the radix passes have sorted by all key bits
 // (make_plan).
 __host__ __device__ constexpr int window_ext(int nl) {
   return window_size(kCellTile, nl, kRunCap) <= (kCellIpt + 1) * kCellThreads ? kRunCap : 0;
@@ -354,7 +354,7 @@ __device__ inline void reorder_tile(const ReorderArgs &g, const WindowLds &s, in
     if (q < t0 || q >= t1) return;
     g.sorted[q] = rec[r];
     g.keys[q] = key;
-    g.perm[q] = p[r];
+    if (FINISH) g.perm[q] = p[r];  // (else the order is in perm)
     if (g.key_out) g.key_out[q] = key;
     bad |= !(rec[r].w > 0.0f && isfinite(rec[r].w));
     if (g.pos_sorted) {
@@ -1248,7 +1248,7 @@ hipError_t launch_cell_scan(const Plan &p, const Work &w, const tb_tree &out,
 // at most n / (kRunCap + 1) runs, and as many tiles as there are.
 static ReorderArgs reorder_args(const Plan &p, const Work &w, const tb_tree &out) {
   ReorderArgs g;
-  g.order = reinterpret_cast<const int32_t *>(w.vals1);
+  g.order = reinterpret_cast<const int32_t *>(sorted_order(p, w, out));
   g.packed = w.packed;
   g.n = p.n;
   g.nl = p.n_leaf;

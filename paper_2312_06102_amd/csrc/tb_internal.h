@@ -110,7 +110,8 @@ struct Plan {
   SortConfig sort;
   int key_passes;   // radix passes over the upper key bits, those above skip_bits
   int low_passes;   // conditional passes over the skip_bits below (see make_plan)
-  int skip_bits;    // low key bits that only the conditional passes look at
+  int skip_bits;    // low key bits that only the conditional passes look at (0: there are
+                    // none, every bit is sorted)
   uint32_t counted; // bit k: key pass k takes its tile offsets from a count and a scan
   int idx_bits;     // bits of the largest index, n - 1 (at least 1); in a batch the index
                     // is the position within the set
@@ -127,7 +128,7 @@ struct Plan {
   int64_t upper_cap;    // cells above the blocks, per depth: at most n / (n_serial + 1) + B
   // offsets
   size_t keys0, keys1;  // u64 [n] ping-pong buffers of keys or packed words
-  size_t vals1;         // u32 [n] payload buffer; the sort's last pass writes it
+  size_t vals1;         // u32 [n] payload buffer; the sort's last pass writes it (or perm)
   size_t hist;          // u32 [key_passes + low_passes][radix] global digit counts, then
                         // bases (single set)
   size_t hist_part;     // u32 [keygen blocks][key_passes][radix] per-workgroup counts
@@ -235,9 +236,10 @@ hipError_t launch_sort_pass(const Plan &p, const Work &w, int pass, const tb_tre
                             hipStream_t s);
 hipError_t launch_low_passes(const Plan &p, const Work &w, const tb_tree &out, hipStream_t s);
 bool sort_config_supported(const SortConfig &c);
+bool sort_pair_built(int form_in, int form_out);
 // Whether the sort is one launch of one workgroup.
 bool one_tile(const Plan &p);
-hipError_t launch_sort_one(const Plan &p, const Work &w, hipStream_t s);
+hipError_t launch_sort_one(const Plan &p, const Work &w, const tb_tree &out, hipStream_t s);
 // tb_cells.hip
 hipError_t launch_cell_scan(const Plan &p, const Work &w, const tb_tree &out,
                             int64_t *cell_offsets, hipStream_t s);
@@ -289,6 +291,11 @@ hipError_t launch_kick_drift(const int32_t *perm, const double *acc, int64_t n, 
 hipError_t launch_permute(const int32_t *perm, int64_t n, const void *src, int32_t width,
                           void *dst, int32_t *status, hipStream_t s);
 size_t gravity_workspace_bytes(int64_t c_max);
+
+// The indices the radix passes leave: perm itself, unless the reorder still orders runs.
+inline uint32_t *sorted_order(const Plan &p, const Work &w, const tb_tree &out) {
+  return reorder_finishes(p.n_leaf) ? w.vals1 : reinterpret_cast<uint32_t *>(out.perm);
+}
 
 // The sorted keys, recomputed from the sorted particles by the reorder pass (the
 // sort passes themselves stop carrying the key once its bits are consumed).

@@ -831,7 +831,7 @@ static hipError_t hist_reduce_t(const Plan &p, const Work &w, hipStream_t s) {
   // the first low pass's look-back words (see launch_low_passes)
   uint64_t *status = p.low_passes % 2 ? w.status1 : w.status0;
   const int64_t tiles = p.sort_tiles;
-  const unsigned low_blocks = (unsigned)(tiles < 512 ? tiles : 512);
+  const unsigned low_blocks = p.low_passes ? (unsigned)(tiles < 512 ? tiles : 512) : 0u;
   uint32_t *counts = w.seg_base;
   if (!p.seg) {
     const int cols = p.key_passes << BITS;
@@ -839,7 +839,7 @@ static hipError_t hist_reduce_t(const Plan &p, const Work &w, hipStream_t s) {
         w.hist_part, keygen_blocks(p.n), cols, w.hist, full, w.keys0, p.n, low, status,
         tiles << BITS);
     counts = w.hist;
-  } else {
+  } else if (low_blocks) {
     k_low_counts_sets<BITS><<<low_blocks, 256, 0, s>>>(
         full, w.keys0, low, w.seg_tile_start, w.seg_tile_set, w.set_off, p.nsets, p.sort.tile(),
         counts, p.key_passes, status);

@@ -16,8 +16,8 @@
 // The global digit counts come from the key-generation pass (and become each
 // digit's base once per build), so the keys are read only once per pass.
 //
-// The passes sort the upper 32 or 40 bits of the 63 (make_plan has the rule).  The
-// reorder orders the particles that agree in those by the rest of their keys and
+// The passes sort the upper 32 or 40 bits of the 63 (make_plan has the rule; all of them
+// for n_leaf above 95).  The reorder orders the particles that agree in those by the rest of their keys and
 // writes perm.  Passes over the low bits come first when the key kernel's sample has
 // found that the keys crowd; they are launched in any case and return at once if not.
 //
@@ -414,7 +414,8 @@ __device__ __forceinline__ void sweep_scatter(const typename S::Lds &L, uint32_t
 // One radix pass, one workgroup per tile.  kin/kout hold the key or packed
 // words; vin/vout the separate index of kFormKey64 (vin NULL: the index is the
 // position) and the output of kFormIdx.  shift: the digit's bit offset in the
-// input word; ib: idx_bits.  hist: the pass's digit bases, where each digit's
+// input word; ib: idx_bits; key_mask: the bits of a whole key that a packed word keeps.
+// hist: the pass's digit bases, where each digit's
 // run starts in the output [radix]; a batch has a row per set (set b at b *
 // base_stride).
 //
@@ -426,11 +427,12 @@ __device__ __forceinline__ void sweep_scatter(const typename S::Lds &L, uint32_t
 // 28-byte spill; the 4096-set batch's sort 6.45 -> 6.34 ms), while the counted
 // single-set pass loses more to its spill than it gains (sort 0.79 -> 0.87 ms)
 // and larger tiles leave no LDS for a third workgroup.
-// The conditional passes' loop over tiles is held to four waves (two workgroups a CU)
-// where the LDS of two fits.
+// The conditional passes' loop over tiles (and any look-back pass over whole keys) is held
+// to four waves (two workgroups a CU) where the LDS of two fits.
 template <int BITS, int IPT, int THREADS, int FIN, int FOUT, bool COUNTED, bool SEG>
 constexpr int sweep_waves() {
-  if (FIN == kFormKey64 && FOUT == kFormKey64) return THREADS == 512 && IPT <= 11 ? 4 : 1;
+  if (FIN == kFormKey64 && FOUT == kFormKey64)
+    return !COUNTED && THREADS == 512 && IPT <= 11 ? 4 : 1;
   if (BITS != 8) return 1;
   if (FIN == kFormPack32) return 6;
   if (FIN == kFormPack64 && SEG && !COUNTED && THREADS == 512 && THREADS * IPT <= 5120) return 6;
@@ -442,7 +444,7 @@ template <int BITS, int IPT, int THREADS, int FIN, int FOUT, bool COUNTED, bool 
 __device__ __forceinline__ bool sweep_tile(
     typename Sweep<BITS, IPT, THREADS, FIN, FOUT>::Lds &L, const void *__restrict__ kin_v,
     void *__restrict__ kout_v, const uint32_t *__restrict__ vin, uint32_t *__restrict__ vout,
-    uint32_t n, int shift, int ib, const uint32_t *__restrict__ hist,
+    uint32_t n, int shift, int ib, uint64_t key_mask, const uint32_t *__restrict__ hist,
     uint64_t *__restrict__ status, uint64_t *__restrict__ status_next,
     uint32_t *__restrict__ tile_counter, const uint32_t *__restrict__ tile_off,
     int32_t *__restrict__ status_word, uint32_t n_tiles, const SegTiles &seg,
@@ -497,9 +499,8 @@ __device__ __forceinline__ bool sweep_tile(
   uint32_t v[IPT];
   sweep_load<S, IPT>(kin, vin, wbase, last, set_lo, k, v);
   if constexpr (FIN == kFormKey64 && !LOW) {
-    // the leading 1 is no part of the packed word
 #pragma unroll
-    for (int j = 0; j < IPT; ++j) k[j] &= ~(1ull << 63);
+    for (int j = 0; j < IPT; ++j) k[j] &= key_mask;
   }
 
   uint32_t tcnt[DPT], trun_d[DPT];
@@ -541,7 +542,8 @@ __device__ __forceinline__ bool sweep_tile(
 template <int BITS, int IPT, int THREADS, int FIN, int FOUT, bool COUNTED, bool SEG>
 __global__ __launch_bounds__(THREADS, (sweep_waves<BITS, IPT, THREADS, FIN, FOUT, COUNTED, SEG>())) void k_onesweep(
     const void *__restrict__ kin, void *__restrict__ kout, const uint32_t *__restrict__ vin,
-    uint32_t *__restrict__ vout, uint32_t n, int shift, int ib, const uint32_t *__restrict__ hist,
+    uint32_t *__restrict__ vout, uint32_t n, int shift, int ib, uint64_t key_mask,
+    const uint32_t *__restrict__ hist,
     uint64_t *__restrict__ status, uint64_t *__restrict__ status_next,
     uint32_t *__restrict__ tile_counter, const uint32_t *__restrict__ tile_off,
     int32_t *__restrict__ status_word, uint32_t n_tiles, SegTiles seg, void *__restrict__ dig_out,
@@ -549,6 +551,7 @@ __global__ __launch_bounds__(THREADS, (sweep_waves<BITS, IPT, THREADS, FIN, FOUT
   __shared__ typename Sweep<BITS, IPT, THREADS, FIN, FOUT>::Lds L;
   // A pass over 64-bit keys that writes them whole sorts low bits, if the sample asked
   // for it; the first pass over the upper bits takes their order then, else the input's.
+  // (Where every bit is sorted in any case, the sample always asks.)
   constexpr bool LOW = FIN == kFormKey64 && FOUT == kFormKey64;
   if constexpr (FIN == kFormKey64) {
     if (*full == 0u) {
@@ -556,15 +559,15 @@ __global__ __launch_bounds__(THREADS, (sweep_waves<BITS, IPT, THREADS, FIN, FOUT
       vin = nullptr;
     }
   }
-  if constexpr (LOW) {
+  if constexpr (LOW && !COUNTED) {
     while (sweep_tile<BITS, IPT, THREADS, FIN, FOUT, COUNTED, SEG>(
-        L, kin, kout, vin, vout, n, shift, ib, hist, status, status_next, tile_counter, tile_off,
-        status_word, n_tiles, seg, dig_out))
+        L, kin, kout, vin, vout, n, shift, ib, key_mask, hist, status, status_next, tile_counter,
+        tile_off, status_word, n_tiles, seg, dig_out))
       __syncthreads();  // the tile's LDS is read out
   } else {
     sweep_tile<BITS, IPT, THREADS, FIN, FOUT, COUNTED, SEG>(
-        L, kin, kout, vin, vout, n, shift, ib, hist, status, status_next, tile_counter, tile_off,
-        status_word, n_tiles, seg, dig_out);
+        L, kin, kout, vin, vout, n, shift, ib, key_mask, hist, status, status_next, tile_counter,
+        tile_off, status_word, n_tiles, seg, dig_out);
   }
 }
 
@@ -595,10 +598,11 @@ static hipError_t launch_sweep(const Plan &p, const Work &w, int pass, const voi
                  : k_onesweep<BITS, IPT, THREADS, FIN, FOUT, COUNTED, false>;
   // (a small grid of the conditional passes returns sooner when there is nothing to do;
   // at 2^26 6.8 us with a workgroup a tile, 3.8 us so)
-  constexpr bool kLow = FIN == kFormKey64 && FOUT == kFormKey64;
+  constexpr bool kLow = FIN == kFormKey64 && FOUT == kFormKey64 && !COUNTED;
+  const uint64_t key_mask = p.skip_bits > 0 ? ~(1ull << 63) : ~0ull;
   const int64_t grid = kLow && p.sort_tiles > 512 ? 512 : p.sort_tiles;
   k<<<(unsigned)grid, THREADS, 0, s>>>(
-      kin, kout, vin, vout, (uint32_t)p.n, shift, p.idx_bits, hist, status, status_next,
+      kin, kout, vin, vout, (uint32_t)p.n, shift, p.idx_bits, key_mask, hist, status, status_next,
       w.counters + pass, w.tile_off, out.status, (uint32_t)p.sort_tiles, seg, dig_out,
       w.counters + kFullSortCounter);
   return hipGetLastError();
@@ -610,29 +614,41 @@ static hipError_t launch_pass_c(const Plan &p, const Work &w, int pass, const tb
   const int P = p.key_passes;
   void *K[2] = {w.keys0, w.keys1};
   uint64_t *S[2] = {w.status0, w.status1};
-  const int shift = FIN == kFormKey64 ? p.skip_bits : p.idx_bits;
+  const int shift = FIN == kFormKey64 ? p.skip_bits + pass * BITS : p.idx_bits;
   // a counted pass that follows needs this pass to leave its digits behind
   void *dig_out = (pass + 1 < P && ((p.counted >> (pass + 1)) & 1u)) ? w.dig : nullptr;
   auto go = ((p.counted >> pass) & 1u) ? launch_sweep<BITS, IPT, THREADS, FIN, FOUT, true>
                                        : launch_sweep<BITS, IPT, THREADS, FIN, FOUT, false>;
-  // vals1: the low passes' indices in (first pass), the sorted indices out (last pass)
-  return go(p, w, pass, K[pass % 2], K[(pass + 1) % 2], w.vals1, w.vals1, shift, S[pass % 2],
+  // the indices beside whole keys: the low passes' in the first pass, by turns in two arrays
+  // where every bit is sorted (the first pass then starts from the positions)
+  uint32_t *V[2] = {reinterpret_cast<uint32_t *>(out.perm), w.vals1};
+  const uint32_t *vin = pass == 0 && p.skip_bits == 0 ? nullptr : V[(pass + 1) % 2];
+  uint32_t *vout = FOUT == kFormIdx ? sorted_order(p, w, out) : V[pass % 2];
+  return go(p, w, pass, K[pass % 2], K[(pass + 1) % 2], vin, vout, shift, S[pass % 2],
             S[(pass + 1) % 2], dig_out, out, s);
 }
 
 // The format pairs make_plan produces for 8- and 9-bit digits and any N below 2^31.
+#define TB_SORT_PAIRS(PAIR)                                                               \
+  PAIR(kFormKey64, kFormKey64) PAIR(kFormKey64, kFormPack64) PAIR(kFormPack64, kFormPack64) \
+  PAIR(kFormPack64, kFormPack32) PAIR(kFormPack64, kFormIdx) PAIR(kFormPack32, kFormPack32) \
+  PAIR(kFormPack32, kFormIdx)
+
+bool sort_pair_built(int form_in, int form_out) {
+#define TB_PAIR(FI, FO) \
+  if (form_in == FI && form_out == FO) return true;
+  TB_SORT_PAIRS(TB_PAIR)
+#undef TB_PAIR
+  return false;
+}
+
 template <int BITS, int IPT, int THREADS>
 static hipError_t launch_pass_t(const Plan &p, const Work &w, int pass, const tb_tree &out,
                                 hipStream_t s) {
   const int fi = p.form[pass], fo = p.form[pass + 1];
 #define TB_PAIR(FI, FO) \
   if (fi == FI && fo == FO) return launch_pass_c<BITS, IPT, THREADS, FI, FO>(p, w, pass, out, s);
-  TB_PAIR(kFormKey64, kFormPack64)
-  TB_PAIR(kFormPack64, kFormPack64)
-  TB_PAIR(kFormPack64, kFormPack32)
-  TB_PAIR(kFormPack64, kFormIdx)
-  TB_PAIR(kFormPack32, kFormPack32)
-  TB_PAIR(kFormPack32, kFormIdx)
+  TB_SORT_PAIRS(TB_PAIR)
 #undef TB_PAIR
   return hipErrorInvalidValue;
 }
@@ -724,13 +740,13 @@ bool one_tile(const Plan &p) {
          !(p.flags & (TB_SORT_LOOKBACK | TB_SORT_COUNTED));
 }
 
-hipError_t launch_sort_one(const Plan &p, const Work &w, hipStream_t s) {
+hipError_t launch_sort_one(const Plan &p, const Work &w, const tb_tree &out, hipStream_t s) {
   auto k = p.n <= kOneThreads       ? k_sort_one<1>
            : p.n <= 2 * kOneThreads ? k_sort_one<2>
            : p.n <= 4 * kOneThreads ? k_sort_one<4>
                                     : k_sort_one<8>;
-  k<<<1, kOneThreads, 0, s>>>(static_cast<const uint64_t *>(w.keys0), w.vals1, (uint32_t)p.n,
-                              p.skip_bits, reorder_finishes(p.n_leaf) ? 0 : 1,
+  k<<<1, kOneThreads, 0, s>>>(static_cast<const uint64_t *>(w.keys0), sorted_order(p, w, out),
+                              (uint32_t)p.n, p.skip_bits, reorder_finishes(p.n_leaf) ? 0 : 1,
                               w.counters + kFullSortCounter);
   return hipGetLastError();
 }

@@ -29,8 +29,14 @@ int main(int argc, char **argv) {
     tb::Plan p;
     if (tb::make_plan(n, (int32_t)nsets, (int32_t)n_leaf, (uint32_t)flags, asked, &p) != TB_OK)
       return 1;
-    std::printf("cell_tile %d cell_tiles %lld group_levels %d total %zu\n", p.cell_tile,
-                (long long)p.cell_tiles, tb::group_levels(p), p.total);
+    std::printf("cell_tile %d cell_tiles %lld group_levels %d total %zu bits %d idx_bits %d "
+                "key_passes %d low_passes %d skip_bits %d counted %u",
+                p.cell_tile, (long long)p.cell_tiles, tb::group_levels(p), p.total, p.sort.bits,
+                p.idx_bits, p.key_passes, p.low_passes, p.skip_bits, p.counted);
+    for (int k = 0; k <= p.key_passes; ++k) std::printf(" form%d %d", k, (int)p.form[k]);
+    for (int k = 0; k < p.key_passes; ++k)
+      std::printf(" built%d %d", k, tb::sort_pair_built(p.form[k], p.form[k + 1]) ? 1 : 0);
+    std::printf("\n");
   }
   return 0;
 }

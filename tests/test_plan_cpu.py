@@ -6,10 +6,12 @@ import subprocess
 import numpy as np
 import pytest
 
+import bench
 from paper_2312_06102_amd import build_lib
 from paper_2312_06102_amd import treebuild as tb
 
 HERE = os.path.dirname(os.path.abspath(__file__))
+FORMS = {0: "idx", 2: "key64", 3: "pack64", 4: "pack32"}
 
 
 @pytest.fixture(scope="module")
@@ -125,3 +127,46 @@ def test_what_fits_the_fixed_scratch(plans):
     n, n_leaf = 2 ** 20 + 1, 40
     need = plans([(n, 1, n_leaf, AUTO_BOX), (2 ** 20, 1, n_leaf, AUTO_BOX)])
     assert need[0]["total"] < need[1]["total"] <= tb.tb_workspace_bytes(n, n_leaf)
+
+
+def _forms(p):
+    return [FORMS[p[f"form{k}"]] for k in range(p["key_passes"] + 1)]
+
+
+def _sizes():
+    sizes = {1, 2, 3, 2 ** 29 + 12345}
+    for b in range(1, 30):
+        sizes |= {(1 << b) - 1, 1 << b, (1 << b) + 1}
+    return sorted(sizes)
+
+
+@pytest.mark.parametrize("config,bits", [(0, 8), (2, 8), (4, 9)])
+@pytest.mark.parametrize("bound", [0, 5, 18, 28])
+def test_large_leaves_sort_every_bit(plans, config, bits, bound):
+    """n_leaf above 95: the passes sort all 63 bits and nothing is left to conditional
+    passes; at 95 they sort the upper bits."""
+    sizes = [n for n in _sizes() if n > 3]
+    flags = tb.TB_SORT_CONFIG(config) | tb.TB_SET_INDEX_BITS(bound)
+    nsets = 3 if bound else 1
+    for n_leaf in (96, 300, 1024):
+        for n, p in zip(sizes, plans([(n, nsets, n_leaf, flags) for n in sizes])):
+            assert p["bits"] == bits and p["low_passes"] == p["skip_bits"] == 0
+            assert _forms(p) == bench.sort_forms(n, bits, bound), n
+    for p in plans([(n, nsets, 95, flags) for n in sizes]):
+        assert 0 < p["skip_bits"] < 32 and p["low_passes"] >= 2
+        assert p["skip_bits"] + p["key_passes"] * bits == 63
+
+
+@pytest.mark.parametrize("flags", [0, tb.TB_SORT_CONFIG(4)])
+@pytest.mark.parametrize("n_leaf", [16, 128])
+def test_every_pass_of_every_plan_is_built(plans, n_leaf, flags):
+    rows = [(n, nsets, n_leaf, flags | tb.TB_SET_INDEX_BITS(k)) for n in _sizes()
+            for nsets in (1, 2, 1000) for k in ((0,) if nsets == 1 else (0, 1, 12, 18, 24, 31))]
+    for r, p in zip(rows, plans(rows)):
+        assert all(p[f"built{k}"] for k in range(p["key_passes"])), (r, _forms(p))
+        # a word holds what is left of the key beside the index
+        top = 63 if p["skip_bits"] else 64
+        for k in range(1, p["key_passes"]):
+            left = top - p["skip_bits"] - k * p["bits"] + p["idx_bits"]
+            form = FORMS[p[f"form{k}"]]
+            assert left <= {"pack32": 32, "pack64": 64, "key64": 1000}[form], (r, k, form)
