@@ -485,104 +485,186 @@ __global__ __launch_bounds__(kCellThreads) void k_reorder_again(ReorderArgs g) {
 }
 
 // Sorts each listed run of the radix passes' order by the key bits below `skip`, one
-// workgroup a run: an LSD radix sort with 8-bit digits of (low bits << 32 | index)
-// words in global memory.  The run lies in listed tiles only, whose sorted keys are not
-// written yet, so keys0 and keys1 hold the words.  A run that is in order already
-// (coincident particles) stays.  Rare (0.1 % of the particles of 2^26 clustered ones),
-// so one workgroup's latency a step is what it costs: 2^26, 1856 runs, 60 us.
-__global__ __launch_bounds__(kCellThreads) void k_sort_runs(
+// workgroup a run.  The run lies in listed tiles only, whose sorted keys are not written
+// yet, so keys0 and keys1 hold its (low bits << 32 | index) words.  Most runs are hardly
+// longer than kRunCap: those below kRunFirst particles go by the ranks of their words in
+// LDS.  A longer one (a clump too small for the sample to see: up to some 0.1 % of the
+// particles) takes an LSD radix sort with 8-bit digits, kRunTile words at a time; a digit
+// that all share takes no pass, and a run in order already (coincident particles) stays.
+// What one CU gathers, ranks and scatters is what it costs, some 7 us a thousand particles:
+// a clump of 80,000 in 2^26 uniform ones 588 us, of 12,000 in 2^24 92 us (1684 and 251 us
+// with 256 words a step; 527 us with 1024 threads, 552 us with 16 words a thread); 1856
+// short runs of 2^26 clustered particles 60 us.
+constexpr int kRunThreads = 512, kRunItems = 8, kRunTile = kRunThreads * kRunItems;
+constexpr int kRunFirst = 128;
+
+__global__ __launch_bounds__(kRunThreads) void k_sort_runs(
     ReorderArgs g, int32_t *__restrict__ order, uint64_t *__restrict__ buf0,
     uint64_t *__restrict__ buf1) {
-  constexpr int kThreads = kCellThreads, kRunWaves = kThreads / 64;
-  static_assert(kThreads == 256, "one thread per digit");
-  __shared__ uint32_t s_hist[256];
+  constexpr int kDigits = 4, kRunWaves = kRunThreads / 64, kEdges = kRunItems * kRunWaves;
+  static_assert(kRunThreads >= 256, "a thread for every digit");
+  __shared__ uint32_t s_hist[kDigits][256];  // counts, then where each digit's words go
   __shared__ uint32_t s_wave[kRunWaves][256];
-  __shared__ uint32_t s_w[kRunWaves];
-  __shared__ int s_set;
+  __shared__ uint64_t s_first[kRunFirst];
+  __shared__ uint32_t s_edge[kEdges + 1];  // low bits before each wave's first word
+  __shared__ uint32_t s_w[4];
+  __shared__ uint64_t s_pre;
+  __shared__ int s_set, s_len;
   const uint32_t n_runs = *g.n_runs;
-  const int t = threadIdx.x, wv = t / 64;
+  const int t = threadIdx.x, wv = t / 64, lane = lane_id();
+  const int digits = (g.skip + 7) / 8;
   for (uint32_t run = blockIdx.x; run < n_runs; run += gridDim.x) {
     const int64_t s = g.runs[run];
-    if (t == 0) s_set = upper_index(g.set_off, g.nsets + 1, s);
+    if (t == 0) {
+      s_set = upper_index(g.set_off, g.nsets + 1, s);
+      s_len = 0;
+    }
+    for (int i = t; i < kDigits * 256; i += kRunThreads) (&s_hist[0][0])[i] = 0;
     __syncthreads();
     const int b = s_set;
     const int64_t E = g.set_off[b + 1];
     const double lo0 = g.box[4 * b + 0], lo1 = g.box[4 * b + 1], lo2 = g.box[4 * b + 2];
     const double scale = 2097152.0 / g.box[4 * b + 3];
-    // the run's words, chunk by chunk up to the first particle past it
-    uint64_t pre = 0;
-    int64_t len = 0;
-    bool rising = true;
-    for (int64_t c0 = s;; c0 += kThreads) {
-      const int64_t q = c0 + t;
-      uint64_t key = 0;
-      int32_t idx = 0;
-      if (q < E) {
-        idx = order[q];
-        const float4 r = g.packed[idx >= 0 && idx < g.n ? idx : 0];
-        key = particle_key(r.x, r.y, r.z, lo0, lo1, lo2, scale, g.hilbert != 0);
-      }
-      if (c0 == s) {
-        if (t == 0) buf1[s] = key;
-        __syncthreads();
-        pre = buf1[s] >> g.skip;
-        __syncthreads();
-      }
-      const bool in = q < E && (key >> g.skip) == pre;
-      const uint64_t low = key & ((1ull << g.skip) - 1);
-      if (in) buf0[q] = low << 32 | (uint32_t)idx;
-      const int members = __syncthreads_count(in ? 1 : 0);
-      // a run is contiguous: its members are the first of the chunk
-      if (in && q > s) rising &= (buf0[q - 1] >> 32) <= low;
-      len += members;
-      if (members < kThreads) break;
+    // the key of the particle with index idx
+    auto key_of = [&](int32_t idx) {
+      const float4 r = g.packed[idx >= 0 && idx < g.n ? idx : 0];
+      return particle_key(r.x, r.y, r.z, lo0, lo1, lo2, scale, g.hilbert != 0);
+    };
+    const uint64_t low_mask = (1ull << g.skip) - 1;
+    uint64_t key = 0, word = ~0ull;
+    int32_t idx = 0;
+    if (t < kRunFirst && s + t < E) {
+      idx = order[s + t];
+      key = key_of(idx);
     }
+    if (t == 0) s_pre = key >> g.skip;
+    __syncthreads();
+    const uint64_t pre = s_pre;
+    const bool in = t < kRunFirst && s + t < E && (key >> g.skip) == pre;
+    if (in) word = (key & low_mask) << 32 | (uint32_t)idx;
+    if (t < kRunFirst) s_first[t] = word;
+    // a run is contiguous: its members are the first of what was looked at
+    const int members = __syncthreads_count(in ? 1 : 0);
+    if (members < kRunFirst) {
+      if (in) {
+        int rank = 0;
+        for (int j = 0; j < members; ++j) rank += s_first[j] < word ? 1 : 0;
+        order[s + rank] = idx;
+      }
+      __syncthreads();
+      continue;
+    }
+    auto count = [&](uint32_t low) {
+      for (int k = 0; k < digits; ++k) atomicAdd(&s_hist[k][(low >> (8 * k)) & 255u], 1u);
+    };
+    bool rising = true;
+    if (in) {
+      buf0[s + t] = word;
+      count((uint32_t)(word >> 32));
+      rising = t == 0 || (s_first[t - 1] >> 32) <= (word >> 32);
+      if (t == kRunFirst - 1) s_edge[kEdges] = (uint32_t)(word >> 32);
+    }
+    // the rest of the run, up to the first particle past it
+    for (int64_t c0 = s + kRunFirst;; c0 += kRunTile) {
+      int32_t id[kRunItems];
+      uint32_t low[kRunItems];
+      bool has[kRunItems];
+      int mine = 0;
+#pragma unroll
+      for (int r = 0; r < kRunItems; ++r) {
+        const int64_t q = c0 + r * kRunThreads + t;
+        id[r] = q < E ? order[q] : -1;
+      }
+#pragma unroll
+      for (int r = 0; r < kRunItems; ++r) {
+        const int64_t q = c0 + r * kRunThreads + t;
+        const uint64_t k = key_of(id[r]);
+        has[r] = q < E && (k >> g.skip) == pre;
+        low[r] = (uint32_t)(k & low_mask);
+      }
+      __syncthreads();  // the edge before this step is written
+      if (t == 0) s_edge[0] = s_edge[kEdges];
+      __syncthreads();
+#pragma unroll
+      for (int r = 0; r < kRunItems; ++r) {
+        if (has[r]) {
+          buf0[c0 + r * kRunThreads + t] = (uint64_t)low[r] << 32 | (uint32_t)id[r];
+          count(low[r]);
+          ++mine;
+        }
+        const uint32_t before = __shfl_up(low[r], 1, 64);
+        rising &= !has[r] || lane == 0 || before <= low[r];
+        if (lane == 63) s_edge[1 + r * kRunWaves + wv] = low[r];
+      }
+      const uint32_t sum = wave_inclusive_scan((uint32_t)mine);
+      if (lane == 63) atomicAdd(&s_len, (int)sum);
+      const bool whole = __syncthreads_and(mine == kRunItems ? 1 : 0) != 0;
+#pragma unroll
+      for (int r = 0; r < kRunItems; ++r)
+        rising &= !has[r] || lane != 0 || s_edge[r * kRunWaves + wv] <= low[r];
+      if (!whole) break;
+    }
+    const int len = kRunFirst + s_len;
     if (__syncthreads_and(rising ? 1 : 0)) continue;
     uint64_t *src = buf0 + s, *dst = buf1 + s;
-    for (int sh = 32; sh < 32 + g.skip; sh += 8) {
-      s_hist[t] = 0;
-      __syncthreads();
-      for (int64_t i = t; i < len; i += kThreads) atomicAdd(&s_hist[(src[i] >> sh) & 255u], 1u);
-      __syncthreads();
-      const uint32_t v = s_hist[t], inc = wave_inclusive_scan(v);
-      if (lane_id() == 63) s_w[wv] = inc;
-      __syncthreads();
-      uint32_t off = inc - v;
-      for (int q = 0; q < wv; ++q) off += s_w[q];
-      s_hist[t] = off;
-      // 256 words at a time, in order: ranks by ballots within a wave, the waves in turn
-      for (int64_t c0 = 0; c0 < len; c0 += kThreads) {
-        for (int q = 0; q < kRunWaves; ++q) s_wave[q][t] = 0;
+    for (int k = 0; k < digits; ++k) {
+      const int sh = 32 + 8 * k;
+      if (s_hist[k][(src[0] >> sh) & 255u] == (uint32_t)len) continue;  // the same for all
+      {
+        const uint32_t v = t < 256 ? s_hist[k][t] : 0u, inc = wave_inclusive_scan(v);
+        if (lane == 63 && wv < 4) s_w[wv] = inc;
         __syncthreads();
-        const bool in = c0 + t < len;
-        const uint64_t word = in ? src[c0 + t] : 0ull;
-        const uint32_t d = (uint32_t)(word >> sh) & 255u;
-        uint64_t peers = __ballot(in);
+        uint32_t off = inc - v;
+        for (int q = 0; q < wv && q < 4; ++q) off += s_w[q];
+        if (t < 256) s_hist[k][t] = off;
+      }
+      // a tile at a time, in order: a wave's words lie together, ranks by ballots within it
+      for (int c0 = 0; c0 < len; c0 += kRunTile) {
+        uint64_t w[kRunItems];
+        uint32_t rk[kRunItems];
+        const int i0 = c0 + wv * 64 * kRunItems + lane;
 #pragma unroll
-        for (int k = 0; k < 8; ++k) {
-          const bool bit = (d >> k) & 1u;
-          const uint64_t m = __ballot(bit);
-          peers &= bit ? m : ~m;
+        for (int r = 0; r < kRunItems; ++r) w[r] = src[min(i0 + r * 64, len - 1)];
+        for (int i = t; i < kRunWaves * 256; i += kRunThreads) (&s_wave[0][0])[i] = 0;
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < kRunItems; ++r) {
+          const bool have = i0 + r * 64 < len;
+          const uint32_t d = (uint32_t)(w[r] >> sh) & 255u;
+          uint64_t peers = __ballot(have);
+#pragma unroll
+          for (int i = 0; i < 8; ++i) {
+            const bool bit = (d >> i) & 1u;
+            const uint64_t m = __ballot(bit);
+            peers &= bit ? m : ~m;
+          }
+          const uint32_t before = (uint32_t)__popcll(peers & lanemask_lt());
+          const uint32_t was = s_wave[wv][d];
+          rk[r] = was + before;
+          if (have && before == 0) s_wave[wv][d] = was + (uint32_t)__popcll(peers);
         }
-        const uint32_t before = (uint32_t)__popcll(peers & lanemask_lt());
-        if (in && before == 0) s_wave[wv][d] = (uint32_t)__popcll(peers);
         __syncthreads();
-        if (in) {
-          uint32_t at = s_hist[d] + before;
-          for (int q = 0; q < wv; ++q) at += s_wave[q][d];
-          dst[at] = word;
+        if (t < 256) {
+          uint32_t at = s_hist[k][t];
+#pragma unroll
+          for (int q = 0; q < kRunWaves; ++q) {
+            const uint32_t c = s_wave[q][t];
+            s_wave[q][t] = at;
+            at += c;
+          }
+          s_hist[k][t] = at;
         }
         __syncthreads();
-        uint32_t add = 0;
-        for (int q = 0; q < kRunWaves; ++q) add += s_wave[q][t];
-        s_hist[t] += add;
-        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < kRunItems; ++r)
+          if (i0 + r * 64 < len) dst[s_wave[wv][(w[r] >> sh) & 255u] + rk[r]] = w[r];
+        __syncthreads();  // s_wave is read out
       }
       uint64_t *x = src;
       src = dst;
       dst = x;
     }
-    for (int64_t i = t; i < len; i += kThreads) order[s + i] = (int32_t)(uint32_t)src[i];
+    for (int i = t; i < len; i += kRunThreads) order[s + i] = (int32_t)(uint32_t)src[i];
     __syncthreads();
   }
 }
@@ -1298,7 +1380,7 @@ hipError_t launch_runs(const Plan &p, const Work &w, const tb_tree &out, hipStre
   // long is left)
   if (most == 0 || !reorder_finishes(p.n_leaf) || one_tile(p)) return hipSuccess;
   // small grids, which return at once in the common case that nothing is listed
-  k_sort_runs<<<(unsigned)(most < 256 ? most : 256), kCellThreads, 0, s>>>(
+  k_sort_runs<<<(unsigned)(most < 256 ? most : 256), kRunThreads, 0, s>>>(
       g, reinterpret_cast<int32_t *>(w.vals1), w.keys0, w.keys1);
   auto k = p.cell_tile == kCellTile ? k_reorder_again<kCellIpt> : k_reorder_again<kSmallIpt>;
   k<<<(unsigned)(p.cell_tiles < 512 ? p.cell_tiles : 512), kCellThreads,

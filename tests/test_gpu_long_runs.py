@@ -1,0 +1,103 @@
+"""Long runs of particles that agree in the sorted key bits, in sets whose sample stays
+quiet: the clumps lie at positions the key kernel does not sample, so k_sort_runs sorts
+them.  Lengths around its first look (128 particles) and its tiles (4096), orders in which
+it has nothing to do, coincident particles and both widths of the passes; exactly against
+the oracle."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2312_06102_amd import treebuild as tb
+
+from test_gpu_runs import check
+
+pytestmark = pytest.mark.gpu
+
+CELL = 2.0 ** -14
+
+
+def unsampled(n):
+    """Positions outside the sample: of 1024 (4096 past 2^20) stretches the k-th is sampled at
+    a place that a multiplicative hash of k picks."""
+    samples = 4096 if n > 2 ** 20 else 1024
+    k = np.arange(samples, dtype=np.uint64)
+    lo, hi = k * np.uint64(n) // np.uint64(samples), (k + np.uint64(1)) * np.uint64(n) // np.uint64(samples)
+    with np.errstate(over="ignore"):
+        h = (k * np.uint64(0x9E3779B97F4A7C15)) >> np.uint64(33)
+    at = lo + h % (hi - lo)
+    keep = np.ones(n, bool)
+    keep[at.astype(np.int64)] = False
+    return np.nonzero(keep)[0]
+
+
+def with_clumps(n, sizes, seed, order="random", same=0):
+    rng = np.random.default_rng(seed)
+    pos = rng.random((n, 3), dtype=np.float32)
+    free = unsampled(n)
+    take = rng.permutation(free)[:sum(sizes)]
+    at = 0
+    for size in sizes:
+        corner = np.floor(rng.random(3) / CELL) * CELL
+        x = (corner + CELL * rng.random((size, 3)) * 0.999).astype(np.float32)
+        x[:same] = x[0]
+        where = take[at:at + size]
+        if order != "random":
+            # (a row of the clump along x only: sorted by x is sorted by key)
+            x[:, 1:] = x[0, 1:]
+            x = x[np.argsort(x[:, 0], kind="stable")]
+            where = np.sort(where)
+            if order == "falling":
+                x = x[::-1]
+        pos[where] = x
+        at += size
+    return pos
+
+
+@pytest.mark.parametrize("size", [127, 128, 129, 130, 640, 4095, 4096, 4223, 4224, 4225, 8320,
+                                  20_001, 60_000])
+@pytest.mark.parametrize("n", [2 ** 18, 300_007])
+def test_lengths(n, size):
+    count = max(1, min(5, n // 10 // size))
+    check(with_clumps(n, [size] * count, size))
+
+
+@pytest.mark.parametrize("order", ["rising", "falling"])
+@pytest.mark.parametrize("size", [100, 5000])
+def test_orders(size, order):
+    check(with_clumps(300_007, [size] * 4, size, order))
+
+
+@pytest.mark.parametrize("same", [100, 4000, 6000])
+def test_coincident(same):
+    check(with_clumps(280_000, [6000, 300, 6000], same, same=same))
+
+
+def test_large_set_and_9_bit_digits():
+    pos = with_clumps(2 ** 20 + 77, [30_000, 200, 9000], 3)
+    check(pos)
+    check(pos, sort_config=4)
+    check(with_clumps(2 ** 18, [30_000], 4), sort_config=4)
+
+
+def test_batch_with_a_dense_set():
+    rng = np.random.default_rng(5)
+    sizes = np.array([400_000, 0, 20_000, 300_000, 5000, 500_000], np.int64)
+    off = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int64)
+    n = int(off[-1])
+    pos = rng.random((n, 3), dtype=np.float32)
+    free = unsampled(n)
+    for b in (2, 4):
+        here = free[(free >= off[b]) & (free < off[b + 1])]
+        pos[here] = (0.25 + CELL * rng.random((here.size, 3))).astype(np.float32)
+    mass = np.full(n, 1.0, np.float32)
+    boxes = np.tile(np.array([0.0, 0.0, 0.0, 1.0]), (sizes.size, 1))
+    for bits in (0, 19):
+        r = tb.build_batched(torch.from_numpy(pos).cuda(), torch.from_numpy(mass).cuda(),
+                             torch.from_numpy(off).cuda(), 16, torch.from_numpy(boxes).cuda(),
+                             set_index_bits=bits)
+        perm = r["perm"].cpu().numpy()
+        for b in (0, 2, 3, 4):
+            s = slice(int(off[b]), int(off[b + 1]))
+            ref = oracle.build(pos[s], mass[s], 16, moments=False)
+            assert np.array_equal(perm[s] - off[b], ref["perm"]), (bits, b)
