@@ -171,8 +171,8 @@ STAGE_OF = [("k_onesweep", "sort_pass"), ("k_sort_one", "sort_pass"), ("k_sort_r
 
 
 def _stage(kernel: str):
-    # the conditional passes read and write 64-bit keys (element format 2)
-    if kernel.startswith("k_onesweep<") and kernel.split(", ")[3:5] == ["2", "2"]:
+    # the conditional passes read element format 5
+    if kernel.startswith("k_onesweep<") and kernel.split(", ")[3] == "5":
         return "sort_low"
     for prefix, st in STAGE_OF:
         if kernel.startswith(prefix):

@@ -99,6 +99,8 @@ int make_plan(int64_t n, int32_t nsets, int32_t n_leaf, uint32_t flags,
     // (at least two: they leave and return to one array)
     p->low_passes = (p->skip_bits + sc.bits - 1) / sc.bits;
     if (p->low_passes < 2) p->low_passes = 2;
+    // what the conditional passes leave fits one word with the index (2^24 particles)
+    p->low_packed = 63 - p->skip_bits + p->idx_bits <= 64;
   } else {
     // The windows of a larger n_leaf (above 95) leave the reorder no room to finish: every
     // key bit is sorted.  Through the passes over the low bits and then the upper ones, as

@@ -94,6 +94,7 @@ enum SortForm : uint8_t {
   kFormKey64 = 2,   // the 64-bit key, with the index in a separate u32 array
   kFormPack64 = 3,  // (key >> consumed bits) << idx_bits | index, in 64 bits
   kFormPack32 = 4,  // the same in 32 bits
+  kFormLow = 5,     // what a conditional pass over the low bits reads: as kFormKey64
 };
 constexpr int kMaxKeyPasses = 8;
 // One radix digit as the counted passes store it between passes.
@@ -112,6 +113,7 @@ struct Plan {
   int low_passes;   // conditional passes over the skip_bits below (see make_plan)
   int skip_bits;    // low key bits that only the conditional passes look at (0: there are
                     // none, every bit is sorted)
+  bool low_packed;  // the conditional passes leave the upper bits packed above the index
   uint32_t counted; // bit k: key pass k takes its tile offsets from a count and a scan
   int idx_bits;     // bits of the largest index, n - 1 (at least 1); in a batch the index
                     // is the position within the set

@@ -429,20 +429,24 @@ __device__ __forceinline__ void key_one(float x, float y, float z, float m, bool
 
 // Whether the keys crowd below the sorted bits: the sampler (one workgroup, beside
 // the key kernel's others) counts how many of its samples agree with an earlier one in
-// the sorted bits and sets *full from min_dups on.  The samples are distinct particles
+// the sorted bits (repeats), and in how many prefixes.  *full is set from a number of
+// prefixes on, which many runs give, or of repeats, which one large run gives.  The samples are distinct particles
 // spread over the whole input; equal prefixes are found through a hash table of 32-bit
 // fingerprints in LDS (a false match only runs passes that are not needed).  4096
 // samples see runs of kRunMean particles each in 2^24 as six pairs, 1024 in 2^20 as
 // many; small inputs take the fewer, whose 6 us the key kernel covers.
 constexpr int kSamples = 4096;
 constexpr int kSampleTable = 2 * kSamples;
+struct SampleLimit {
+  uint32_t prefixes, repeats;
+};
 static int64_t sample_count(int64_t n) { return n > (int64_t{1} << 20) ? kSamples : kSamples / 4; }
 
 template <int SAMPLES>
 __device__ inline void sample_keys(const float *__restrict__ pos, int64_t n,
                                    const int64_t *__restrict__ set_off, int32_t nsets,
                                    const double *__restrict__ box, int skip, bool hilbert,
-                                   uint32_t min_dups, uint32_t *table, uint32_t *s_dups,
+                                   SampleLimit limit, uint32_t *table, uint32_t *s_dups,
                                    uint32_t *__restrict__ full) {
   constexpr int kTable = 2 * SAMPLES;
   for (int i = threadIdx.x; i < kTable; i += kKeygenThreads) table[i] = 0;
@@ -494,33 +498,55 @@ __device__ inline void sample_keys(const float *__restrict__ pos, int64_t n,
       uint64_t hash =
           ((key >> skip) + (uint64_t)set[r] * 0xd1342543de82ef95ull) * 0x9e3779b97f4a7c15ull;
       hash = (hash ^ (hash >> 29)) * 0xbf58476d1ce4e5b9ull;
-      const uint32_t tag = (uint32_t)(hash >> 32) | 1u;
+      const uint32_t tag = ((uint32_t)(hash >> 32) & ~3u) | 1u;  // bit 1: seen again
       uint32_t slot = (uint32_t)hash % kTable;
       // at most half of the slots are taken, so the probe ends
       for (int probe = 0; use[r] && probe < kTable; ++probe) {
         const uint32_t was = atomicCAS(&table[slot], 0u, tag);
-        if (was == tag) ++dups;
-        if (was == 0u || was == tag) break;
+        if ((was & ~2u) == tag) {
+          ++dups;
+          atomicOr(&table[slot], 2u);
+        }
+        if (was == 0u || (was & ~2u) == tag) break;
         slot = (slot + 1) % kTable;
       }
     }
   }
   if (dups) atomicAdd(s_dups, dups);
   __syncthreads();
-  if (threadIdx.x == 0 && *s_dups >= min_dups) *full = 1u;
+  const uint32_t repeats = *s_dups;
+  bool crowd = repeats >= limit.repeats;
+  if (!crowd && repeats >= limit.prefixes) {  // the same for all
+    __syncthreads();
+    if (threadIdx.x == 0) *s_dups = 0;
+    __syncthreads();
+    uint32_t seen = 0;
+#pragma unroll 1
+    for (int i = threadIdx.x; i < kTable; i += kKeygenThreads) seen += (table[i] >> 1) & 1u;
+    if (seen) atomicAdd(s_dups, seen);
+    __syncthreads();
+    crowd = *s_dups >= limit.prefixes;
+  }
+  if (threadIdx.x == 0 && crowd) *full = 1u;
 }
 
-// Samples that may agree with an earlier one before the low bits are sorted as well:
-// what runs of kRunMean particles each would give.
-// (None, if the reorder does not finish the sort.)
-static uint32_t sample_limit(const Plan &p) {
-  if (!reorder_finishes(p.n_leaf)) return 0u;
-  const int64_t n = p.n;
+// From when on the low bits are sorted as well.  Prefixes: what runs of kRunMean
+// particles each would give.  Repeats: what a run gives that k_sort_runs sorts no faster
+// than the conditional passes do, 7 us a thousand particles against 45 us and 22 us a
+// million of all.  (Builds of 2^24 uniform particles with a clump of 12,000 or 28,000 in
+// one cell, by the passes / as a run: 1738 / 1486 and 1731 / 1588 us; 2^26 with 80,000
+// 7098 / 6057.)
+// (No limit, if the reorder does not finish the sort.)
+static SampleLimit sample_limit(const Plan &p) {
+  if (!reorder_finishes(p.n_leaf)) return {0u, 0u};
+  const double n = (double)p.n;
   constexpr double kRunMean = 12.0;
-  const double s = (double)(n < sample_count(n) ? n : sample_count(n));
-  const double per_run = kRunMean * s / (double)n;  // samples in a run
+  const double s = p.n < sample_count(p.n) ? n : (double)sample_count(p.n);
+  const double per_run = kRunMean * s / n;  // samples in a run
   const double dups = s * (1.0 - (1.0 - std::exp(-per_run)) / per_run);
-  return dups < 4.0 ? 4u : (uint32_t)dups;
+  const double run = (45.0 + 22e-6 * n) / 7e-3;
+  const double repeats = s * run / n;
+  return {dups < 4.0 ? 4u : (uint32_t)dups, repeats < 4.0 ? 4u : (uint32_t)repeats};
 }
 
 // A single set: a grid-stride loop, one histogram per workgroup.
@@ -529,16 +555,16 @@ __global__ __launch_bounds__(kKeygenThreads) void k_keygen(
     const float *__restrict__ pos, const float *__restrict__ mass, int64_t n,
     const double *__restrict__ box, uint64_t *__restrict__ keys, float4 *__restrict__ packed,
     void *__restrict__ dig0, uint32_t *__restrict__ hist_part, int passes, int skip, int hilbert,
-    int few, uint32_t min_dups, uint32_t *__restrict__ full, int32_t *__restrict__ status_word) {
+    int few, SampleLimit limit, uint32_t *__restrict__ full, int32_t *__restrict__ status_word) {
   constexpr int R = 1 << BITS;
   __shared__ uint32_t h[kSampleTable];  // [passes][R] digit counts
   __shared__ uint32_t s_dups;
   static_assert(kMaxKeyPasses * R <= kSampleTable, "the counts fit in the sampler's table");
   if (blockIdx.x == 0) {
     if (few)
-      sample_keys<kSamples / 4>(pos, n, nullptr, 1, box, skip, hilbert != 0, min_dups, h, &s_dups, full);
+      sample_keys<kSamples / 4>(pos, n, nullptr, 1, box, skip, hilbert != 0, limit, h, &s_dups, full);
     else
-      sample_keys<kSamples>(pos, n, nullptr, 1, box, skip, hilbert != 0, min_dups, h, &s_dups, full);
+      sample_keys<kSamples>(pos, n, nullptr, 1, box, skip, hilbert != 0, limit, h, &s_dups, full);
     return;
   }
   const int64_t block = blockIdx.x - 1, blocks = gridDim.x - 1;
@@ -584,7 +610,7 @@ __global__ __launch_bounds__(kKeygenThreads) void k_keygen_sets(
     const int64_t *__restrict__ set_off, int32_t nsets, const double *__restrict__ box,
     uint64_t *__restrict__ keys, float4 *__restrict__ packed, void *__restrict__ dig0,
     uint32_t *__restrict__ set_counts, int passes, int rows, int skip, int hilbert,
-    int few, uint32_t min_dups, uint32_t *__restrict__ full, int32_t *__restrict__ status_word) {
+    int few, SampleLimit limit, uint32_t *__restrict__ full, int32_t *__restrict__ status_word) {
   constexpr int R = 1 << BITS;
   constexpr int64_t kStep = (int64_t)kKeygenThreads * kKeygenIpt;
   __shared__ uint32_t h[kSampleTable];  // [passes][R] digit counts
@@ -593,9 +619,9 @@ __global__ __launch_bounds__(kKeygenThreads) void k_keygen_sets(
   static_assert(kMaxKeyPasses * R <= kSampleTable, "the counts fit in the sampler's table");
   if (blockIdx.x == 0) {
     if (few)
-      sample_keys<kSamples / 4>(pos, n, set_off, nsets, box, skip, hilbert != 0, min_dups, h, &s_dups, full);
+      sample_keys<kSamples / 4>(pos, n, set_off, nsets, box, skip, hilbert != 0, limit, h, &s_dups, full);
     else
-      sample_keys<kSamples>(pos, n, set_off, nsets, box, skip, hilbert != 0, min_dups, h, &s_dups, full);
+      sample_keys<kSamples>(pos, n, set_off, nsets, box, skip, hilbert != 0, limit, h, &s_dups, full);
     return;
   }
   const int64_t per = (n + gridDim.x - 2) / (gridDim.x - 1);
@@ -683,6 +709,18 @@ struct LowDigits {
   int shift[kMaxKeyPasses];
 };
 
+constexpr int kLowLoads = 8;  // keys in flight a thread (2^24: 45 us, with one 102 us)
+
+template <int BITS>
+__device__ __forceinline__ void count_low(uint64_t k, const LowDigits &low, uint32_t *h) {
+  constexpr int R = 1 << BITS;
+#pragma unroll
+  for (int p = 0; p < kMaxKeyPasses; ++p) {
+    if (p >= low.passes) break;
+    atomicAdd(&h[p * R + ((uint32_t)(k >> low.shift[p]) & (R - 1))], 1u);
+  }
+}
+
 // Digit counts of the conditional passes of a single set, added to rows `hist`
 // [passes][R] by the workgroups [first, gridDim.x), which also clear the first such
 // pass's look-back words.
@@ -696,10 +734,15 @@ __device__ inline void low_counts(const uint64_t *__restrict__ keys, int64_t n, 
   const int64_t step = (int64_t)(gridDim.x - first) * blockDim.x;
   const int64_t i0 = (int64_t)(blockIdx.x - first) * blockDim.x + threadIdx.x;
   for (int64_t i = i0; i < n_status; i += step) status[i] = 0;
-  for (int64_t i = i0; i < n; i += step) {
-    const uint64_t k = keys[i];
-    for (int p = 0; p < low.passes; ++p)
-      atomicAdd(&h[p * R + ((uint32_t)(k >> low.shift[p]) & (R - 1))], 1u);
+  for (int64_t i = i0; i < n; i += kLowLoads * step) {
+    uint64_t k[kLowLoads];
+#pragma unroll
+    for (int r = 0; r < kLowLoads; ++r) k[r] = keys[min(i + r * step, n - 1)];
+#pragma unroll
+    for (int r = 0; r < kLowLoads; ++r) {
+      if (i + r * step >= n) break;
+      count_low<BITS>(k[r], low, h);
+    }
   }
   __syncthreads();
   for (int i = threadIdx.x; i < low.passes * R; i += blockDim.x)
@@ -757,10 +800,15 @@ __global__ __launch_bounds__(256) void k_low_counts_sets(
     const int64_t lo = set_off[b] + (tile - tile_start[b]) * tile_keys;
     const int64_t hi = min(lo + tile_keys, set_off[b + 1]);
     for (int i = threadIdx.x; i < R; i += blockDim.x) status[tile * R + i] = 0;
-    for (int64_t i = lo + threadIdx.x; i < hi; i += blockDim.x) {
-      const uint64_t k = keys[i];
-      for (int p = 0; p < low.passes; ++p)
-        atomicAdd(&h[p * R + ((uint32_t)(k >> low.shift[p]) & (R - 1))], 1u);
+    for (int64_t i = lo + threadIdx.x; i < hi; i += kLowLoads * blockDim.x) {
+      uint64_t k[kLowLoads];
+#pragma unroll
+      for (int r = 0; r < kLowLoads; ++r) k[r] = keys[min(i + r * blockDim.x, hi - 1)];
+#pragma unroll
+      for (int r = 0; r < kLowLoads; ++r) {
+        if (i + r * blockDim.x >= hi) break;
+        count_low<BITS>(k[r], low, h);
+      }
     }
     __syncthreads();
     uint32_t *dst = set_counts + ((int64_t)b * (high + low.passes) + high) * R;

@@ -82,6 +82,10 @@ template <>
 struct FormType<kFormPack64> {
   using T = uint64_t;
 };
+template <>
+struct FormType<kFormLow> {
+  using T = uint64_t;
+};
 
 // Digit at bit offset `shift` (uniform): the pass's digit position for a 64-bit
 // key, idx_bits for a packed element.
@@ -217,12 +221,13 @@ __device__ __forceinline__ uint32_t lane_bit_mask(uint32_t d, int b) {
 }
 
 // Shape and LDS of one radix tile.  FIN / FOUT: element format read / written
-// (FIN is never kFormIdx).
+// (FIN is never kFormIdx, FOUT never kFormLow).
 template <int BITS, int IPT, int THREADS, int FIN, int FOUT>
 struct Sweep {
   using KI = typename FormType<FIN>::T;
   using KO = typename FormType<FOUT>::T;
-  static constexpr bool PIN = FIN != kFormKey64;  // packed input: the index is in the word
+  // packed input: the index is in the word
+  static constexpr bool PIN = FIN != kFormKey64 && FIN != kFormLow;
   static constexpr int R = 1 << BITS;
   static constexpr int WAVES = THREADS / 64;
   static constexpr int TILE = THREADS * IPT;
@@ -247,16 +252,24 @@ struct Sweep {
 // are clamped and the items masked later) so that all of them are in flight
 // together.  v: the separate index of kFormKey64; when vin is NULL, the position
 // less vbase (the set's first position in a batch, whose sort carries indices
-// within the set).
+// within the set).  in_word > 0: the words are key bits above an index of that many bits
+// all the same; the key bits then move up by `shift`.
 template <class S, int IPT>
 __device__ __forceinline__ void sweep_load(const typename S::KI *__restrict__ kin,
                                            const uint32_t *__restrict__ vin, uint32_t wbase,
                                            uint32_t last, uint32_t vbase,
-                                           typename S::KI (&k)[IPT], uint32_t (&v)[IPT]) {
+                                           typename S::KI (&k)[IPT], uint32_t (&v)[IPT],
+                                           int in_word = 0, int shift = 0) {
 #pragma unroll
   for (int j = 0; j < IPT; ++j) k[j] = kin[min(wbase + j * 64, last)];
   if constexpr (!S::PIN) {
-    if (vin) {
+    if (in_word > 0) {
+#pragma unroll
+      for (int j = 0; j < IPT; ++j) {
+        v[j] = (uint32_t)k[j] & (in_word >= 32 ? 0xffffffffu : (1u << in_word) - 1u);
+        k[j] = (k[j] >> in_word) << shift;
+      }
+    } else if (vin) {
 #pragma unroll
       for (int j = 0; j < IPT; ++j) v[j] = vin[min(wbase + j * 64, last)];
     } else {
@@ -427,12 +440,11 @@ __device__ __forceinline__ void sweep_scatter(const typename S::Lds &L, uint32_t
 // 28-byte spill; the 4096-set batch's sort 6.45 -> 6.34 ms), while the counted
 // single-set pass loses more to its spill than it gains (sort 0.79 -> 0.87 ms)
 // and larger tiles leave no LDS for a third workgroup.
-// The conditional passes' loop over tiles (and any look-back pass over whole keys) is held
-// to four waves (two workgroups a CU) where the LDS of two fits.
+// The conditional passes' loop over tiles is held to four waves (two workgroups a CU)
+// where the LDS of two fits.
 template <int BITS, int IPT, int THREADS, int FIN, int FOUT, bool COUNTED, bool SEG>
 constexpr int sweep_waves() {
-  if (FIN == kFormKey64 && FOUT == kFormKey64)
-    return !COUNTED && THREADS == 512 && IPT <= 11 ? 4 : 1;
+  if (FIN == kFormLow) return THREADS == 512 && IPT <= 11 ? 4 : 1;
   if (BITS != 8) return 1;
   if (FIN == kFormPack32) return 6;
   if (FIN == kFormPack64 && SEG && !COUNTED && THREADS == 512 && THREADS * IPT <= 5120) return 6;
@@ -448,11 +460,11 @@ __device__ __forceinline__ bool sweep_tile(
     uint64_t *__restrict__ status, uint64_t *__restrict__ status_next,
     uint32_t *__restrict__ tile_counter, const uint32_t *__restrict__ tile_off,
     int32_t *__restrict__ status_word, uint32_t n_tiles, const SegTiles &seg,
-    void *__restrict__ dig_out) {
+    void *__restrict__ dig_out, int in_word) {
   using S = Sweep<BITS, IPT, THREADS, FIN, FOUT>;
   using KI = typename S::KI;
   constexpr int R = S::R, WAVES = S::WAVES, TILE = S::TILE, DPT = S::DPT;
-  constexpr bool LOW = FIN == kFormKey64 && FOUT == kFormKey64;
+  constexpr bool LOW = FIN == kFormLow;
   const KI *__restrict__ kin = static_cast<const KI *>(kin_v);
   typename S::KO *__restrict__ kout = static_cast<typename S::KO *>(kout_v);
   constexpr bool batch = SEG;
@@ -497,8 +509,8 @@ __device__ __forceinline__ bool sweep_tile(
   const uint32_t wbase = lo + (uint32_t)(threadIdx.x / 64) * 64u * IPT + (uint32_t)lane_id();
   KI k[IPT];
   uint32_t v[IPT];
-  sweep_load<S, IPT>(kin, vin, wbase, last, set_lo, k, v);
-  if constexpr (FIN == kFormKey64 && !LOW) {
+  sweep_load<S, IPT>(kin, vin, wbase, last, set_lo, k, v, in_word, shift);
+  if constexpr (!S::PIN && FOUT != kFormKey64) {
 #pragma unroll
     for (int j = 0; j < IPT; ++j) k[j] &= key_mask;
   }
@@ -547,27 +559,30 @@ __global__ __launch_bounds__(THREADS, (sweep_waves<BITS, IPT, THREADS, FIN, FOUT
     uint64_t *__restrict__ status, uint64_t *__restrict__ status_next,
     uint32_t *__restrict__ tile_counter, const uint32_t *__restrict__ tile_off,
     int32_t *__restrict__ status_word, uint32_t n_tiles, SegTiles seg, void *__restrict__ dig_out,
-    const uint32_t *__restrict__ full) {
+    const uint32_t *__restrict__ full, int low_word) {
   __shared__ typename Sweep<BITS, IPT, THREADS, FIN, FOUT>::Lds L;
-  // A pass over 64-bit keys that writes them whole sorts low bits, if the sample asked
-  // for it; the first pass over the upper bits takes their order then, else the input's.
+  // The conditional passes sort the low bits, if the sample asked for it; the first pass
+  // over the upper bits takes their order and words (low_word) then, else the input's.
   // (Where every bit is sorted in any case, the sample always asks.)
-  constexpr bool LOW = FIN == kFormKey64 && FOUT == kFormKey64;
-  if constexpr (FIN == kFormKey64) {
+  constexpr bool LOW = FIN == kFormLow;
+  int in_word = 0;
+  if constexpr (FIN == kFormKey64 || LOW) {
     if (*full == 0u) {
       if constexpr (LOW) return;
       vin = nullptr;
+    } else if (!LOW) {
+      in_word = low_word;
     }
   }
-  if constexpr (LOW && !COUNTED) {
+  if constexpr (LOW) {
     while (sweep_tile<BITS, IPT, THREADS, FIN, FOUT, COUNTED, SEG>(
         L, kin, kout, vin, vout, n, shift, ib, key_mask, hist, status, status_next, tile_counter,
-        tile_off, status_word, n_tiles, seg, dig_out))
+        tile_off, status_word, n_tiles, seg, dig_out, in_word))
       __syncthreads();  // the tile's LDS is read out
   } else {
     sweep_tile<BITS, IPT, THREADS, FIN, FOUT, COUNTED, SEG>(
         L, kin, kout, vin, vout, n, shift, ib, key_mask, hist, status, status_next, tile_counter,
-        tile_off, status_word, n_tiles, seg, dig_out);
+        tile_off, status_word, n_tiles, seg, dig_out, in_word);
   }
 }
 
@@ -598,13 +613,13 @@ static hipError_t launch_sweep(const Plan &p, const Work &w, int pass, const voi
                  : k_onesweep<BITS, IPT, THREADS, FIN, FOUT, COUNTED, false>;
   // (a small grid of the conditional passes returns sooner when there is nothing to do;
   // at 2^26 6.8 us with a workgroup a tile, 3.8 us so)
-  constexpr bool kLow = FIN == kFormKey64 && FOUT == kFormKey64 && !COUNTED;
+  constexpr bool kLow = FIN == kFormLow;
   const uint64_t key_mask = p.skip_bits > 0 ? ~(1ull << 63) : ~0ull;
   const int64_t grid = kLow && p.sort_tiles > 512 ? 512 : p.sort_tiles;
   k<<<(unsigned)grid, THREADS, 0, s>>>(
       kin, kout, vin, vout, (uint32_t)p.n, shift, p.idx_bits, key_mask, hist, status, status_next,
       w.counters + pass, w.tile_off, out.status, (uint32_t)p.sort_tiles, seg, dig_out,
-      w.counters + kFullSortCounter);
+      w.counters + kFullSortCounter, pass == 0 && p.low_packed ? p.idx_bits : 0);
   return hipGetLastError();
 }
 
@@ -655,7 +670,8 @@ static hipError_t launch_pass_t(const Plan &p, const Work &w, int pass, const tb
 
 // The conditional passes over the low key bits, before the others: whole keys and
 // their indices from keys0 through the space of the sorted records and back to keys0,
-// the indices through perm and vals1 to vals1.  They look back whatever the others do
+// the indices through perm and vals1 to vals1 (or, once both fit a word, the upper bits
+// packed above the index to keys0).  They look back whatever the others do
 // (their launches return at once unless the sample asked for them), on the look-back
 // words that leave status0 clear for the first pass that follows.
 template <int BITS, int IPT, int THREADS>
@@ -672,9 +688,11 @@ static hipError_t launch_low_t(const Plan &p, const Work &w, const tb_tree &out,
     uint64_t *kout = last ? w.keys0 : K[k % 2];
     uint32_t *vout = V[(L - 1 - k) % 2];
     void *dig_out = last && (p.counted & 1u) ? w.dig : nullptr;
-    const hipError_t e = launch_sweep<BITS, IPT, THREADS, kFormKey64, kFormKey64, false>(
-        p, w, p.key_passes + k, kin, kout, vin, vout, low_shift(p, k), S[(k + L) % 2],
-        S[(k + L + 1) % 2], dig_out, out, s);
+    auto go = last && p.low_packed
+                  ? launch_sweep<BITS, IPT, THREADS, kFormLow, kFormPack64, false>
+                  : launch_sweep<BITS, IPT, THREADS, kFormLow, kFormKey64, false>;
+    const hipError_t e = go(p, w, p.key_passes + k, kin, kout, vin, vout, low_shift(p, k),
+                            S[(k + L) % 2], S[(k + L + 1) % 2], dig_out, out, s);
     if (e != hipSuccess) return e;
     kin = kout;
     vin = vout;

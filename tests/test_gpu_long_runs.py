@@ -101,3 +101,15 @@ def test_batch_with_a_dense_set():
             s = slice(int(off[b]), int(off[b + 1]))
             ref = oracle.build(pos[s], mass[s], 16, moments=False)
             assert np.array_equal(perm[s] - off[b], ref["perm"]), (bits, b)
+
+
+@pytest.mark.parametrize("share", [0.004, 0.01, 0.02, 0.05, 0.2, 0.6])
+@pytest.mark.parametrize("n", [40_000, 300_007, 2 ** 20 + 77])
+def test_clumps_that_the_sample_sees(n, share):
+    """One clump of a share of all particles, anywhere: as a run while it is small, by the
+    passes over the low bits from some size on."""
+    rng = np.random.default_rng(int(n * share))
+    pos = rng.random((n, 3), dtype=np.float32)
+    at = rng.permutation(n)[:int(n * share)]
+    pos[at] = (0.625 + CELL * rng.random((at.size, 3))).astype(np.float32)
+    check(pos)
