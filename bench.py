@@ -433,7 +433,7 @@ def kernel_bytes(n: int, cells: int, leaves: int, key_passes: int, precision: st
     compulsory traffic), per build.
 
     keygen      read pos 12 + mass 4; write key 8 + packed (x, y, z, m) record 16
-    sort_pass   of a sort by all 63 bits (upper_sort_bytes: of the passes that run);
+    sort_pass   of a sort by all 63 bits (upper_sort_bytes: by the upper ones);
                 per pass, what its element format moves in and out (sort_forms):
                 key 8 + index 4 while the key is 64-bit (pass 0 reads the key alone:
                 its index is the position), then one packed word of 8 or 4 bytes;
@@ -473,8 +473,9 @@ def kernel_bytes(n: int, cells: int, leaves: int, key_passes: int, precision: st
 
 
 def sort_forms(n: int, bits: int, index_bits: int = 0) -> list:
-    """Element format read by each radix pass, then the last pass's output, as
-    the library plans them: the index needs ib = bits(n - 1) bits (or a batch's
+    """Element format read by each radix pass, then the last pass's output, of a
+    sort by all 63 key bits, as the library plans it for n_leaf above 95 (smaller
+    leaves: upper_sort_bytes): the index needs ib = bits(n - 1) bits (or a batch's
     set-size bound, index_bits, when smaller); once the key bits not yet
     consumed (with its leading 1) fit beside it in 64 or 32 bits, key and index
     travel as one packed word."""
@@ -663,7 +664,9 @@ def run_single(args, tb, dg, torch, np):
     trace = traced_kernels(run, args.steps, tb)
     key_passes = trace["sort_pass"][0] // args.steps
     alg = kernel_bytes(n, cells, leaves, key_passes, precision)
-    alg["sort_pass"] = upper_sort_bytes(n, tb.tb_sort_configs()[k][0], key_passes)
+    bits = tb.tb_sort_configs()[k][0]
+    if key_passes * bits < 63:
+        alg["sort_pass"] = upper_sort_bytes(n, bits, key_passes)
     total_method = method_bytes(n, cells, key_passes, precision)
     line = {
         "metric": METRIC, "value": n / sec, "unit": "particles/s", "n_gpus": 1,
@@ -758,7 +761,9 @@ def run_batched(args, tb, dg, torch, np):
     trace = traced_kernels(eager, args.steps, tb)
     key_passes = trace["sort_pass"][0] // args.steps
     alg = kernel_bytes(n, cells, leaves, key_passes, precision, set_bits)
-    alg["sort_pass"] = upper_sort_bytes(n, tb.tb_sort_configs()[k][0], key_passes, set_bits)
+    bits = tb.tb_sort_configs()[k][0]
+    if key_passes * bits < 63:
+        alg["sort_pass"] = upper_sort_bytes(n, bits, key_passes, set_bits)
     total_method = method_bytes(n, cells, key_passes, precision)
     line = {
         "metric": METRIC, "value": n / sec, "unit": "particles/s", "n_gpus": 1,

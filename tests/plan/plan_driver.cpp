@@ -33,6 +33,8 @@ int main(int argc, char **argv) {
                 "key_passes %d low_passes %d skip_bits %d counted %u",
                 p.cell_tile, (long long)p.cell_tiles, tb::group_levels(p), p.total, p.sort.bits,
                 p.idx_bits, p.key_passes, p.low_passes, p.skip_bits, p.counted);
+    std::printf(" low_packed %d", p.low_packed ? 1 : 0);
+    for (int k = 0; k < p.low_passes; ++k) std::printf(" low%d %d", k, tb::low_shift(p, k));
     for (int k = 0; k <= p.key_passes; ++k) std::printf(" form%d %d", k, (int)p.form[k]);
     for (int k = 0; k < p.key_passes; ++k)
       std::printf(" built%d %d", k, tb::sort_pair_built(p.form[k], p.form[k + 1]) ? 1 : 0);

@@ -170,3 +170,75 @@ def test_every_pass_of_every_plan_is_built(plans, n_leaf, flags):
             left = top - p["skip_bits"] - k * p["bits"] + p["idx_bits"]
             form = FORMS[p[f"form{k}"]]
             assert left <= {"pack32": 32, "pack64": 64, "key64": 1000}[form], (r, k, form)
+
+
+@pytest.mark.parametrize("config,bits", [(0, 8), (4, 9)])
+@pytest.mark.parametrize("bound", [0, 12, 18, 31])
+def test_byte_model_of_the_upper_bits(plans, config, bits, bound):
+    """bench.upper_sort_bytes adds up the formats of the plan."""
+    rows = [(n, 5 if bound else 1, 16, tb.TB_SORT_CONFIG(config) | tb.TB_SET_INDEX_BITS(bound))
+            for n in _sizes()]
+    size = {"key64": 8, "pack64": 8, "pack32": 4, "idx": 4}
+    for (n, *_), p in zip(rows, plans(rows)):
+        f = _forms(p)
+        want = n * sum(size[a] + size[b] for a, b in zip(f, f[1:]))
+        assert bench.upper_sort_bytes(n, bits, p["key_passes"], bound) == want, (n, f)
+
+
+def _emulate(keys, p):
+    """The passes of a plan as the kernels compute them: the first reads whole keys and drops
+    what is not sorted (and the leading 1, unless every bit is); a packed word has its digit
+    at bit idx_bits.  Every pass's digit is the key's (as the key kernel counts it)."""
+    bits, ib, skip = p["bits"], p["idx_bits"], p["skip_bits"]
+    u = np.uint64
+    words, idx = keys.copy(), np.arange(keys.shape[0], dtype=np.uint64)
+    for k in range(p["key_passes"]):
+        fi, fo = FORMS[p[f"form{k}"]], FORMS[p[f"form{k + 1}"]]
+        shift = skip + k * bits if fi == "key64" else ib
+        if fi != "key64":
+            idx = words & u((1 << ib) - 1)
+        elif fo != "key64" and skip > 0:
+            words = words & u((1 << 63) - 1)
+        d = (words >> u(shift)) & u((1 << bits) - 1)
+        want = (keys[idx.astype(np.int64)] >> u(skip + k * bits)) & u((1 << bits) - 1)
+        assert np.array_equal(d, want), (k, fi)
+        order = np.argsort(d, kind="stable")
+        words, idx = words[order], idx[order]
+        if fo in ("pack64", "pack32"):
+            words = ((words >> u(shift + bits)) << u(ib)) | idx
+            if fo == "pack32":
+                assert not np.any(words >> u(32))
+    return idx
+
+
+@pytest.mark.parametrize("config", [0, 4])
+@pytest.mark.parametrize("n_leaf", [16, 128])
+@pytest.mark.parametrize("log_n", [1, 2, 7, 12, 16, 17, 18, 19, 23, 24, 25, 26, 28])
+def test_passes_sort_stably_by_the_bits_of_the_plan(plans, config, n_leaf, log_n):
+    p = plans([(1 << log_n, 1, n_leaf, tb.TB_SORT_CONFIG(config))])[0]
+    rng = np.random.default_rng(log_n * 10 + config)
+    n = min(4000, 1 << log_n)
+    body = rng.integers(0, 1 << 63, n, dtype=np.uint64)
+    # duplicates, keys that differ only in the lowest or highest bits, or below the sorted ones
+    body[::7] = body[1::7][: body[::7].shape[0]]
+    body[3::11] ^= np.uint64(1)
+    body[5::13] ^= np.uint64(1 << 62)
+    body[2::5] = (body[2::5] & np.uint64(2 ** 20 - 1)) | np.uint64(5 << 40)
+    keys = body | np.uint64(1 << 63)
+    got = _emulate(keys, p)
+    assert np.array_equal(got, np.argsort(keys >> np.uint64(p["skip_bits"]), kind="stable"))
+
+
+@pytest.mark.parametrize("log_n", [10, 17, 18, 19, 24, 25, 28])
+@pytest.mark.parametrize("config", [0, 4])
+def test_conditional_passes_meet_the_upper_ones(plans, config, log_n):
+    """The digits of the conditional passes cover the bits that the others leave, and their
+    packed output, where the plan has it, fits one word."""
+    for n in (1 << log_n, (1 << log_n) + 1):
+        p = plans([(n, 1, 16, tb.TB_SORT_CONFIG(config))])[0]
+        low = [max(0, p["skip_bits"] - p["bits"] * (p["low_passes"] - k))
+               for k in range(p["low_passes"])]
+        assert low == [p[f"low{k}"] for k in range(p["low_passes"])]
+        assert low[0] == 0 and all(b <= a + p["bits"] for a, b in zip(low, low[1:]))
+        assert low[-1] + p["bits"] == p["skip_bits"]
+        assert p["low_packed"] == (63 - p["skip_bits"] + p["idx_bits"] <= 64)
