@@ -11,9 +11,8 @@
  *   4. every leaf straight from the sorted keys, with the leaf depth
  *      D_k = max(minDepth(k, k-1), minDepth(k, k+n_leaf)) of Sec. 2.3.1 and
  *      Appendix A, evaluated for all particles at once;
- *   5. the parents, one depth at a time from the deepest upwards, each created
- *      by the first of its children in key order and linked to all of them
- *      (Sec. 2.3.2, Algorithm 2);
+ *   5. the parents from the deepest upwards, each created by the first of its
+ *      children in key order and linked to all of them (Sec. 2.3.2, Algorithm 2);
  *   6. monopole, centre of mass and traceless quadrupole of every cell, leaves
  *      from their particles and parents from their children as soon as the
  *      children are complete (Sec. 2.3.2 and its footnotes).
@@ -93,7 +92,8 @@ extern "C" {
 #define TB_MIXED 1u
 
 /* Optional radix-sort shape in flag bits 8..15: an index into the table that
- * tb_sort_configs() lists; 0 is the default.  Every shape gives bit-identical
+ * tb_sort_configs() lists; 0 is the default: the shape listed there for large builds,
+ * shapes of 2048 or 4096 keys a tile for smaller ones.  Every shape gives bit-identical
  * results; only speed and workspace size differ. */
 #define TB_SORT_CONFIG(k) (((uint32_t)(k)&0xffu) << 8)
 
@@ -116,8 +116,9 @@ extern "C" {
  * cells and moments with the leaf depth D_k = max(minDepth(k, k-1),
  * minDepth(k, k + n_leaf), d_root), d_root the block's depth; the cells above
  * the blocks are built from the block roots last.  Without the flag the cells
- * are placed tile by tile and the parents built one depth at a time over the
- * whole tree.  The tree is identical either way; only speed and workspace
+ * are placed tile by tile and the parents built by the tiles that hold their
+ * particles, then by groups of tiles (very small leaves: one depth at a time
+ * over the whole tree).  The tree is identical either way; only speed and workspace
  * differ. */
 #define TB_SUBTREES (1u << 18)
 
@@ -370,8 +371,8 @@ int tb_trace_enable(int on);
 int tb_trace_read(tb_trace_entry *out, int cap, int *count);
 
 /* The selectable radix-sort shapes: desc[3k..3k+2] = {digit bits, keys per
- * thread, threads per workgroup} of TB_SORT_CONFIG(k).  With cap = 0 only
- * *count (the table size) is written. */
+ * thread, threads per workgroup} of TB_SORT_CONFIG(k) (entry 0: that of large
+ * builds).  With cap = 0 only *count (the table size) is written. */
 int tb_sort_configs(int32_t *desc, int cap, int *count);
 
 /* Library version string, e.g. "treebuild 0.2 gfx950". */

@@ -227,8 +227,9 @@ __device__ inline void depths_from_window(const WindowLds &s, int64_t S, int64_t
 // a_i | D_i << 8 for every particle of the tile and the tile's cell count per
 // depth.  Every thread issues all of a batch's index loads, then all of its
 // gathers, so the random reads overlap; they bound the pass (one 128-byte line a
-// 16-byte record: 2^24 in random order, 2.1 GB of lines in 0.45 ms).  Also fills perm and the optional
-// pos_sorted / mass_sorted / key_sorted outputs and checks the masses.
+// 16-byte record: 2^24 in random order, 2.1 GB of lines in 0.45 ms).  Also fills perm (if
+// the sort has not) and the optional pos_sorted / mass_sorted / key_sorted outputs and
+// checks the masses.
 //
 // The radix passes sort by the key bits from `skip` on, so a run of particles that
 // agree in those arrives in input order.  A particle's place in its run follows from
@@ -930,8 +931,8 @@ struct SetScan {
 // With one set of at most kFewTiles tiles the emit pass takes the prefixes over the tile
 // counts itself, every workgroup its own (22 depths of at most 1 KB each, all loads in
 // flight at once), instead of waiting for two launches that do little: 2^16 particles
-// 119.5 -> 114.1 us (7 us of launches for 2 us in the emit pass).  The first tile's workgroup writes what the
-// set scan would.
+// 119.5 -> 114.1 us (7 us of launches for 2 us in the emit pass).  The first tile's
+// workgroup writes what the set scan would.
 constexpr int kFewTiles = 256;
 bool few_tiles(const Plan &p) {
   return p.nsets == 1 && p.cell_tiles <= kFewTiles && !(p.flags & TB_SUBTREES);

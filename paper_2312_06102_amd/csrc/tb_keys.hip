@@ -430,11 +430,11 @@ __device__ __forceinline__ void key_one(float x, float y, float z, float m, bool
 // Whether the keys crowd below the sorted bits: the sampler (one workgroup, beside
 // the key kernel's others) counts how many of its samples agree with an earlier one in
 // the sorted bits (repeats), and in how many prefixes.  *full is set from a number of
-// prefixes on, which many runs give, or of repeats, which one large run gives.  The samples are distinct particles
-// spread over the whole input; equal prefixes are found through a hash table of 32-bit
-// fingerprints in LDS (a false match only runs passes that are not needed).  4096
-// samples see runs of kRunMean particles each in 2^24 as six pairs, 1024 in 2^20 as
-// many; small inputs take the fewer, whose 6 us the key kernel covers.
+// prefixes on, which many runs give, or of repeats, which one large run gives.  The
+// samples are distinct particles spread over the whole input; equal prefixes are found
+// through a hash table of 32-bit fingerprints in LDS (a false match only runs passes that
+// are not needed).  4096 samples see runs of kRunMean particles each in 2^24 as six pairs,
+// 1024 in 2^20 as many; small inputs take the fewer, whose 6 us the key kernel covers.
 constexpr int kSamples = 4096;
 constexpr int kSampleTable = 2 * kSamples;
 struct SampleLimit {
@@ -600,8 +600,8 @@ __global__ __launch_bounds__(kKeygenThreads) void k_keygen(
   for (int i = threadIdx.x; i < passes * R; i += blockDim.x) dst[i] = h[i];
 }
 
-// A batch: the first workgroup samples; of the G others, workgroup g takes the particles [g N / G, (g + 1) N / G) of the whole
-// batch, which may span several sets (or part of one).  Its histogram is added
+// A batch: the first workgroup samples; of the G others, workgroup g takes the particles
+// [g N / G, (g + 1) N / G) of the whole batch, which may span several sets (or part of one).  Its histogram is added
 // to the set's counts, set_counts[b][p][d], each time its range leaves a set, so
 // every workgroup has the same number of particles whatever the set sizes.
 template <int BITS>

@@ -1,5 +1,6 @@
-// tb_parents.hip -- parents one depth at a time, deepest first (Sec. 2.3.2,
-// Algorithm 2), with their counts, child links and moments.
+// tb_parents.hip -- parents, deepest first (Sec. 2.3.2, Algorithm 2), with their counts,
+// child links and moments: by the tiles of particles that hold them, or, where leaves are
+// very small, one launch a depth.
 //
 // Algorithm 2 scans the depth-(d+1) cells in key order and hangs each one on
 // the parent whose key is its own key shifted right by three bits, opening a
@@ -9,7 +10,7 @@
 // depth-d cell are one contiguous run at depth d+1, and the cell placement pass
 // already recorded each internal cell's first child and, for that first child,
 // the slot of its parent.  Two ways to go up the tree (owned_parents has the rule
-// between them):  a few launches in which every tile of particles, then every group of
+// between them): a few launches in which every tile of particles, then every group of
 // tiles, builds the cells it holds entirely (second half of this file), and, for very
 // small leaves, one launch per depth: the depth-(d+1) cells (and the
 // parent slots of their first children) are staged through LDS in key order; a

@@ -17,9 +17,10 @@
 // digit's base once per build), so the keys are read only once per pass.
 //
 // The passes sort the upper 32 or 40 bits of the 63 (make_plan has the rule; all of them
-// for n_leaf above 95).  The reorder orders the particles that agree in those by the rest of their keys and
-// writes perm.  Passes over the low bits come first when the key kernel's sample has
-// found that the keys crowd; they are launched in any case and return at once if not.
+// for n_leaf above 95).  The reorder orders the particles that agree in those by the rest
+// of their keys and writes perm.  Passes over the low bits come first when the key
+// kernel's sample has found that the keys crowd; they are launched in any case and return
+// at once if not.
 //
 // By default the passes of a large single set are "counted" instead (reduce, then
 // scan; a batch with TB_SORT_COUNTED too): a first kernel reads each element's
@@ -43,7 +44,9 @@
 // consumed or not sorted, over the index in one packed word, (key bits << idx_bits) |
 // index, whose digit is read at bit idx_bits; once both fit in 32 bits the word has 32.
 // The last pass writes the index alone.  (The low passes move whole keys and indices in
-// two arrays.)  The sorted keys themselves are recomputed from the sorted particles in
+// two arrays, and leave the upper bits packed where that fits.  Where every bit is sorted
+// the first passes do the same, until the rest of the key fits beside the index.)  The
+// sorted keys themselves are recomputed from the sorted particles in
 // the reorder pass, which reads those particles anyway.
 #include "tb_internal.h"
 
