@@ -29,6 +29,8 @@
 // take every S-th source of a batch; U (1 to 4) is the one that wastes the
 // fewest lanes.  The S partial sums of a particle are added in order at the end.
 // A source is read from LDS once for U particles.
+#include <cmath>
+
 #include "tb_internal.h"
 #include "tb_moments.h"
 
@@ -68,7 +70,7 @@ struct GravArgs {
   const double *box;
   const float *pos;   // sorted positions [n][3]
   const float *mass;  // sorted masses [n]
-  double theta2, eps2;
+  double theta2, eps2;  // (eps2: minus infinity stands for infinity)
   int hilbert;  // the cell keys are Peano-Hilbert keys
 };
 
@@ -193,7 +195,7 @@ __device__ __forceinline__ void add_sums(double (&ai)[U][4], const double (&bi)[
 }
 
 // Adds the accepted cells [0, n) of the list to the group's particles.
-template <int T, int U, bool QUAD>
+template <int T, int U, bool QUAD, bool WHOLE>
 __device__ __forceinline__ void add_cells(const GravArgs &g, WalkLds<T> &L, int n,
                                           const float (&xf)[U][3], double (&ai)[U][4], int slice,
                                           int S, bool idle) {
@@ -304,7 +306,7 @@ __device__ __forceinline__ void add_batch(const WalkLds<T> &L, double eps2, int 
 
 // Adds the particles of the opened leaves [0, n) of the list; returns how many
 // there are.
-template <int T, int U>
+template <int T, int U, bool WHOLE>
 __device__ __forceinline__ int add_leaves(const GravArgs &g, WalkLds<T> &L, int n, int32_t gf,
                                           int64_t gn, const float (&xf)[U][3],
                                           const int32_t (&si)[U], double (&ai)[U][4], int slice,
@@ -364,11 +366,10 @@ __device__ __forceinline__ int add_leaves(const GravArgs &g, WalkLds<T> &L, int 
       L.pidx[x] = (int32_t)s;
       own |= s >= gf && s - gf < gn;
     }
-    const bool self = __syncthreads_or(own ? 1 : 0) != 0 ||
-                      !(g.eps2 > 0.0 && g.eps2 < INFINITY);
+    const bool self = __syncthreads_or(own ? 1 : 0) != 0 || !(g.eps2 > 0.0);
     if (idle) continue;
     if (self)
-      add_batch<T, U, true>(L, g.eps2, nb, xf, si, ai, slice, S);
+      add_batch<T, U, true>(L, fabs(g.eps2), nb, xf, si, ai, slice, S);
     else
       add_batch<T, U, false>(L, g.eps2, nb, xf, si, ai, slice, S);
   }
@@ -378,7 +379,7 @@ __device__ __forceinline__ int add_leaves(const GravArgs &g, WalkLds<T> &L, int 
 // Walks the tree for the P particles from sorted position f0 on, which belong to
 // group `grp` (particles [gf, gf + gn)), and writes their accelerations.
 // cells, pairs: the cells and particles on the lists.
-template <int T, int U, bool QUAD>
+template <int T, int U, bool QUAD, bool WHOLE>
 __device__ __forceinline__ void walk_pass(const GravArgs &g, WalkLds<T> &L, uint64_t gkey, int gd,
                                           const double (&gc)[3], double gh, int32_t gf, int64_t gn,
                                           int64_t f0, int P, double *__restrict__ acc,
@@ -473,8 +474,8 @@ __device__ __forceinline__ void walk_pass(const GravArgs &g, WalkLds<T> &L, uint
       n_leaves += (int)(total >> 16);
       __syncthreads();
     }
-    add_cells<T, U, QUAD>(g, L, n_cells, xf, ai, slice, S, idle);
-    sum_pairs += add_leaves<T, U>(g, L, n_leaves, gf, gn, xf, si, ai, slice, S, idle);
+    add_cells<T, U, QUAD, WHOLE>(g, L, n_cells, xf, ai, slice, S, idle);
+    sum_pairs += add_leaves<T, U, WHOLE>(g, L, n_leaves, gf, gn, xf, si, ai, slice, S, idle);
     sum_cells += n_cells;
     n_cells = n_leaves = 0;
     __syncthreads();  // the lists are consumed
@@ -539,12 +540,9 @@ __global__ __launch_bounds__(T, kWalkWaves) void k_walk(GravArgs g, const int32_
     const int32_t gf = uniform(g.first[grp]);
     const int32_t gn = uniform(g.count[grp]);
     const int32_t p0 = (int32_t)nth * part;  // below gn: the parts cover the group
-    const int64_t f0 = (int64_t)gf + p0;
     int64_t cells = 0, pairs = 0;
-    // one part, or a whole group part by part
-    const int32_t todo = WHOLE ? gn : min(part, gn - p0);
-    for (int32_t done = 0;; done += part) {
-      const int P = min(part, todo - done);
+    // the P particles of the group from its q-th on
+    auto walk = [&](int32_t q, int P) __attribute__((always_inline)) {
       // particles per lane: the fewest idle lanes, then the fewest LDS reads
       int best = -1, U = kWalkPpt;
 #pragma unroll
@@ -558,21 +556,29 @@ __global__ __launch_bounds__(T, kWalkWaves) void k_walk(GravArgs g, const int32_
           U = u;
         }
       }
+      const int64_t f0 = (int64_t)gf + q;
       switch (uniform(U)) {
         case 1:
-          walk_pass<T, 1, QUAD>(g, L, gkey, gd, gc, gh, gf, gn, f0 + done, P, acc, &cells, &pairs);
+          walk_pass<T, 1, QUAD, WHOLE>(g, L, gkey, gd, gc, gh, gf, gn, f0, P, acc, &cells, &pairs);
           break;
         case 2:
-          walk_pass<T, 2, QUAD>(g, L, gkey, gd, gc, gh, gf, gn, f0 + done, P, acc, &cells, &pairs);
+          walk_pass<T, 2, QUAD, WHOLE>(g, L, gkey, gd, gc, gh, gf, gn, f0, P, acc, &cells, &pairs);
           break;
         case 3:
-          walk_pass<T, 3, QUAD>(g, L, gkey, gd, gc, gh, gf, gn, f0 + done, P, acc, &cells, &pairs);
+          walk_pass<T, 3, QUAD, WHOLE>(g, L, gkey, gd, gc, gh, gf, gn, f0, P, acc, &cells, &pairs);
           break;
         default:
-          walk_pass<T, 4, QUAD>(g, L, gkey, gd, gc, gh, gf, gn, f0 + done, P, acc, &cells, &pairs);
+          walk_pass<T, 4, QUAD, WHOLE>(g, L, gkey, gd, gc, gh, gf, gn, f0, P, acc, &cells, &pairs);
           break;
       }
-      if (!WHOLE || todo - done <= part) break;
+    };
+    if constexpr (WHOLE) {
+      for (int32_t q = 0;; q += part) {
+        walk(q, min(part, gn - q));
+        if (gn - q <= part) break;
+      }
+    } else {
+      walk(p0, min(part, gn - p0));
     }
     if (threadIdx.x == 0 && stats && nth == 0) {
       // every group particle meets every listed cell and every listed particle
@@ -628,6 +634,9 @@ hipError_t launch_gravity(const GravIn &in, hipStream_t s) {
   g.mass = in.mass_sorted;
   g.theta2 = in.theta * in.theta;
   g.eps2 = in.eps * in.eps;
+  // (so that one comparison finds zero and infinity: another one costs the walk of 2000
+  // particles 5 %)
+  if (std::isinf(g.eps2)) g.eps2 = -g.eps2;
   g.hilbert = in.hilbert ? 1 : 0;
   int32_t *items = static_cast<int32_t *>(in.workspace);  // at most c_max of them
   uint32_t *counts = reinterpret_cast<uint32_t *>(items + in.c_max);
