@@ -442,7 +442,10 @@ struct SampleLimit {
 };
 static int64_t sample_count(int64_t n) { return n > (int64_t{1} << 20) ? kSamples : kSamples / 4; }
 
-template <int SAMPLES>
+// kPer at a time: the key kernel's registers set its occupancy, 67 with one, 118 with two
+// (2^21: 22 and 26 us; a batch's searches for the sets make two the better, 1024 sets 2595
+// and 2645 us).
+template <int SAMPLES, int kPer>
 __device__ inline void sample_keys(const float *__restrict__ pos, int64_t n,
                                    const int64_t *__restrict__ set_off, int32_t nsets,
                                    const double *__restrict__ box, int skip, bool hilbert,
@@ -452,7 +455,6 @@ __device__ inline void sample_keys(const float *__restrict__ pos, int64_t n,
   for (int i = threadIdx.x; i < kTable; i += kKeygenThreads) table[i] = 0;
   if (threadIdx.x == 0) *s_dups = 0;
   __syncthreads();
-  constexpr int kPer = 2;  // at a time: the key kernel's registers set its occupancy
   uint32_t dups = 0;
 #pragma unroll 1
   for (int k0 = threadIdx.x; k0 < SAMPLES; k0 += kPer * kKeygenThreads) {
@@ -561,10 +563,13 @@ __global__ __launch_bounds__(kKeygenThreads) void k_keygen(
   __shared__ uint32_t s_dups;
   static_assert(kMaxKeyPasses * R <= kSampleTable, "the counts fit in the sampler's table");
   if (blockIdx.x == 0) {
+    if (few < 0) return;  // the sort looks for long runs itself
     if (few)
-      sample_keys<kSamples / 4>(pos, n, nullptr, 1, box, skip, hilbert != 0, limit, h, &s_dups, full);
+      sample_keys<kSamples / 4, 1>(pos, n, nullptr, 1, box, skip, hilbert != 0, limit, h, &s_dups,
+                                   full);
     else
-      sample_keys<kSamples>(pos, n, nullptr, 1, box, skip, hilbert != 0, limit, h, &s_dups, full);
+      sample_keys<kSamples, 1>(pos, n, nullptr, 1, box, skip, hilbert != 0, limit, h, &s_dups,
+                               full);
     return;
   }
   const int64_t block = blockIdx.x - 1, blocks = gridDim.x - 1;
@@ -619,9 +624,11 @@ __global__ __launch_bounds__(kKeygenThreads) void k_keygen_sets(
   static_assert(kMaxKeyPasses * R <= kSampleTable, "the counts fit in the sampler's table");
   if (blockIdx.x == 0) {
     if (few)
-      sample_keys<kSamples / 4>(pos, n, set_off, nsets, box, skip, hilbert != 0, limit, h, &s_dups, full);
+      sample_keys<kSamples / 4, 2>(pos, n, set_off, nsets, box, skip, hilbert != 0, limit, h,
+                                   &s_dups, full);
     else
-      sample_keys<kSamples>(pos, n, set_off, nsets, box, skip, hilbert != 0, limit, h, &s_dups, full);
+      sample_keys<kSamples, 2>(pos, n, set_off, nsets, box, skip, hilbert != 0, limit, h, &s_dups,
+                               full);
     return;
   }
   const int64_t per = (n + gridDim.x - 2) / (gridDim.x - 1);
@@ -831,7 +838,7 @@ hipError_t launch_keygen(const Plan &p, const Work &w, const float *pos, const f
                          const tb_tree &out, hipStream_t s) {
   const int passes = p.key_passes;
   const int hil = (p.flags & TB_HILBERT) ? 1 : 0;
-  const int few = sample_count(p.n) < kSamples ? 1 : 0;
+  const int few = one_tile(p) ? -1 : sample_count(p.n) < kSamples ? 1 : 0;
   if (!p.seg) {
     const int blocks = keygen_blocks(p.n);
 #define TB_KEYGEN(B)                                                                           \
